@@ -348,58 +348,56 @@ __device__ __forceinline__ int placed_block(int chunk) {
   return b;
 }
 
-template <int XGROUP = 0>
-__device__ bool cursor_begin(const BatchDesc* D, int kind, ItemCursor& c, int* s_pos) {
-  const WorkList wl = D->lists[kind];
-  int total = wl.total;
-  if (total <= 0) return false;
-  int chunk = (total + gridDim.x - 1) / gridDim.x;
-  c.item = placed_block<XGROUP>(chunk) * chunk;
-  c.end = min(c.item + chunk, total);
-  if (c.item >= c.end) return false;
-  if (threadIdx.x == 0) {
-    const int* off = D->list_off + (size_t)kind * (D->max_slots + 1);
-    int lo = 0, hi = wl.n_slots - 1;
-    while (lo < hi) {  // largest pos with off[pos] <= item
-      int mid = (lo + hi + 1) >> 1;
-      if (off[mid] <= c.item) lo = mid; else hi = mid - 1;
-    }
-    *s_pos = lo;
+// Largest position in [0, n) with off[position] <= item (off ascending, off[0] = 0), found by a
+// whole wavefront: 64 evenly spaced entries are read at once and the ballot of those not above
+// the item picks the next interval, so 4096 slots take two dependent loads where a binary
+// search takes twelve. Every wavefront of the block searches by itself: no LDS, no barrier.
+__device__ __forceinline__ int list_find(const int* off, int n, int item) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, len = n;
+  while (len > 1) {
+    const int step = (len + 63) >> 6, i = lane * step;
+    const unsigned long long le = __ballot(i < len && off[lo + min(i, len - 1)] <= item);
+    const int k = max(__popcll(le) - 1, 0);
+    lo += k * step;
+    len = min(step, len - k * step);
   }
-  __syncthreads();
-  c.pos = __builtin_amdgcn_readfirstlane(*s_pos);  // block-uniform
-  __syncthreads();
-  return true;
+  return __builtin_amdgcn_readfirstlane(lo);  // block-uniform
 }
 
 // The items [item0, item1) of one list (uniform over the block; false when empty).
-__device__ bool cursor_range(const BatchDesc* D, int kind, int item0, int item1, ItemCursor& c,
-                             int* s_pos) {
+__device__ __forceinline__ bool cursor_range(const BatchDesc* D, int kind, int item0, int item1,
+                                             ItemCursor& c) {
   if (item0 >= item1) return false;
   c.item = item0;
   c.end = item1;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int* off = D->list_off + (size_t)kind * (D->max_slots + 1);
-    int lo = 0, hi = D->lists[kind].n_slots - 1;
-    while (lo < hi) {  // largest pos with off[pos] <= item
-      int mid = (lo + hi + 1) >> 1;
-      if (off[mid] <= c.item) lo = mid; else hi = mid - 1;
-    }
-    *s_pos = lo;
-  }
-  __syncthreads();
-  c.pos = __builtin_amdgcn_readfirstlane(*s_pos);  // block-uniform
-  __syncthreads();
+  c.pos = list_find(D->list_off + (size_t)kind * (D->max_slots + 1), D->lists[kind].n_slots,
+                    item0);
   return true;
+}
+
+template <int XGROUP = 0>
+__device__ __forceinline__ bool cursor_begin(const BatchDesc* D, int kind, ItemCursor& c) {
+  const int total = D->lists[kind].total;
+  if (total <= 0) return false;
+  const int chunk = (total + gridDim.x - 1) / gridDim.x;
+  const int b0 = placed_block<XGROUP>(chunk) * chunk;
+  return cursor_range(D, kind, b0, min(b0 + chunk, total), c);
 }
 
 __device__ __forceinline__ void cursor_slot(const BatchDesc* D, int kind, ItemCursor& c,
                                             int& slot, int& local) {
   const int* off = D->list_off + (size_t)kind * (D->max_slots + 1);
-  while (c.item >= off[c.pos + 1]) c.pos++;
-  slot = D->list_slots[(size_t)kind * D->max_slots + c.pos];
-  local = c.item - off[c.pos];
+  const int* list = D->list_slots + (size_t)kind * D->max_slots;
+  int first = off[c.pos], next = off[c.pos + 1];  // with list[pos]: one round of loads
+  slot = list[c.pos];
+  while (c.item >= next) {
+    c.pos++;
+    first = next;
+    next = off[c.pos + 1];
+    slot = list[c.pos];
+  }
+  local = c.item - first;
 }
 
 __device__ __forceinline__ double* slot_partial(const BatchDesc* D, int s, int kind, int item) {
@@ -534,6 +532,7 @@ __device__ void plan_body(BatchDesc* D, PlanLds<NT>& P) {
     int tot = 0;
     for (int w = 0; w < NT / 64; ++w) tot += P.active[w];
     D->active = tot;
+    if (D->active_host) *D->active_host = tot;
   }
   if (threadIdx.x < WK_COUNT) {
     int k = threadIdx.x;
@@ -931,21 +930,20 @@ __global__ void __launch_bounds__(BLOCK, LB_ENERGY) k_energy_step(BatchDesc* D) 
   __shared__ EnergyLds<5, 3 * NC + 3> L;
   float *s_ux = L.field(0), *s_uy = L.field(1), *s_r = L.field(2), *s_dx = L.field(3),
         *s_dy = L.field(4);
-  __shared__ int s_pos;
   const int ne = D->lists[WK_EVAL].total, nl = D->lists[WK_LADDER].total;
   const int total = ne + nl;
   if (total <= 0) return;
   int chunk = (total + gridDim.x - 1) / gridDim.x;
   int b0 = placed_block<16>(chunk) * chunk, b1 = min(b0 + chunk, total);
   ItemCursor c;
-  if (b0 < ne && cursor_range(D, WK_EVAL, b0, min(b1, ne), c, &s_pos)) {
+  if (b0 < ne && cursor_range(D, WK_EVAL, b0, min(b1, ne), c)) {
     for (; c.item < c.end; ++c.item) {
       int s, t;
       cursor_slot(D, WK_EVAL, c, s, t);
       energy_item<0, 1>(D, s, t, s_ux, s_uy, s_dx, s_dy, s_r, L.buf);
     }
   }
-  if (b1 > ne && cursor_range(D, WK_LADDER, max(b0, ne) - ne, b1 - ne, c, &s_pos)) {
+  if (b1 > ne && cursor_range(D, WK_LADDER, max(b0, ne) - ne, b1 - ne, c)) {
     for (; c.item < c.end; ++c.item) {
       int s, t;
       cursor_slot(D, WK_LADDER, c, s, t);
@@ -1175,21 +1173,20 @@ __device__ __forceinline__ void grad_item(BatchDesc* D, int s, int t, GradLds<TX
 template <int TX, int TY>
 __global__ void __launch_bounds__(BLOCK, LB_GRAD) k_grad(BatchDesc* D) {
   __shared__ GradLds<TX, TY> L;
-  __shared__ int s_pos;
   const int ng = D->lists[WK_GRAD].total, np = D->lists[WK_PROLONG].total;
   const int total = ng + np;
   if (total <= 0) return;
   int chunk = (total + gridDim.x - 1) / gridDim.x;
   int b0 = placed_block<16>(chunk) * chunk, b1 = min(b0 + chunk, total);
   ItemCursor c;
-  if (b0 < ng && cursor_range(D, WK_GRAD, b0, min(b1, ng), c, &s_pos)) {
+  if (b0 < ng && cursor_range(D, WK_GRAD, b0, min(b1, ng), c)) {
     for (; c.item < c.end; ++c.item) {
       int s, t;
       cursor_slot(D, WK_GRAD, c, s, t);
       grad_item<TX, TY>(D, s, t, L);
     }
   }
-  if (b1 > ng && cursor_range(D, WK_PROLONG, max(b0, ng) - ng, b1 - ng, c, &s_pos)) {
+  if (b1 > ng && cursor_range(D, WK_PROLONG, max(b0, ng) - ng, b1 - ng, c)) {
     for (; c.item < c.end; ++c.item) {
       int s, t;
       cursor_slot(D, WK_PROLONG, c, s, t);
@@ -1490,12 +1487,11 @@ template <int DIR, bool BIG>
 __global__ void __launch_bounds__(BLOCK, DIR ? LB_SMX : LB_SMOOTH) k_smooth(BatchDesc* D) {
   extern __shared__ float s_buf[];
   __shared__ double s_red[(BLOCK / 64) * 2];
-  __shared__ int s_pos;
   const int kind = DIR ? WK_SMX : WK_SMY;
   ItemCursor c;
   // column strips: a strip of 16 lines reads and writes one half of each 128-byte line, its
   // neighbour the other half
-  if (!cursor_begin<DIR ? 0 : 16>(D, kind, c, &s_pos)) return;
+  if (!cursor_begin<DIR ? 0 : 16>(D, kind, c)) return;
   for (; c.item < c.end; ++c.item) {
     int s, t;
     cursor_slot(D, kind, c, s, t);
@@ -1551,10 +1547,9 @@ __global__ void __launch_bounds__(SW_THREADS) k_smooth_win(BatchDesc* D) {
   constexpr int PITCH = WM + 1;
   __shared__ float s[WM * PITCH];
   __shared__ double s_red[2][SW_THREADS / 64];
-  __shared__ int s_pos;
   const int tid = threadIdx.x;
   ItemCursor c;
-  if (!cursor_begin(D, WK_SMX, c, &s_pos)) return;
+  if (!cursor_begin(D, WK_SMX, c)) return;
   for (; c.item < c.end; ++c.item) {
     int sl, t;
     cursor_slot(D, WK_SMX, c, sl, t);
@@ -2219,21 +2214,20 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_energy_step(BatchDesc* D) {
   constexpr int NV = 3 * NC + 3, KG = NV < BLOCK / 16 ? NV : BLOCK / 16;
   __shared__ float s_r[NN];
   __shared__ double s_stage[KG * (BLOCK / 2)];  // the partial sums' reduction stage
-  __shared__ int s_pos;
   const int ne = D->lists[WK_EVAL].total, nl = D->lists[WK_LADDER].total;
   const int total = ne + nl;
   if (total <= 0) return;
   int chunk = (total + gridDim.x - 1) / gridDim.x;
   int b0 = blockIdx.x * chunk, b1 = min(b0 + chunk, total);
   ItemCursor c;
-  if (b0 < ne && cursor_range(D, WK_EVAL, b0, min(b1, ne), c, &s_pos)) {
+  if (b0 < ne && cursor_range(D, WK_EVAL, b0, min(b1, ne), c)) {
     for (; c.item < c.end; ++c.item) {
       int s, t;
       cursor_slot(D, WK_EVAL, c, s, t);
       rigid_energy_item<0, 1>(D, s, t, s_r, s_stage);
     }
   }
-  if (b1 > ne && cursor_range(D, WK_LADDER, max(b0, ne) - ne, b1 - ne, c, &s_pos)) {
+  if (b1 > ne && cursor_range(D, WK_LADDER, max(b0, ne) - ne, b1 - ne, c)) {
     for (; c.item < c.end; ++c.item) {
       int s, t;
       cursor_slot(D, WK_LADDER, c, s, t);
@@ -2247,9 +2241,8 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_grad(BatchDesc* D) {
   constexpr int NXN = ET_X + 1, NYN = ET_Y + 1, NN = NXN * NYN;
   __shared__ float s_r[NN];
   __shared__ double s_stage[3 * (BLOCK / 2)];  // the partial sums' reduction stage
-  __shared__ int s_pos;
   ItemCursor c;
-  if (!cursor_begin(D, WK_GRAD, c, &s_pos)) return;
+  if (!cursor_begin(D, WK_GRAD, c)) return;
   for (; c.item < c.end; ++c.item) {
     int s, t;
     cursor_slot(D, WK_GRAD, c, s, t);

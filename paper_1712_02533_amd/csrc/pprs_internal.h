@@ -140,7 +140,7 @@ struct BatchDesc {
   float* tcoef;            // per pyramid node (same offsets x 4): v, v(+x) - v, v(+y) - v,
                            // v(+x+y) - v(+y) - v(+x) + v (0 past the last row / column)
   int active;              // written by the plan kernel
-  int* active_host;        // mapped host word (may be null)
+  int* active_host;        // mapped host word the plan kernel writes too (may be null)
 };
 
 #define PW 24   // doubles per partial record (3 * MAX_CAND + 3)

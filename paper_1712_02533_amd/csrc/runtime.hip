@@ -66,6 +66,7 @@ static pprs_status fail(pprs_status s, const char* fmt, ...) {
 namespace {
 
 const int kGridFin = 512;       // finalisation: one workgroup per listed slot (grid-stride)
+const int kMaxStepGraphs = 32;  // captured step groups a context keeps
 const int kPoolSlotsDefault = 512;  // concurrent registrations of a series (pprs_set_pool)
 
 // A device buffer of a context: grown by ensure(), freed with the context unless it is a
@@ -102,6 +103,30 @@ const double kBytesPerNode[TK_COUNT] = {0.0, 12.0, 16.0, 40.0, 16.0, 24.0, 24.0,
 
 int level_n(int l) { return (1 << l) + 1; }
 
+// Workgroups of a step's launches: one per item that the active slots can have at most.
+struct StepGrid {
+  int energy, grad, smooth, fin;
+  bool operator==(const StepGrid& o) const {
+    return energy == o.energy && grad == o.grad && smooth == o.smooth && fin == o.fin;
+  }
+};
+
+// A captured group of steps: every launch's kernel and arguments follow from these values (the
+// batch descriptor's contents lie on the device and are read at replay).
+struct StepGraph {
+  StepGrid grid;
+  const void* desc;
+  int steps, nc, variant, halo, rigid;
+  bool big;
+  size_t lds[2];
+  hipGraphExec_t exec;
+  bool same(const StepGraph& o) const {
+    return grid == o.grid && desc == o.desc && steps == o.steps && nc == o.nc &&
+           variant == o.variant && halo == o.halo && rigid == o.rigid && big == o.big &&
+           lds[0] == o.lds[0] && lds[1] == o.lds[1];
+  }
+};
+
 }  // namespace
 
 struct pprs_ctx {
@@ -116,7 +141,9 @@ struct pprs_ctx {
       lists, desc, opidx;
   // scan elements [M][2][nL^2] and staging
   DevBuf elems;
-  int* active_host = nullptr;
+  int* active_host = nullptr;        // mapped host word: slots active in the last planned step
+  std::vector<StepGraph> graphs;     // captured step groups (empty where eager is set)
+  bool eager = false;                // launch every step (no graph: nothing is allocated)
   bool log = false;  // one progress line per batch on stderr (environment PPRS_LOG=1)
   pprs_cnn* cnn = nullptr;  // warm start network (not owned)
   double warm_max_cells = 8.0;
@@ -386,7 +413,7 @@ pprs_status ensure_slots(pprs_ctx* c, int cap, int L, int m0, double beta, bool 
     hd.list_slots = P<int>(c->list_slots);
     hd.list_off = P<int>(c->list_off);
     hd.lists = P<WorkList>(c->lists);
-    hd.active_host = nullptr;  // the host polls the device word instead
+    hd.active_host = c->active_host;
     // the field buffers cover cap slots of this geometry only when allocated now
     c->slots_fields = fields;
     c->slots_cap = cap;
@@ -451,7 +478,7 @@ FrameBytes frame_bytes(size_t nodes, int NT, int Nmax) {
   b.frame_off = sizeof(long long) * (size_t)NT * PPRS_MAXL;
   b.rsum = sizeof(double) * (size_t)NT * PPRS_MAXL;
   b.fr_part = sizeof(double) * 2 * (size_t)Nmax * kSumBands;
-  b.fr_ms = sizeof(double) * 2 * (size_t)Nmax * PPRS_MAXL;
+  b.fr_ms = sizeof(double) * 2 * (size_t)NT * PPRS_MAXL;
   return b;
 }
 
@@ -487,6 +514,10 @@ pprs_status prepare_series(pprs_ctx* c, const std::vector<SeriesIn>& ser) {
   hd.frame_off = P<long long>(c->frame_off);
   hd.rsum = P<double>(c->rsum);
   hd.tcoef = P<float>(c->tcoef);
+  // a series' means and deviations: one block of N pairs per level, at its first frame's place
+  auto ms_at = [](const SeriesIn& x, int l) {
+    return 2 * ((size_t)x.f0 * PPRS_MAXL + (size_t)x.N * l);
+  };
   for (const SeriesIn& x : ser) {
     int N = x.N;
     auto lvl = [&](int l) { return hd.pyr + off[(size_t)x.f0 * PPRS_MAXL + l]; };
@@ -498,24 +529,14 @@ pprs_status prepare_series(pprs_ctx* c, const std::vector<SeriesIn>& ser) {
       HIPCHK(pprs_k::restrict_planes(lvl(l), (long long)nf * nf, 0, lvl(l - 1),
                                      (long long)nc * nc, 0, 1, nf, N, c->stream));
     }
-    std::vector<double> ms(2 * (size_t)N);
     double* rs = P<double>(c->rsum) + (size_t)x.f0 * PPRS_MAXL;
     for (int l = x.m0; l <= x.L; ++l) {
       int n = level_n(l);
-      double* msd = P<double>(c->fr_ms) + 2 * (size_t)N * l;
+      double* msd = P<double>(c->fr_ms) + ms_at(x, l);
       HIPCHK(pprs_k::elem_sums(lvl(l), (long long)n * n, n, bands, N, P<double>(c->fr_part),
                                c->stream));
       HIPCHK(pprs_k::elem_final(P<double>(c->fr_part), bands, N, 0, msd, nullptr, 0, 0,
                                 c->stream));
-      HIPCHK(hipMemcpyAsync(ms.data(), msd, sizeof(double) * 2 * N, hipMemcpyDeviceToHost,
-                            c->stream));
-      HIPCHK(hipStreamSynchronize(c->stream));
-      for (int f = 0; f < N; ++f) {
-        double m = ms[2 * f], sg = ms[2 * f + 1];
-        bool is_ref = x.ref_mask ? (*x.ref_mask)[f] != 0 : f < x.n_ref;
-        if (sg <= 1e-12 * std::max(1.0, fabs(m)) && is_ref)
-          return fail(PPRS_EINVAL, "reference frame %d is constant on level %d", f, l);
-      }
       HIPCHK(pprs_k::normalize(lvl(l), (long long)n * n, (long long)n * n, N, msd, c->stream));
       HIPCHK(pprs_k::tcoef(lvl(l), n, N, hd.tcoef + 4 * off[(size_t)x.f0 * PPRS_MAXL + l],
                            c->stream));
@@ -525,6 +546,22 @@ pprs_status prepare_series(pprs_ctx* c, const std::vector<SeriesIn>& ser) {
                                 c->stream));
     }
   }
+  // the frames' means and deviations of every series and level come back in one wait (a
+  // constant frame has been left as it was)
+  std::vector<double> ms(2 * (size_t)NT * PPRS_MAXL);
+  for (const SeriesIn& x : ser)
+    HIPCHK(hipMemcpyAsync(ms.data() + ms_at(x, x.m0), P<double>(c->fr_ms) + ms_at(x, x.m0),
+                          sizeof(double) * 2 * x.N * (x.L - x.m0 + 1), hipMemcpyDeviceToHost,
+                          c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
+  for (const SeriesIn& x : ser)
+    for (int l = x.m0; l <= x.L; ++l)
+      for (int f = 0; f < x.N; ++f) {
+        const double* v = ms.data() + ms_at(x, l) + 2 * f;
+        bool is_ref = x.ref_mask ? (*x.ref_mask)[f] != 0 : f < x.n_ref;
+        if (v[1] <= 1e-12 * std::max(1.0, fabs(v[0])) && is_ref)
+          return fail(PPRS_EINVAL, "reference frame %d is constant on level %d", f, l);
+      }
   return PPRS_OK;
 }
 
@@ -592,44 +629,145 @@ long long ladder_pass_bound(const pprs_params* p, int nc) {
   return groups * G / nc + groups + 2;
 }
 
+// Most items a slot whose registration ends on level l can have in one launch per kernel kind
+// (a slot is in one list of a launch at a time).
+struct SlotItems {
+  long long energy = 0, grad = 0, smooth = 0;
+};
+SlotItems slot_items(const BatchDesc& hd, int l_stop) {
+  SlotItems m;
+  for (int l = hd.coarsest; l <= l_stop; ++l) {
+    const LevelGeom& g = hd.geom[l];
+    m.energy = std::max<long long>(m.energy, g.tiles_elem);
+    m.grad = std::max<long long>(m.grad, std::max(g.tiles_grad, g.tiles_prol));
+    m.smooth = std::max<long long>(
+        m.smooth, hd.smooth_halo ? 2LL * g.sw_tiles * g.sw_tiles : 2LL * g.sm_items);
+  }
+  return m;
+}
+
+// Launch grids for a step whose slots have at most these items: the tuned grid, or as many
+// workgroups as there can be items where that is fewer (a power of two of at least 128, which
+// the XCD placement of items needs; few distinct shapes, so few captured graphs). A workgroup
+// without an item still costs its dispatch: 8192 of them 2 us a launch, measured with one 64 x
+// 64 pair (launches of the empty kernels 3.2 us at 8192 workgroups, 1.6 us at 128).
+StepGrid step_grid(const pprs_ctx* c, const SlotItems& items, int slots) {
+  auto fit = [](int cfg, long long n) {
+    long long g = 128;
+    while (g < n && g < cfg) g *= 2;
+    return (int)std::min<long long>(g, cfg);
+  };
+  int fin = 1;
+  while (fin < slots && fin < kGridFin) fin *= 2;
+  return StepGrid{fit(c->grid_energy, items.energy), fit(c->grid_grad, items.grad),
+                  fit(c->grid_smooth, items.smooth), fin};
+}
+
 // One step of every active slot: plan, gradient (with the prolongations of slots that
 // finished a level), metric solve, line search.
-pprs_status launch_step(pprs_ctx* c, BatchDesc* d, int nc) {
+pprs_status launch_step(pprs_ctx* c, BatchDesc* d, int nc, const StepGrid& g) {
   size_t lds0 = c->lds_smooth[0], lds1 = c->lds_smooth[1];
   TIMED(TK_PLAN, pprs_k::plan(d, c->stream));
-  TIMED(TK_GRAD, pprs_k::grad(d, grad_variant(c->tile_grad), c->grid_grad, c->stream));
+  TIMED(TK_GRAD, pprs_k::grad(d, grad_variant(c->tile_grad), g.grad, c->stream));
   if (c->hd.smooth_halo) {
-    TIMED(TK_SMW, pprs_k::smooth_win(d, c->hd.smooth_halo, c->grid_smooth, c->stream));
+    TIMED(TK_SMW, pprs_k::smooth_win(d, c->hd.smooth_halo, g.smooth, c->stream));
   } else {
     bool big = level_n(c->hd.finest) > 9 * 64;  // lines longer than 9 nodes per lane
-    TIMED(TK_SMY, pprs_k::smooth(d, 0, big, c->grid_smooth, lds0, c->stream));
-    TIMED(TK_SMX, pprs_k::smooth(d, 1, big, c->grid_smooth, lds1, c->stream));
+    TIMED(TK_SMY, pprs_k::smooth(d, 0, big, g.smooth, lds0, c->stream));
+    TIMED(TK_SMX, pprs_k::smooth(d, 1, big, g.smooth, lds1, c->stream));
   }
-  TIMED(TK_FIN, pprs_k::smooth_fin(d, kGridFin, c->stream));
+  TIMED(TK_FIN, pprs_k::smooth_fin(d, g.fin, c->stream));
   // start energies of the slots that begin a level and the line-search passes, one launch
-  TIMED(TK_LADDER, pprs_k::energy_step(d, nc, c->grid_energy, c->stream));
-  TIMED(TK_FIN, pprs_k::energy_step_fin(d, nc, kGridFin, c->stream));
+  TIMED(TK_LADDER, pprs_k::energy_step(d, nc, g.energy, c->stream));
+  TIMED(TK_FIN, pprs_k::energy_step_fin(d, nc, g.fin, c->stream));
   return PPRS_OK;
+}
+
+// One step of the rigid variant: the parameter gradient with its finaliser, then in one launch
+// the start energies of the slots that begin a level and the line-search passes (a slot that
+// begins a level iterates from the next step on, as the plan lists it), and the finaliser the
+// field path uses.
+pprs_status launch_step_rigid(pprs_ctx* c, BatchDesc* d, int nc, const StepGrid& g) {
+  TIMED(TK_PLAN, pprs_k::plan(d, c->stream));
+  TIMED(TK_GRAD, pprs_k::rigid_grad(d, g.grad, c->stream));
+  TIMED(TK_FIN, pprs_k::rigid_grad_fin(d, g.fin, c->stream));
+  // start energies of the slots that begin a level and the line-search passes, one launch
+  TIMED(TK_LADDER, pprs_k::rigid_energy_step(d, nc, g.energy, c->stream));
+  TIMED(TK_FIN, pprs_k::energy_step_fin(d, nc, g.fin, c->stream));
+  return PPRS_OK;
+}
+
+// Runs `steps` steps of the batch descriptor's slots. They always launch the same kernels with
+// the same arguments (all per-slot state lives on the device), so a group is captured once and
+// replayed, in this call and in later ones of the same launch shape (a context keeps at most
+// kMaxStepGraphs groups); with per-launch timing events, or in a context that must not
+// allocate, the steps launch one by one.
+pprs_status run_steps(pprs_ctx* c, BatchDesc* d, int steps, int nc, const StepGrid& g) {
+  const bool rigid = c->hd.rigid != 0;
+  auto launch = [&]() -> pprs_status {
+    for (int k = 0; k < steps; ++k)
+      STCHK(rigid ? launch_step_rigid(c, d, nc, g) : launch_step(c, d, nc, g));
+    return PPRS_OK;
+  };
+  if (c->timing || c->eager) return launch();
+  StepGraph key{g, d, steps, nc, grad_variant(c->tile_grad), c->hd.smooth_halo,
+                rigid ? 1 : 0, level_n(c->hd.finest) > 9 * 64,
+                {c->lds_smooth[0], c->lds_smooth[1]}, nullptr};
+  if (rigid) key.variant = key.halo = key.big = 0, key.lds[0] = key.lds[1] = 0;
+  for (const StepGraph& e : c->graphs)
+    if (e.same(key)) {
+      HIPCHK(hipGraphLaunch(e.exec, c->stream));
+      return PPRS_OK;
+    }
+  if ((int)c->graphs.size() >= kMaxStepGraphs) {
+    HIPCHK(hipStreamSynchronize(c->stream));
+    for (StepGraph& e : c->graphs) (void)hipGraphExecDestroy(e.exec);
+    c->graphs.clear();
+  }
+  hipGraph_t graph = nullptr;
+  HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+  pprs_status cs = launch();
+  hipError_t ce = hipStreamEndCapture(c->stream, &graph);
+  if (cs != PPRS_OK) {
+    if (graph) (void)hipGraphDestroy(graph);
+    return cs;
+  }
+  if (ce != hipSuccess) return fail(PPRS_EHIP, "graph capture failed: %s", hipGetErrorString(ce));
+  hipError_t ie = hipGraphInstantiate(&key.exec, graph, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(graph);
+  if (ie != hipSuccess)
+    return fail(PPRS_EHIP, "graph instantiation failed: %s", hipGetErrorString(ie));
+  c->graphs.push_back(key);
+  HIPCHK(hipGraphLaunch(key.exec, c->stream));
+  return PPRS_OK;
+}
+
+// Runs groups of steps until no slot is active: 8 steps, then 8, 16 and 32 at a time, each
+// followed by one wait (the plan of every step writes the number of active slots to a mapped
+// host word, or the host copies it where there is none).
+pprs_status run_until_done(pprs_ctx* c, BatchDesc* d, int nc, const StepGrid& g,
+                           long long max_steps, long long* done_steps) {
+  const int kGroup = 8;
+  for (int reps = 1, polls = 0;; ++polls) {
+    for (int k = 0; k < reps; ++k) STCHK(run_steps(c, d, kGroup, nc, g));
+    *done_steps += (long long)reps * kGroup;
+    int active = 0;
+    if (!c->active_host)
+      HIPCHK(hipMemcpyAsync(&active, &d->active, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    if (c->active_host) active = *(volatile int*)c->active_host;
+    if (c->timing) STCHK(tk_collect(c));
+    if (active == 0) return PPRS_OK;
+    if (*done_steps > max_steps)
+      return fail(PPRS_ESTATE, "batch did not finish within %lld steps", max_steps);
+    if (polls > 0) reps = std::min(reps * 2, 4);
+  }
 }
 
 // INIT_RESUME: the op continues, on its start level, a result another op left on the level
 // below (copied in, then prolongated by the state machine as between two levels).
 enum InitKind { INIT_IDENTITY = 0, INIT_COMPOSE = 1, INIT_GIVEN = 2, INIT_PREPARED = 3,
                 INIT_RESUME = 4 };
-
-// One step of the rigid variant: the parameter gradient with its finaliser, then in one launch
-// the start energies of the slots that begin a level and the line-search passes (a slot that
-// begins a level iterates from the next step on, as the plan lists it), and the finaliser the
-// field path uses.
-pprs_status launch_step_rigid(pprs_ctx* c, BatchDesc* d, int nc) {
-  TIMED(TK_PLAN, pprs_k::plan(d, c->stream));
-  TIMED(TK_GRAD, pprs_k::rigid_grad(d, c->grid_grad, c->stream));
-  TIMED(TK_FIN, pprs_k::rigid_grad_fin(d, kGridFin, c->stream));
-  // start energies of the slots that begin a level and the line-search passes, one launch
-  TIMED(TK_LADDER, pprs_k::rigid_energy_step(d, nc, c->grid_energy, c->stream));
-  TIMED(TK_FIN, pprs_k::energy_step_fin(d, nc, kGridFin, c->stream));
-  return PPRS_OK;
-}
 
 // Runs n slots (reference ref[s], template tmpl[s]) to completion and writes each result
 // (domain units, [2][nL][nL]) to elems[out_idx[s]]. INIT_COMPOSE composes elems[left[s]]
@@ -710,19 +848,11 @@ pprs_status run_batch(pprs_ctx* c, int n, const int* ref, const int* tmpl, InitK
   long long max_steps =
       (long long)p->levels * ((long long)p->iter_max + 2) * (passes_per_iter + 2) + 64;
   long long done_steps = 0;
-  int group = 4;
-  while (true) {
-    for (int k = 0; k < group; ++k) STCHK(launch_step(c, d, nc));
-    done_steps += group;
-    int active = 0;
-    HIPCHK(hipMemcpyAsync(&active, &d->active, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    if (c->timing) STCHK(tk_collect(c));
-    if (active == 0) break;
-    if (done_steps > max_steps)
-      return fail(PPRS_ESTATE, "batch did not finish within %lld steps", max_steps);
-    group = std::min(group * 2, 32);
-  }
+  SlotItems items = slot_items(hd, L);
+  items.energy *= n;
+  items.grad *= n;
+  items.smooth *= n;
+  STCHK(run_until_done(c, d, nc, step_grid(c, items, n), max_steps, &done_steps));
   HIPCHK(pprs_k::finish(d, didx + 2 * n, elems, est, (long long)n * est, c->stream));
   if (c->log) {
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -878,13 +1008,6 @@ struct PoolSpec {
   int stage_level = -1;
 };
 
-struct GraphExec {
-  hipGraphExec_t exec = nullptr;
-  ~GraphExec() {
-    if (exec) (void)hipGraphExecDestroy(exec);
-  }
-};
-
 // Bytes of one poll's packed upload for a pool of S slots: at most S finished slots (slot and
 // version offset each), S starting registrations (staged state and slot) and their initial-
 // guess lists (slot, stage index, two version offsets), every list 8-byte aligned, with one
@@ -1007,26 +1130,8 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
   std::vector<long long> lst_o0(S), lst_o1(S);
   std::vector<SlotState> h_states(S);
   int G = std::max(1, c->pool_group);
-  // the G steps between polls always launch the same kernels with the same arguments (all
-  // per-slot state lives on the device): one captured graph replays them, unless per-launch
-  // timing events are wanted
-  GraphExec graph;
-  if (!c->timing) {
-    hipGraph_t g = nullptr;
-    HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    pprs_status cs = PPRS_OK;
-    for (int k = 0; k < G && cs == PPRS_OK; ++k) cs = launch_step(c, d, nc);
-    hipError_t ce = hipStreamEndCapture(c->stream, &g);
-    if (cs != PPRS_OK) {
-      if (g) (void)hipGraphDestroy(g);
-      return cs;
-    }
-    if (ce != hipSuccess) return fail(PPRS_EHIP, "graph capture failed: %s", hipGetErrorString(ce));
-    hipError_t ie = hipGraphInstantiate(&graph.exec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (ie != hipSuccess)
-      return fail(PPRS_EHIP, "graph instantiation failed: %s", hipGetErrorString(ie));
-  }
+  std::vector<SlotItems> level_items(Lmax + 1);
+  for (int l = m0min; l <= Lmax; ++l) level_items[l] = slot_items(hd, l);
   // The finished slots' results go to their versions (grouped by finest level) before the
   // slots are handed to new registrations: those lists open the next upload.
   auto launch_finish = [&]() -> pprs_status {
@@ -1164,12 +1269,18 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
           HIPCHK(pprs_k::pool_restrict(d, l, level_n(l - 1), ds, cnt, c->stream));
       }
     }
-    // 2. step every slot G times
-    if (graph.exec) {
-      HIPCHK(hipGraphLaunch(graph.exec, c->stream));
-    } else {
-      for (int k = 0; k < G; ++k) STCHK(launch_step(c, d, nc));
+    // 2. step every slot G times, on grids for the slots in use
+    SlotItems items;
+    int busy = 0;
+    for (int s = 0; s < S; ++s) {
+      if (slot_op[s] < 0) continue;
+      const SlotItems& m = level_items[ops[slot_op[s]].stop_level()];
+      items.energy += m.energy;
+      items.grad += m.grad;
+      items.smooth += m.smooth;
+      ++busy;
     }
+    STCHK(run_steps(c, d, G, nc, step_grid(c, items, busy)));
     done_steps += G;
     // 3. poll: retire finished slots, release their dependents
     HIPCHK(hipMemcpyAsync(st.data(), hd.state, sizeof(SlotState) * S, hipMemcpyDeviceToHost,
@@ -1512,6 +1623,7 @@ void pprs_destroy(pprs_ctx* c) {
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
+  for (StepGraph& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   if (c->active_host) (void)hipHostFree(c->active_host);
   if (c->own_stream) (void)hipStreamDestroy(c->stream);
   delete c;  // every DevBuf frees its device memory
@@ -1627,6 +1739,7 @@ pprs_status pprs_register_pair_noalloc(pprs_ctx* c, const float* f_ref, const fl
   memset(&w.hd, 0, sizeof(BatchDesc));
   w.device = c->device;
   w.stream = c->stream;
+  w.eager = true;
   w.log = c->log;
   w.grid_energy = c->grid_energy;
   w.grid_grad = c->grid_grad;
@@ -1738,22 +1851,13 @@ pprs_status run_batch_rigid(pprs_ctx* c, int n, const int* ref, const int* tmpl,
   long long max_steps = (long long)p->levels * ((long long)p->iter_max + 2) *
                             (ladder_pass_bound(p, nc) + 2) + 64;
   long long done_steps = 0;
-  int group = 4;
-  while (true) {
-    for (int k = 0; k < group; ++k) STCHK(launch_step_rigid(c, d, nc));
-    done_steps += group;
-    int active = 0;
-    HIPCHK(hipMemcpyAsync(&active, &d->active, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    if (c->timing) STCHK(tk_collect(c));
-    if (active == 0) break;
-    if (done_steps > max_steps) {
-      hd.rigid = 0;
-      return fail(PPRS_ESTATE, "rigid batch did not finish within %lld steps", max_steps);
-    }
-    group = std::min(group * 2, 32);
-  }
+  SlotItems items = slot_items(hd, L);
+  items.energy *= n;
+  items.grad *= n;
+  items.smooth = 0;
+  pprs_status rs = run_until_done(c, d, nc, step_grid(c, items, n), max_steps, &done_steps);
   hd.rigid = 0;
+  STCHK(rs);
   HIPCHK(hipMemcpyAsync(st.data(), hd.state, sizeof(SlotState) * n, hipMemcpyDeviceToHost,
                         c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
