@@ -296,7 +296,8 @@ __device__ __forceinline__ float* slot_u(const BatchDesc* D, int s, int l, int b
 __device__ __forceinline__ void load_head(SlotState& dst, const SlotState& src) {
   dst.phase = src.phase; dst.level = src.level; dst.ub = src.ub; dst.iter = src.iter;
   dst.flags = src.flags; dst.ref = src.ref; dst.tmpl = src.tmpl; dst.finest = src.finest;
-  dst.coarsest = src.coarsest; dst.rung = src.rung; dst.E = src.E; dst.ncc = src.ncc; dst.mean = src.mean;
+  dst.coarsest = src.coarsest; dst.rung = src.rung;
+  dst.roff = src.roff; dst.toff = src.toff; dst.rs = src.rs; dst.E = src.E; dst.ncc = src.ncc; dst.mean = src.mean;
   dst.sigma = src.sigma; dst.tau_prev = src.tau_prev; dst.top = src.top;
   dst.tau_max = src.tau_max; dst.tau_pend = src.tau_pend; dst.gtd = src.gtd; dst.dmax = src.dmax;
   for (int k = 0; k < 3; ++k) {
@@ -310,6 +311,12 @@ __device__ __forceinline__ void store_head(SlotState& dst, const SlotState& src)
 
 __device__ __forceinline__ void level_done(SlotState& st) {
   st.phase = st.level < st.finest ? PH_PROLONG : PH_DONE;
+}
+// A slot that finished a level works on the next one's frames from here on.
+__device__ __forceinline__ void next_frames(const BatchDesc* D, SlotState& st) {
+  if (st.phase != PH_PROLONG) return;
+  st.roff = D->frame_off[(size_t)st.ref * PPRS_MAXL + st.level + 1];
+  st.toff = D->frame_off[(size_t)st.tmpl * PPRS_MAXL + st.level + 1];
 }
 
 // Items of a kind for a slot whose effective level is l.
@@ -334,10 +341,6 @@ __device__ __forceinline__ int kind_items(const BatchDesc* D, int kind, int l) {
 // [0, gridDim.x) when gridDim.x is a multiple of 8 XGROUP. Neighbouring items that read two
 // halves of the same 128-byte lines then fetch them into one L2.
 
-struct ItemCursor {
-  int item, end, pos;
-};
-
 template <int XGROUP>
 __device__ __forceinline__ int placed_block(int chunk) {
   int b = blockIdx.x;
@@ -348,56 +351,103 @@ __device__ __forceinline__ int placed_block(int chunk) {
   return b;
 }
 
-// Largest position in [0, n) with off[position] <= item (off ascending, off[0] = 0), found by a
-// whole wavefront: 64 evenly spaced entries are read at once and the ballot of those not above
-// the item picks the next interval, so 4096 slots take two dependent loads where a binary
-// search takes twelve. Every wavefront of the block searches by itself: no LDS, no barrier.
-__device__ __forceinline__ int list_find(const int* off, int n, int item) {
+// What every step kernel begins with is a chain of dependent loads, each from beyond the L2 (a
+// kernel's first reads of what the one before wrote): with one 64 x 64 pair a launch spent 4 of
+// its 7 us on it. So the descriptor comes as a kernel argument, the head of a list with its
+// first entries, and the slot's state next.
+
+__device__ __forceinline__ ListEntry* list_of(const BatchDesc* D, int kind) {
+  return D->lists + (size_t)kind * (D->max_slots + LIST_PAD);
+}
+
+// Position in a list: the slot of the current item and the offsets its items lie between.
+struct ItemCursor {
+  int pos, slot, first, next;
+};
+
+// Moves to `item` of the list at e (n slots; v: the caller's lane's entry e[1 + lane]). 64
+// entries are compared at once and the ballot of those not above the item picks the slot; a
+// list of more than 63 slots first narrows to a stretch of 63, with one more load per factor of
+// 64. Every wavefront does it by itself: no LDS, no barrier.
+__device__ __forceinline__ void list_seek(const ListEntry* e, int n, ListEntry v, int item,
+                                          ItemCursor& c) {
   const int lane = threadIdx.x & 63;
   int lo = 0, len = n;
-  while (len > 1) {
-    const int step = (len + 63) >> 6, i = lane * step;
-    const unsigned long long le = __ballot(i < len && off[lo + min(i, len - 1)] <= item);
-    const int k = max(__popcll(le) - 1, 0);
-    lo += k * step;
-    len = min(step, len - k * step);
+  if (n > 63) {
+    while (len > 63) {
+      const int step = (len + 63) >> 6, i = lane * step;
+      const unsigned long long le =
+          __ballot(i < len && e[1 + lo + min(i, len - 1)].off <= item);
+      const int k = max(__popcll(le) - 1, 0);
+      lo += k * step;
+      len = min(step, len - k * step);
+    }
+    v = e[1 + lo + min(lane, len)];
   }
-  return __builtin_amdgcn_readfirstlane(lo);  // block-uniform
+  const int k = max(__popcll(__ballot(lane < len && v.off <= item)) - 1, 0);
+  c.pos = lo + k;
+  c.slot = __builtin_amdgcn_readlane(v.slot, k);
+  c.first = __builtin_amdgcn_readlane(v.off, k);
+  c.next = __builtin_amdgcn_readlane(v.off, k + 1);
 }
 
-// The items [item0, item1) of one list (uniform over the block; false when empty).
-__device__ __forceinline__ bool cursor_range(const BatchDesc* D, int kind, int item0, int item1,
-                                             ItemCursor& c) {
-  if (item0 >= item1) return false;
-  c.item = item0;
-  c.end = item1;
-  c.pos = list_find(D->list_off + (size_t)kind * (D->max_slots + 1), D->lists[kind].n_slots,
-                    item0);
-  return true;
-}
-
-template <int XGROUP = 0>
-__device__ __forceinline__ bool cursor_begin(const BatchDesc* D, int kind, ItemCursor& c) {
-  const int total = D->lists[kind].total;
-  if (total <= 0) return false;
-  const int chunk = (total + gridDim.x - 1) / gridDim.x;
-  const int b0 = placed_block<XGROUP>(chunk) * chunk;
-  return cursor_range(D, kind, b0, min(b0 + chunk, total), c);
-}
-
-__device__ __forceinline__ void cursor_slot(const BatchDesc* D, int kind, ItemCursor& c,
-                                            int& slot, int& local) {
-  const int* off = D->list_off + (size_t)kind * (D->max_slots + 1);
-  const int* list = D->list_slots + (size_t)kind * D->max_slots;
-  int first = off[c.pos], next = off[c.pos + 1];  // with list[pos]: one round of loads
-  slot = list[c.pos];
-  while (c.item >= next) {
+// Moves on to `item`, at or after the current one.
+__device__ __forceinline__ void list_advance(const ListEntry* e, int item, ItemCursor& c) {
+  while (item >= c.next) {
     c.pos++;
-    first = next;
-    next = off[c.pos + 1];
-    slot = list[c.pos];
+    c.first = c.next;
+    c.slot = __builtin_amdgcn_readfirstlane(e[1 + c.pos].slot);
+    c.next = __builtin_amdgcn_readfirstlane(e[2 + c.pos].off);
   }
-  local = c.item - first;
+}
+
+// Calls fn(slot, local item) for this workgroup's items of one list.
+template <int XGROUP, class F>
+__device__ __forceinline__ void list_items(const BatchDesc* D, int kind, F fn) {
+  const ListEntry* e = list_of(D, kind);
+  const ListEntry head = e[0], v = e[1 + (threadIdx.x & 63)];
+  const int total = __builtin_amdgcn_readfirstlane(head.off);
+  if (total <= 0) return;
+  const int chunk = (total + gridDim.x - 1) / gridDim.x;
+  const int b0 = placed_block<XGROUP>(chunk) * chunk, b1 = min(b0 + chunk, total);
+  if (b0 >= b1) return;
+  ItemCursor c;
+  list_seek(e, __builtin_amdgcn_readfirstlane(head.slot), v, b0, c);
+  for (int item = b0; item < b1; ++item) {
+    list_advance(e, item, c);
+    fn(c.slot, item - c.first);
+  }
+}
+
+// The same over the items of two lists, one item space made of both in that order.
+template <int XGROUP, class FA, class FB>
+__device__ __forceinline__ void two_list_items(const BatchDesc* D, int kind_a, int kind_b, FA fa,
+                                               FB fb) {
+  const ListEntry *ea = list_of(D, kind_a), *eb = list_of(D, kind_b);
+  const int lane = threadIdx.x & 63;
+  const ListEntry ha = ea[0], hb = eb[0], va = ea[1 + lane], vb = eb[1 + lane];
+  const int na = __builtin_amdgcn_readfirstlane(ha.off);
+  const int total = na + __builtin_amdgcn_readfirstlane(hb.off);
+  if (total <= 0) return;
+  const int chunk = (total + gridDim.x - 1) / gridDim.x;
+  const int b0 = placed_block<XGROUP>(chunk) * chunk, b1 = min(b0 + chunk, total);
+  if (b0 >= b1) return;
+  ItemCursor c;
+  if (b0 < na) {
+    list_seek(ea, __builtin_amdgcn_readfirstlane(ha.slot), va, b0, c);
+    for (int item = b0; item < min(b1, na); ++item) {
+      list_advance(ea, item, c);
+      fa(c.slot, item - c.first);
+    }
+  }
+  if (b1 > na) {
+    const int i0 = max(b0, na) - na;
+    list_seek(eb, __builtin_amdgcn_readfirstlane(hb.slot), vb, i0, c);
+    for (int item = i0; item < b1 - na; ++item) {
+      list_advance(eb, item, c);
+      fb(c.slot, item - c.first);
+    }
+  }
 }
 
 __device__ __forceinline__ double* slot_partial(const BatchDesc* D, int s, int kind, int item) {
@@ -405,10 +455,19 @@ __device__ __forceinline__ double* slot_partial(const BatchDesc* D, int s, int k
          (size_t)item * PW;
 }
 
+// Partials of the metric solve (row strips or windows): G.d and max |d| of item t, each in a
+// dense array of its own, so that a wavefront reads a slot's values in whole lines (the energy
+// pass takes the maximum in every tile).
+__device__ __forceinline__ double* slot_gd(const BatchDesc* D, int s) {
+  return slot_partial(D, s, WK_SMX, 0);
+}
+__device__ __forceinline__ float* slot_dm(const BatchDesc* D, int s) {
+  return reinterpret_cast<float*>(slot_gd(D, s) + D->part_kind_stride / PW);
+}
+
 // Fixed-order sum of NV columns over n_items partial records; result in thread 0's out[].
 // (Compile-time NV keeps out[] in registers; a record's NV loads are issued together.)
-// partials_local: each thread's share (records threadIdx.x, + BLOCK, ...); sum_partials: that
-// and the block reduction.
+// partials_local: each thread's share (records threadIdx.x, + BLOCK, ...); block_sum reduces.
 template <int NV>
 __device__ __forceinline__ void partials_local(const BatchDesc* D, int s, int kind, int n_items,
                                                double (&out)[NV], bool max_last) {
@@ -426,17 +485,11 @@ __device__ __forceinline__ void partials_local(const BatchDesc* D, int s, int ki
     }
   }
 }
-template <int NV>
-__device__ __forceinline__ void sum_partials(const BatchDesc* D, int s, int kind, int n_items,
-                                             double (&out)[NV], double* scratch, bool max_last) {
-  partials_local<NV>(D, s, kind, n_items, out, max_last);
-  block_sum<NV>(out, scratch, max_last);
-}
-
 // ------------------------------------------------------------------------------------------
 // Planning kernel: one workgroup of PLAN_T threads, a slot per thread and round.
 
 #define PLAN_T 512
+// scanned per kind: membership and items
 #define PLAN_V (2 * WK_COUNT)
 template <int NT>
 struct PlanLds {
@@ -464,13 +517,13 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
 // of their item counts. The item counts per level come from a table in LDS (filled while the
 // slot states load); wave-level DPP scans, then a scan over the wave totals.
 template <int NT>
-__device__ void plan_body(BatchDesc* D, PlanLds<NT>& P) {
+__device__ void plan_body(const BatchDesc* D, PlanLds<NT>& P) {
   int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int n_slots = D->n_slots;
   int active = 0;
   if (threadIdx.x < PLAN_V) P.carry[threadIdx.x] = 0;
-  if (threadIdx.x < PPRS_MAXL * WK_COUNT) {
-    int l = threadIdx.x / WK_COUNT, k = threadIdx.x - l * WK_COUNT;
+  for (int i = threadIdx.x; i < PPRS_MAXL * WK_COUNT; i += NT) {
+    int l = i / WK_COUNT, k = i - l * WK_COUNT;
     P.items[l][k] = (l >= D->coarsest && l <= D->finest) ? kind_items(D, k, l) : 0;
   }
   for (int base = 0; base < n_slots; base += NT) {
@@ -520,39 +573,40 @@ __device__ void plan_body(BatchDesc* D, PlanLds<NT>& P) {
       if (val[2 * k]) {
         int pos = P.woff[wv][2 * k] + inc[2 * k] - 1;
         int off = P.woff[wv][2 * k + 1] + inc[2 * k + 1] - val[2 * k + 1];
-        D->list_slots[(size_t)k * D->max_slots + pos] = s;
-        D->list_off[(size_t)k * (D->max_slots + 1) + pos] = off;
+        list_of(D, k)[1 + pos] = ListEntry{off, s};
       }
     }
   }
-  for (int o = 32; o > 0; o >>= 1) active += __shfl_down(active, o, 64);
-  if (lane == 0) P.active[wv] = active;
+  active = wave_scan_incl(active);  // lane 63: the wave's total
+  if (lane == 63) P.active[wv] = active;
   __syncthreads();
   if (threadIdx.x == 0) {
     int tot = 0;
     for (int w = 0; w < NT / 64; ++w) tot += P.active[w];
-    D->active = tot;
+    *D->active = tot;
     if (D->active_host) *D->active_host = tot;
   }
   if (threadIdx.x < WK_COUNT) {
     int k = threadIdx.x;
     int cnt = P.carry[2 * k], items = P.carry[2 * k + 1];
-    D->list_off[(size_t)k * (D->max_slots + 1) + cnt] = items;
-    D->lists[k].n_slots = cnt;
-    D->lists[k].total = items;
+    ListEntry* e = list_of(D, k);
+    e[0] = ListEntry{items, cnt};
+    e[1 + cnt] = ListEntry{items, 0};
   }
 }
 
-__global__ void __launch_bounds__(PLAN_T) k_plan(BatchDesc* D) {
-  __shared__ PlanLds<PLAN_T> P;
-  plan_body<PLAN_T>(D, P);
+// A pool of at most 64 slots is planned by one wavefront, whose barriers cost nothing.
+template <int NT>
+__global__ void __launch_bounds__(NT) k_plan(const BatchDesc Dv) {
+  __shared__ PlanLds<NT> P;
+  plan_body<NT>(&Dv, P);
 }
 
 // ------------------------------------------------------------------------------------------
 // Prolongation of u (level l -> l+1) with the pending step applied: u_l - tau_pend d.
 
 // One prolongation item: fine-level tile t of slot s.
-__device__ __forceinline__ void prolong_item(BatchDesc* D, int s, int t) {
+__device__ __forceinline__ void prolong_item(const BatchDesc* D, int s, int t) {
   {
     const SlotState& st = D->state[s];
     if (st.phase != PH_PROLONG) return;
@@ -624,10 +678,10 @@ __device__ __forceinline__ void ke_apply(const float u[4], float out[4]) {
 // store would otherwise wait for it); only the slot's own finaliser writes them within a launch.
 struct FinOperands {
   double rsum;
-  long long nodes_kind, nodes_prol;
+  long long nodes_kind, nodes_prol, nodes_grad, nodes_smy, nodes_smx;
   int eval_only, passes;
-  double sigma, tau_min_rel, eps;
-  int iter_max, rigid;
+  double sigma, tau_min_rel, eps, step_cap;
+  int iter_max, rigid, ladder_k, halo;
   unsigned char* dlog;
 };
 template <int MODE>
@@ -636,23 +690,61 @@ __device__ __forceinline__ void load_fin_operands(const BatchDesc* D, const Slot
                                                   FinOperands& fo) {
   const int kind = MODE ? WK_LADDER : WK_EVAL;
   const long long* nc_s = D->node_count + (size_t)s * WK_COUNT;
-  fo.rsum = D->rsum[(size_t)st.ref * PPRS_MAXL + l];
+  fo.rsum = MODE ? st.rs : D->rsum[(size_t)st.ref * PPRS_MAXL + l];
   fo.nodes_kind = nc_s[kind];
   fo.nodes_prol = MODE ? 0 : nc_s[WK_PROLONG];
+  fo.nodes_grad = MODE ? nc_s[WK_GRAD] : 0;
+  fo.nodes_smy = MODE ? nc_s[WK_SMY] : 0;
+  fo.nodes_smx = MODE ? nc_s[WK_SMX] : 0;
   fo.eval_only = MODE ? 0 : stp->eval_only;
   fo.passes = MODE ? stp->passes[st.level - st.coarsest] : 0;
   fo.sigma = D->sigma;
   fo.tau_min_rel = D->tau_min_rel;
   fo.eps = D->eps;
+  fo.step_cap = D->step_cap;
+  fo.ladder_k = D->ladder_k;
+  fo.halo = D->smooth_halo;
   fo.iter_max = D->iter_max;
   fo.rigid = D->rigid;
   fo.dlog = D->dlog;
 }
 
+// The line search of a new direction d: the step bound tau_max = cap h / max|d| and the first
+// step of the ladder.
+__device__ __forceinline__ double ladder_top(double step_cap, int n, double dmax, double tau_prev,
+                                             int ladder_k, double* tau_max) {
+  double h = 1.0 / (n - 1);
+  *tau_max = step_cap * h / dmax;
+  return fmin(ldexp(tau_prev, ladder_k), *tau_max);
+}
+
+// Finalisation of the metric solve: G.d, max |d|, step bound and first ladder step (st is the
+// register copy of the slot's scalars).
+__device__ __forceinline__ void smooth_finalize(const BatchDesc* D, SlotState& st, int s, int n,
+                                                double gtd, double dmax, const FinOperands& fo) {
+  long long* nc_s = D->node_count + (size_t)s * WK_COUNT;
+  nc_s[WK_GRAD] = fo.nodes_grad + (long long)n * n;
+  if (!fo.halo) nc_s[WK_SMY] = fo.nodes_smy + (long long)n * n;
+  nc_s[WK_SMX] = fo.nodes_smx + (long long)n * n;
+  st.ub ^= 1;  // the gradient kernel wrote u - tau_pend d to the other buffer
+  st.tau_pend = 0.0;
+  st.gtd = gtd;
+  st.dmax = dmax;
+  if (!(gtd > 0.0) || !(dmax > 0.0)) {
+    level_done(st);
+  } else {
+    st.top = ladder_top(fo.step_cap, n, dmax, st.tau_prev, fo.ladder_k, &st.tau_max);
+    st.rung = 0;
+    // a line search whose first step is already below tau_min_rel * tau_max is not begun
+    if (st.top < fo.tau_min_rel * st.tau_max) level_done(st);
+    else st.phase = PH_LADDER;
+  }
+}
+
 // Works on a register copy of the slot's scalar fields (loaded together up front, stored back
 // at the end): every read of global state would otherwise wait behind the previous store.
 template <int MODE, int NC>
-__device__ __forceinline__ void energy_finalize(BatchDesc* D, SlotState* stp, SlotState& st,
+__device__ __forceinline__ void energy_finalize(const BatchDesc* D, SlotState* stp, SlotState& st,
                                                 int s, int l, int n, int ph, double top,
                                                 const double (&tot)[3 * NC + 3],
                                                 const FinOperands& fo) {
@@ -680,6 +772,7 @@ __device__ __forceinline__ void energy_finalize(BatchDesc* D, SlotState* stp, Sl
       st.ub = 0;
     }
     st.iter = 0;
+    st.rs = rs;
     st.tau_prev = INFINITY;
     st.tau_pend = 0.0;
     st.E = e_j[0];
@@ -770,19 +863,48 @@ __device__ __forceinline__ void energy_finalize(BatchDesc* D, SlotState* stp, Sl
       else st.phase = PH_LADDER;
     }
   }
-  store_head(*stp, st);
 }
 
 // Staged nodes of an element tile (ET_X x ET_Y elements).
 #define ET_NN ((ET_X + 1) * (ET_Y + 1))
 
+// Largest max |d| of a slot's metric-solve partials by one wavefront (exact in any order).
+// load: this lane's share, two values in flight at once (a 1025-node level has 130); reduce:
+// across the wave.
+__device__ __forceinline__ float dmax_load(const BatchDesc* D, int s, int n_items) {
+  const float* p = slot_dm(D, s);
+  const int lane = threadIdx.x & 63;
+  float m = fmaxf(p[min(lane, n_items - 1)], p[min(lane + 64, n_items - 1)]);
+  for (int it = lane + 128; it < n_items; it += 64) m = fmaxf(m, p[it]);
+  return m;
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_maxf(float m) {
+  return fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), CTRL, ROW_MASK,
+                                                             0xf, false)));
+}
+__device__ __forceinline__ float dmax_reduce(float m) {
+  m = dpp_maxf<kRowShr1, 0xf>(m);
+  m = dpp_maxf<kRowShr2, 0xf>(m);
+  m = dpp_maxf<kRowShr4, 0xf>(m);
+  m = dpp_maxf<kRowShr8, 0xf>(m);
+  m = dpp_maxf<kRowBcast15, 0xa>(m);
+  m = dpp_maxf<kRowBcast31, 0xc>(m);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), kTotalLane));
+}
+
 // One energy item: element tile t of slot s (MODE 0: the start energy of a level; MODE 1: a
 // line-search pass at NC step sizes). The LDS arrays are the caller's (s_dx, s_dy unused in
 // MODE 0).
+// A slot whose direction the metric solve of this step has just written (still in GRAD: its
+// state moves on in the finaliser after this pass) takes its first step size from the solve's
+// partials here, tile by tile: the first wavefront reduces them (2 (n + 15) / 16 values, loaded
+// with the tile's) and leaves the step sizes in s_tau. A launch between the solve and this pass
+// cost 4.6 us of every step; reducing in all four wavefronts cost the pass 6%.
 template <int MODE, int NC>
-__device__ __forceinline__ void energy_item(BatchDesc* D, int s, int t, float* s_ux, float* s_uy,
+__device__ __forceinline__ void energy_item(const BatchDesc* D, int s, int t, float* s_ux, float* s_uy,
                                             float* s_dx, float* s_dy, float* s_r,
-                                            double* s_stage) {
+                                            float* s_tau, double* s_stage) {
   constexpr int NXN = ET_X + 1, NN = ET_NN;
   constexpr int NV = 3 * NC + 3;
   const int kind = MODE ? WK_LADDER : WK_EVAL;
@@ -790,20 +912,22 @@ __device__ __forceinline__ void energy_item(BatchDesc* D, int s, int t, float* s
     SlotState* stp = D->state + s;
     int ph = stp->phase;
     if (MODE == 0 && !(ph == PH_INIT || ph == PH_PROLONG)) return;
-    if (MODE == 1 && ph != PH_LADDER) return;
+    const bool fresh = MODE == 1 && ph == PH_GRAD;
+    if (MODE == 1 && !fresh && ph != PH_LADDER) return;
     int l = (ph == PH_PROLONG) ? stp->level + 1 : stp->level;
-    int ub = (ph == PH_PROLONG) ? 0 : stp->ub;
+    int ub = (ph == PH_PROLONG) ? 0 : stp->ub ^ (fresh ? 1 : 0);
     int n = lvl_n(l);
     size_t nn = (size_t)n * n;
     const float* u = uni(slot_u(D, s, l, ub));
     const float* d = uni(D->dbuf + (size_t)s * D->slot_f_stride);
-    const float* R = uni(D->pyr + D->frame_off[(size_t)stp->ref * PPRS_MAXL + l]);
-    const float* TC = uni(D->tcoef + 4 * D->frame_off[(size_t)stp->tmpl * PPRS_MAXL + l]);
+    const float* R = uni(D->pyr + stp->roff);
+    const float* TC = uni(D->tcoef + 4 * stp->toff);
     const unsigned nn4 = (unsigned)nn << 2;
-    double top = MODE ? stp->top : 0.0;
-    float taus[NC];
-#pragma unroll
-    for (int j = 0; j < NC; ++j) taus[j] = MODE ? (float)ldexp(top, -j) : 0.f;
+    const bool lead = fresh && threadIdx.x < 64;
+    float dm_lane = 0.f;
+    if (lead) dm_lane = dmax_load(D, s, kind_items(D, WK_SMX, l));
+    const double tau_prev = stp->tau_prev, step_cap = D->step_cap, top0 = stp->top;
+    const int ladder_k = D->ladder_k;
     float inv_h = (float)(n - 1);
     int ntx = (n - 1 + ET_X - 1) / ET_X;
     int e0x = (t % ntx) * ET_X, e0y = (t / ntx) * ET_Y;
@@ -843,7 +967,24 @@ __device__ __forceinline__ void energy_item(BatchDesc* D, int s, int t, float* s
         }
       }
     }
+    if (lead) {
+      const float dmax = dmax_reduce(dm_lane);
+      double tau_max;
+      const double top =
+          ladder_top(step_cap, n, (double)dmax, tau_prev, ladder_k, &tau_max);
+      if (threadIdx.x < NC)  // 0 everywhere where there is no direction
+        s_tau[threadIdx.x] = dmax > 0.f ? (float)ldexp(top, -(int)threadIdx.x) : 0.f;
+    }
     __syncthreads();
+    float taus[NC];
+    if (fresh) {
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+        taus[j] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_tau[j])));
+    } else {
+#pragma unroll
+      for (int j = 0; j < NC; ++j) taus[j] = MODE ? (float)ldexp(top0, -j) : 0.f;
+    }
     // per-thread FP32 sums over the thread's elements of the tile (at most
     // ET_X * ET_Y / BLOCK), converted to FP64 once per tile
     float es[3 * NC], dir[3];
@@ -926,66 +1067,87 @@ struct EnergyLds {
 // the two lists in that order. The two slot sets are disjoint (the plan gives a slot that
 // begins a level no gradient work in the same step).
 template <int NC>
-__global__ void __launch_bounds__(BLOCK, LB_ENERGY) k_energy_step(BatchDesc* D) {
+__global__ void __launch_bounds__(BLOCK, LB_ENERGY) k_energy_step(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
   __shared__ EnergyLds<5, 3 * NC + 3> L;
+  __shared__ float s_tau[NC];
   float *s_ux = L.field(0), *s_uy = L.field(1), *s_r = L.field(2), *s_dx = L.field(3),
         *s_dy = L.field(4);
-  const int ne = D->lists[WK_EVAL].total, nl = D->lists[WK_LADDER].total;
-  const int total = ne + nl;
-  if (total <= 0) return;
-  int chunk = (total + gridDim.x - 1) / gridDim.x;
-  int b0 = placed_block<16>(chunk) * chunk, b1 = min(b0 + chunk, total);
-  ItemCursor c;
-  if (b0 < ne && cursor_range(D, WK_EVAL, b0, min(b1, ne), c)) {
-    for (; c.item < c.end; ++c.item) {
-      int s, t;
-      cursor_slot(D, WK_EVAL, c, s, t);
-      energy_item<0, 1>(D, s, t, s_ux, s_uy, s_dx, s_dy, s_r, L.buf);
-    }
-  }
-  if (b1 > ne && cursor_range(D, WK_LADDER, max(b0, ne) - ne, b1 - ne, c)) {
-    for (; c.item < c.end; ++c.item) {
-      int s, t;
-      cursor_slot(D, WK_LADDER, c, s, t);
-      energy_item<1, NC>(D, s, t, s_ux, s_uy, s_dx, s_dy, s_r, L.buf);
-    }
-  }
+  two_list_items<16>(
+      D, WK_EVAL, WK_LADDER,
+      [&](int s, int t) { energy_item<0, 1>(D, s, t, s_ux, s_uy, s_dx, s_dy, s_r, s_tau, L.buf); },
+      [&](int s, int t) { energy_item<1, NC>(D, s, t, s_ux, s_uy, s_dx, s_dy, s_r, s_tau, L.buf); });
 }
 
 // Per-slot finalisation of an energy pass: one workgroup per listed slot sums the tile
 // partials in tile order and advances the slot (the kernel boundary orders it after the pass).
 // The slot's item count comes from the list offsets the plan wrote (the slot's tiles on the
-// level it was listed for), so the partial loads do not wait for the slot state; a slot the
-// metric-solve finaliser already moved off its line search is skipped after the sums.
+// level it was listed for), so the partial loads do not wait for the slot state. A slot of the
+// ladder list that is still in GRAD is first moved on from its metric solve, whose partials it
+// sums in the same reduction; a slot that leaves its level there is done with the step.
 template <int MODE, int NC>
-__device__ __forceinline__ void energy_fin_slot(BatchDesc* D, int pos, double* s_red) {
+__device__ __forceinline__ void energy_fin_slot(const BatchDesc* D, int pos, double* s_red) {
   constexpr int NV = 3 * NC + 3;
   const int kind = MODE ? WK_LADDER : WK_EVAL;
-  const int* off = D->list_off + (size_t)kind * (D->max_slots + 1);
-  const int s = D->list_slots[(size_t)kind * D->max_slots + pos];
-  const int n_items = off[pos + 1] - off[pos];
+  const ListEntry* e = list_of(D, kind) + 1 + pos;
+  const int s = __builtin_amdgcn_readfirstlane(e[0].slot);
+  const int n_items = e[1].off - e[0].off;
   SlotState* stp = D->state + s;
   SlotState st;
   load_head(st, *stp);  // in flight with the partial loads
+  // the metric solve's first BLOCK values, loaded before the level is known and masked after
+  double gd0 = 0.0;
+  float dm0 = 0.f;
+  if (MODE == 1) {
+    const int i = min((int)threadIdx.x, (int)(D->part_kind_stride / PW) - 1);
+    gd0 = slot_gd(D, s)[i];
+    dm0 = slot_dm(D, s)[i];
+  }
   double tot[NV];
   partials_local<NV>(D, s, kind, n_items, tot, false);
   const int ph = st.phase;
-  bool live = MODE == 0 ? (ph == PH_INIT || ph == PH_PROLONG) : ph == PH_LADDER;
+  const bool fresh = MODE == 1 && ph == PH_GRAD;
+  bool live = MODE == 0 ? (ph == PH_INIT || ph == PH_PROLONG) : fresh || ph == PH_LADDER;
   const int l = (ph == PH_PROLONG) ? st.level + 1 : st.level;
   FinOperands fo;
   if (live && threadIdx.x == 0) load_fin_operands<MODE>(D, stp, st, s, l, fo);
-  block_sum<NV>(tot, s_red, false);
-  if (live && threadIdx.x == 0)
-    energy_finalize<MODE, NC>(D, stp, st, s, l, lvl_n(l), ph, MODE ? st.top : 0.0, tot, fo);
+  double gd = 0.0, dm = 0.0;
+  if (MODE == 1) {
+    // summed for every slot of the list; only a fresh one uses them
+    const int n_sm = fresh ? kind_items(D, WK_SMX, l) : 0;
+    double all[NV + 2];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) all[k] = tot[k];
+    all[NV] = (int)threadIdx.x < n_sm ? gd0 : 0.0;
+    all[NV + 1] = (int)threadIdx.x < n_sm ? (double)dm0 : 0.0;
+    for (int it = threadIdx.x + BLOCK; it < n_sm; it += BLOCK) {
+      all[NV] += slot_gd(D, s)[it];
+      all[NV + 1] = fmax(all[NV + 1], (double)slot_dm(D, s)[it]);
+    }
+    block_sum<NV + 2>(all, s_red, true);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) tot[k] = all[k];
+    gd = all[NV];
+    dm = all[NV + 1];
+  } else {
+    block_sum<NV>(tot, s_red, false);
+  }
+  if (live && threadIdx.x == 0) {
+    if (fresh) smooth_finalize(D, st, s, lvl_n(l), gd, dm, fo);
+    if (MODE == 0 || st.phase == PH_LADDER)
+      energy_finalize<MODE, NC>(D, stp, st, s, l, lvl_n(l), ph, MODE ? st.top : 0.0, tot, fo);
+    next_frames(D, st);
+    store_head(*stp, st);
+  }
   __syncthreads();
 }
 
 // Finalisers of k_energy_step: the eval list's slots, then the ladder list's.
 template <int NC>
-__global__ void __launch_bounds__(BLOCK) k_energy_step_fin(BatchDesc* D) {
-  constexpr int NV = 3 * NC + 3;
-  __shared__ double s_red[(BLOCK / 64) * NV];
-  const int ne = D->lists[WK_EVAL].n_slots, nl = D->lists[WK_LADDER].n_slots;
+__global__ void __launch_bounds__(BLOCK) k_energy_step_fin(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
+  __shared__ double s_red[(BLOCK / 64) * (3 * NC + 5)];
+  const int ne = list_of(D, WK_EVAL)[0].slot, nl = list_of(D, WK_LADDER)[0].slot;
   for (int pos = blockIdx.x; pos < ne + nl; pos += gridDim.x) {
     if (pos < ne)
       energy_fin_slot<0, 1>(D, pos, s_red);
@@ -1014,7 +1176,7 @@ struct GradLds {
 
 // One gradient item: node tile t of slot s (the LDS block is the caller's).
 template <int TX, int TY>
-__device__ __forceinline__ void grad_item(BatchDesc* D, int s, int t, GradLds<TX, TY>& L) {
+__device__ __forceinline__ void grad_item(const BatchDesc* D, int s, int t, GradLds<TX, TY>& L) {
   constexpr int GT_X = TX, GT_Y = TY;
   static_assert((TX & (TX - 1)) == 0 && (TY & (TY - 1)) == 0, "tile sides are powers of two");
   constexpr int NX = GradLds<TX, TY>::NX, NY = GradLds<TX, TY>::NY;
@@ -1035,8 +1197,8 @@ __device__ __forceinline__ void grad_item(BatchDesc* D, int s, int t, GradLds<TX
     float* G = uni(D->gbuf + (size_t)s * D->slot_p_stride);
     const int gpi = row_pitch(n);
     const unsigned nn4 = (unsigned)nn << 2, gpn4 = (unsigned)(n * gpi) << 2;
-    const float* R = uni(D->pyr + D->frame_off[(size_t)stp->ref * PPRS_MAXL + l]);
-    const float* T = uni(D->pyr + D->frame_off[(size_t)stp->tmpl * PPRS_MAXL + l]);
+    const float* R = uni(D->pyr + stp->roff);
+    const float* T = uni(D->pyr + stp->toff);
     const float* T1 = uni(T + n);  // the row below, as a second scalar base
     const unsigned n4 = (unsigned)n << 2;
     float tau = (float)stp->tau_pend;
@@ -1171,28 +1333,12 @@ __device__ __forceinline__ void grad_item(BatchDesc* D, int s, int t, GradLds<TX
 // from the gradient slots, and nothing here reads what they write), one item space made of
 // the two lists in that order.
 template <int TX, int TY>
-__global__ void __launch_bounds__(BLOCK, LB_GRAD) k_grad(BatchDesc* D) {
+__global__ void __launch_bounds__(BLOCK, LB_GRAD) k_grad(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
   __shared__ GradLds<TX, TY> L;
-  const int ng = D->lists[WK_GRAD].total, np = D->lists[WK_PROLONG].total;
-  const int total = ng + np;
-  if (total <= 0) return;
-  int chunk = (total + gridDim.x - 1) / gridDim.x;
-  int b0 = placed_block<16>(chunk) * chunk, b1 = min(b0 + chunk, total);
-  ItemCursor c;
-  if (b0 < ng && cursor_range(D, WK_GRAD, b0, min(b1, ng), c)) {
-    for (; c.item < c.end; ++c.item) {
-      int s, t;
-      cursor_slot(D, WK_GRAD, c, s, t);
-      grad_item<TX, TY>(D, s, t, L);
-    }
-  }
-  if (b1 > ng && cursor_range(D, WK_PROLONG, max(b0, ng) - ng, b1 - ng, c)) {
-    for (; c.item < c.end; ++c.item) {
-      int s, t;
-      cursor_slot(D, WK_PROLONG, c, s, t);
-      prolong_item(D, s, t);
-    }
-  }
+  two_list_items<16>(D, WK_GRAD, WK_PROLONG,
+                     [&](int s, int t) { grad_item<TX, TY>(D, s, t, L); },
+                     [&](int s, int t) { prolong_item(D, s, t); });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1484,19 +1630,16 @@ __device__ __forceinline__ void smooth_item(const float* src, float* dst, const 
 // launches BIG only when the batch's finest level needs it.
 #define LB_SMX LB_SMOOTH
 template <int DIR, bool BIG>
-__global__ void __launch_bounds__(BLOCK, DIR ? LB_SMX : LB_SMOOTH) k_smooth(BatchDesc* D) {
+__global__ void __launch_bounds__(BLOCK, DIR ? LB_SMX : LB_SMOOTH) k_smooth(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
   extern __shared__ float s_buf[];
   __shared__ double s_red[(BLOCK / 64) * 2];
   const int kind = DIR ? WK_SMX : WK_SMY;
-  ItemCursor c;
   // column strips: a strip of 16 lines reads and writes one half of each 128-byte line, its
   // neighbour the other half
-  if (!cursor_begin<DIR ? 0 : 16>(D, kind, c)) return;
-  for (; c.item < c.end; ++c.item) {
-    int s, t;
-    cursor_slot(D, kind, c, s, t);
+  list_items<DIR ? 0 : 16>(D, kind, [&](int s, int t) {
     const SlotState* stp = D->state + s;
-    if (stp->phase != PH_GRAD) continue;
+    if (stp->phase != PH_GRAD) return;
     int l = stp->level;
     int n = lvl_n(l);
     size_t nn = (size_t)n * n;
@@ -1525,12 +1668,11 @@ __global__ void __launch_bounds__(BLOCK, DIR ? LB_SMX : LB_SMOOTH) k_smooth(Batc
       double acc[2] = {gd, dm};
       block_sum<2>(acc, s_red, true);
       if (threadIdx.x == 0) {
-        double* pr = slot_partial(D, s, kind, t);
-        pr[0] = acc[0];
-        pr[1] = acc[1];
+        slot_gd(D, s)[t] = acc[0];
+        slot_dm(D, s)[t] = (float)acc[1];
       }
     }
-  }
+  });
 }
 
 // Windowed metric solve: d = (S1^-1 (x) S1^-1) G for one SW_T x SW_T tile of one component in
@@ -1542,19 +1684,16 @@ __global__ void __launch_bounds__(BLOCK, DIR ? LB_SMX : LB_SMOOTH) k_smooth(Batc
 // exact one. Reads G once (halo re-reads hit the cache) and writes d: 16 B per node instead of
 // the 40 of two full passes through an intermediate. Partials: G.d and max |d| per tile.
 template <int H>
-__global__ void __launch_bounds__(SW_THREADS) k_smooth_win(BatchDesc* D) {
+__global__ void __launch_bounds__(SW_THREADS) k_smooth_win(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
   constexpr int WM = SW_T + 1 + 2 * H;  // largest window extent (last tile holds SW_T + 1)
   constexpr int PITCH = WM + 1;
   __shared__ float s[WM * PITCH];
   __shared__ double s_red[2][SW_THREADS / 64];
   const int tid = threadIdx.x;
-  ItemCursor c;
-  if (!cursor_begin(D, WK_SMX, c)) return;
-  for (; c.item < c.end; ++c.item) {
-    int sl, t;
-    cursor_slot(D, WK_SMX, c, sl, t);
+  list_items<0>(D, WK_SMX, [&](int sl, int t) {
     const SlotState* stp = D->state + sl;
-    if (stp->phase != PH_GRAD) continue;
+    if (stp->phase != PH_GRAD) return;
     int l = stp->level;
     int n = lvl_n(l);
     size_t nn = (size_t)n * n;
@@ -1653,68 +1792,10 @@ __global__ void __launch_bounds__(SW_THREADS) k_smooth_win(BatchDesc* D) {
         a += s_red[0][w];
         b = fmax(b, s_red[1][w]);
       }
-      double* pr = slot_partial(D, sl, WK_SMX, t);
-      pr[0] = a;
-      pr[1] = b;
+      slot_gd(D, sl)[t] = a;
+      slot_dm(D, sl)[t] = (float)b;
     }
-  }
-}
-
-// Per-slot finalisation of the metric solve: G.d, max |d|, step bound and first ladder top.
-__global__ void __launch_bounds__(BLOCK) k_smooth_fin(BatchDesc* D) {
-  __shared__ double s_red[(BLOCK / 64) * 2];
-  const WorkList wl = D->lists[WK_SMX];
-  const int* off = D->list_off + (size_t)WK_SMX * (D->max_slots + 1);
-  for (int pos = blockIdx.x; pos < wl.n_slots; pos += gridDim.x) {
-    // listed slots are in GRAD (nothing between the plan and here changes a phase); the item
-    // count comes from the list offsets, so the partial loads do not wait for the slot state
-    int s = D->list_slots[(size_t)WK_SMX * D->max_slots + pos];
-    SlotState* stp = D->state + s;
-    SlotState st;
-    load_head(st, *stp);  // in flight with the partial loads
-    double tot[2];
-    partials_local<2>(D, s, WK_SMX, off[pos + 1] - off[pos], tot, true);
-    // the node counters (only this workgroup writes them) and the run's parameters load while
-    // the partials reduce, instead of after the first store
-    long long* nc_s = D->node_count + (size_t)s * WK_COUNT;
-    long long nodes[3];
-    double step_cap, tau_min_rel;
-    int ladder_k, halo;
-    if (threadIdx.x == 0) {
-      nodes[0] = nc_s[WK_GRAD];
-      nodes[1] = nc_s[WK_SMY];
-      nodes[2] = nc_s[WK_SMX];
-      step_cap = D->step_cap;
-      tau_min_rel = D->tau_min_rel;
-      ladder_k = D->ladder_k;
-      halo = D->smooth_halo;
-    }
-    block_sum<2>(tot, s_red, true);
-    if (threadIdx.x == 0) {
-      int l = st.level;
-      int n = lvl_n(l);
-      nc_s[WK_GRAD] = nodes[0] + (long long)n * n;
-      if (!halo) nc_s[WK_SMY] = nodes[1] + (long long)n * n;
-      nc_s[WK_SMX] = nodes[2] + (long long)n * n;
-      st.ub ^= 1;          // the gradient kernel wrote u - tau_pend d to the other buffer
-      st.tau_pend = 0.0;
-      st.gtd = tot[0];
-      st.dmax = tot[1];
-      if (!(st.gtd > 0.0) || !(st.dmax > 0.0)) {
-        level_done(st);
-      } else {
-        double h = 1.0 / (n - 1);
-        st.tau_max = step_cap * h / st.dmax;
-        st.top = fmin(ldexp(st.tau_prev, ladder_k), st.tau_max);
-        st.rung = 0;
-        // a line search whose first step is already below tau_min_rel * tau_max is not begun
-        if (st.top < tau_min_rel * st.tau_max) level_done(st);
-        else st.phase = PH_LADDER;
-      }
-      store_head(*stp, st);
-    }
-    __syncthreads();
-  }
+  });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2114,7 +2195,7 @@ __device__ __forceinline__ void rigid_node_offset(const RigidMap& m, int a, int 
 // rp - tau_j rd for the NC steps of a line-search pass), one element tile. Partials as the
 // field energy pass's, the three regulariser columns zero.
 template <int MODE, int NC>
-__device__ __forceinline__ void rigid_energy_item(BatchDesc* D, int s, int t, float* s_r,
+__device__ __forceinline__ void rigid_energy_item(const BatchDesc* D, int s, int t, float* s_r,
                                                   double* s_stage) {
   constexpr int NXN = ET_X + 1, NYN = ET_Y + 1, NN = NXN * NYN;
   constexpr int NV = 3 * NC + 3;
@@ -2126,8 +2207,8 @@ __device__ __forceinline__ void rigid_energy_item(BatchDesc* D, int s, int t, fl
     if (MODE == 1 && ph != PH_LADDER) return;
     int l = (ph == PH_PROLONG) ? stp->level + 1 : stp->level;
     int n = lvl_n(l);
-    const float* R = uni(D->pyr + D->frame_off[(size_t)stp->ref * PPRS_MAXL + l]);
-    const float* TC = uni(D->tcoef + 4 * D->frame_off[(size_t)stp->tmpl * PPRS_MAXL + l]);
+    const float* R = uni(D->pyr + stp->roff);
+    const float* TC = uni(D->tcoef + 4 * stp->toff);
     const unsigned n16 = (unsigned)n << 4;
     double top = MODE ? stp->top : 0.0;
     RigidMap mp[NC];
@@ -2209,49 +2290,30 @@ __device__ __forceinline__ void rigid_energy_item(BatchDesc* D, int s, int t, fl
 // level (the eval list) and the line-search passes (the ladder list), one item space made of
 // the two lists in that order (disjoint slot sets, as for the fields' k_energy_step).
 template <int NC>
-__global__ void __launch_bounds__(BLOCK) k_rigid_energy_step(BatchDesc* D) {
+__global__ void __launch_bounds__(BLOCK) k_rigid_energy_step(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
   constexpr int NXN = ET_X + 1, NYN = ET_Y + 1, NN = NXN * NYN;
   constexpr int NV = 3 * NC + 3, KG = NV < BLOCK / 16 ? NV : BLOCK / 16;
   __shared__ float s_r[NN];
   __shared__ double s_stage[KG * (BLOCK / 2)];  // the partial sums' reduction stage
-  const int ne = D->lists[WK_EVAL].total, nl = D->lists[WK_LADDER].total;
-  const int total = ne + nl;
-  if (total <= 0) return;
-  int chunk = (total + gridDim.x - 1) / gridDim.x;
-  int b0 = blockIdx.x * chunk, b1 = min(b0 + chunk, total);
-  ItemCursor c;
-  if (b0 < ne && cursor_range(D, WK_EVAL, b0, min(b1, ne), c)) {
-    for (; c.item < c.end; ++c.item) {
-      int s, t;
-      cursor_slot(D, WK_EVAL, c, s, t);
-      rigid_energy_item<0, 1>(D, s, t, s_r, s_stage);
-    }
-  }
-  if (b1 > ne && cursor_range(D, WK_LADDER, max(b0, ne) - ne, b1 - ne, c)) {
-    for (; c.item < c.end; ++c.item) {
-      int s, t;
-      cursor_slot(D, WK_LADDER, c, s, t);
-      rigid_energy_item<1, NC>(D, s, t, s_r, s_stage);
-    }
-  }
+  two_list_items<0>(D, WK_EVAL, WK_LADDER,
+                    [&](int s, int t) { rigid_energy_item<0, 1>(D, s, t, s_r, s_stage); },
+                    [&](int s, int t) { rigid_energy_item<1, NC>(D, s, t, s_r, s_stage); });
 }
 
 // Parameter gradient of the slots in GRAD: three FP64 partials per element tile.
-__global__ void __launch_bounds__(BLOCK) k_rigid_grad(BatchDesc* D) {
+__global__ void __launch_bounds__(BLOCK) k_rigid_grad(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
   constexpr int NXN = ET_X + 1, NYN = ET_Y + 1, NN = NXN * NYN;
   __shared__ float s_r[NN];
   __shared__ double s_stage[3 * (BLOCK / 2)];  // the partial sums' reduction stage
-  ItemCursor c;
-  if (!cursor_begin(D, WK_GRAD, c)) return;
-  for (; c.item < c.end; ++c.item) {
-    int s, t;
-    cursor_slot(D, WK_GRAD, c, s, t);
+  list_items<0>(D, WK_GRAD, [&](int s, int t) {
     const SlotState* stp = D->state + s;
-    if (stp->phase != PH_GRAD) continue;
+    if (stp->phase != PH_GRAD) return;
     int l = stp->level;
     int n = lvl_n(l);
-    const float* R = uni(D->pyr + D->frame_off[(size_t)stp->ref * PPRS_MAXL + l]);
-    const float* T = uni(D->pyr + D->frame_off[(size_t)stp->tmpl * PPRS_MAXL + l]);
+    const float* R = uni(D->pyr + stp->roff);
+    const float* T = uni(D->pyr + stp->toff);
     RigidMap mp = rigid_map(stp->rp[0], stp->rp[1], stp->rp[2], n);
     const float cm1 = (float)mp.cm1, sn = (float)mp.s, cs = (float)cos(stp->rp[0]);
     double sg = stp->sigma;
@@ -2312,27 +2374,32 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_grad(BatchDesc* D) {
     }
     const double acc[3] = {(double)ga, (double)g0, (double)g1};
     block_sum_store<3>(acc, s_stage, slot_partial(D, s, WK_GRAD, t));
-  }
+  });
 }
 
 // Per slot after the gradient pass: steepest-descent direction rd = grad, G.d = |grad|^2,
 // max |d| over the level's nodes of the direction's displacement field (affine: its extreme
 // at a corner of the domain), then the line-search start as for the fields.
-__global__ void __launch_bounds__(BLOCK) k_rigid_grad_fin(BatchDesc* D) {
+__global__ void __launch_bounds__(BLOCK) k_rigid_grad_fin(const BatchDesc Dv) {
+  const BatchDesc* D = &Dv;
   __shared__ double s_red[(BLOCK / 64) * 3];
-  const WorkList wl = D->lists[WK_GRAD];
-  for (int pos = blockIdx.x; pos < wl.n_slots; pos += gridDim.x) {
-    int s = D->list_slots[(size_t)WK_GRAD * D->max_slots + pos];
+  const ListEntry* e = list_of(D, WK_GRAD);
+  const int n_slots = e[0].slot;
+  for (int pos = blockIdx.x; pos < n_slots; pos += gridDim.x) {
+    // listed slots are in GRAD; the item count comes from the list, so the partial loads do not
+    // wait for the slot state
+    const int s = __builtin_amdgcn_readfirstlane(e[1 + pos].slot);
     SlotState* stp = D->state + s;
-    if (stp->phase != PH_GRAD) continue;
-    int l = stp->level;
-    int n = lvl_n(l);
+    SlotState st;
+    load_head(st, *stp);
     double tot[3];
-    sum_partials<3>(D, s, WK_GRAD, D->geom[l].tiles_elem, tot, s_red, false);
+    partials_local<3>(D, s, WK_GRAD, e[2 + pos].off - e[1 + pos].off, tot, false);
+    long long nodes = threadIdx.x == 0 ? D->node_count[(size_t)s * WK_COUNT + WK_GRAD] : 0;
+    block_sum<3>(tot, s_red, false);
     if (threadIdx.x == 0) {
-      SlotState st;
-      load_head(st, *stp);
-      D->node_count[(size_t)s * WK_COUNT + WK_GRAD] += (long long)n * n;
+      int l = st.level;
+      int n = lvl_n(l);
+      D->node_count[(size_t)s * WK_COUNT + WK_GRAD] = nodes + (long long)n * n;
       double ca = cos(st.rp[0]), sa = sin(st.rp[0]);
       double dm = 0.0;
       for (int k = 0; k < 3; ++k) st.rd[k] = tot[k];
@@ -2354,6 +2421,7 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_grad_fin(BatchDesc* D) {
         if (st.top < D->tau_min_rel * st.tau_max) level_done(st);
         else st.phase = PH_LADDER;
       }
+      next_frames(D, st);
       store_head(*stp, st);
     }
     __syncthreads();
@@ -2419,12 +2487,15 @@ static int grid_for(long long work, int cap = 8192) {
   return (int)g;
 }
 
-hipError_t plan(BatchDesc* d, hipStream_t st) {
-  hipLaunchKernelGGL(k_plan, dim3(1), dim3(PLAN_T), 0, st, d);
+hipError_t plan(const BatchDesc& d, hipStream_t st) {
+  if (d.n_slots <= 64)
+    hipLaunchKernelGGL(k_plan<64>, dim3(1), dim3(64), 0, st, d);
+  else
+    hipLaunchKernelGGL(k_plan<PLAN_T>, dim3(1), dim3(PLAN_T), 0, st, d);
   return hipGetLastError();
 }
 bool ladder_rungs_ok(int nc) { return nc == 1 || nc == 2 || nc == 3 || nc == 5 || nc == 7; }
-hipError_t energy_step(BatchDesc* d, int nc, int grid, hipStream_t st) {
+hipError_t energy_step(const BatchDesc& d, int nc, int grid, hipStream_t st) {
   switch (nc) {
     case 1: hipLaunchKernelGGL((k_energy_step<1>), dim3(grid), dim3(BLOCK), 0, st, d); break;
     case 2: hipLaunchKernelGGL((k_energy_step<2>), dim3(grid), dim3(BLOCK), 0, st, d); break;
@@ -2435,7 +2506,7 @@ hipError_t energy_step(BatchDesc* d, int nc, int grid, hipStream_t st) {
   }
   return hipGetLastError();
 }
-hipError_t energy_step_fin(BatchDesc* d, int nc, int grid, hipStream_t st) {
+hipError_t energy_step_fin(const BatchDesc& d, int nc, int grid, hipStream_t st) {
   switch (nc) {
     case 1: hipLaunchKernelGGL((k_energy_step_fin<1>), dim3(grid), dim3(BLOCK), 0, st, d); break;
     case 2: hipLaunchKernelGGL((k_energy_step_fin<2>), dim3(grid), dim3(BLOCK), 0, st, d); break;
@@ -2446,17 +2517,13 @@ hipError_t energy_step_fin(BatchDesc* d, int nc, int grid, hipStream_t st) {
   }
   return hipGetLastError();
 }
-hipError_t smooth_fin(BatchDesc* d, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_smooth_fin, dim3(grid), dim3(BLOCK), 0, st, d);
-  return hipGetLastError();
-}
 const int kGradTiles[4][2] = {{32, 16}, {64, 8}, {128, 4}, {64, 16}};
 void grad_tile(int variant, int* tx, int* ty) {
   if (variant < 0 || variant > 3) variant = 0;
   *tx = kGradTiles[variant][0];
   *ty = kGradTiles[variant][1];
 }
-hipError_t grad(BatchDesc* d, int variant, int grid, hipStream_t st) {
+hipError_t grad(const BatchDesc& d, int variant, int grid, hipStream_t st) {
   switch (variant) {
     case 1: hipLaunchKernelGGL((k_grad<64, 8>), dim3(grid), dim3(BLOCK), 0, st, d); break;
     case 2: hipLaunchKernelGGL((k_grad<128, 4>), dim3(grid), dim3(BLOCK), 0, st, d); break;
@@ -2465,7 +2532,7 @@ hipError_t grad(BatchDesc* d, int variant, int grid, hipStream_t st) {
   }
   return hipGetLastError();
 }
-hipError_t smooth(BatchDesc* d, int dir, bool big, int grid, size_t lds_bytes, hipStream_t st) {
+hipError_t smooth(const BatchDesc& d, int dir, bool big, int grid, size_t lds_bytes, hipStream_t st) {
   if (big) {
     if (dir == 0) hipLaunchKernelGGL((k_smooth<0, true>), dim3(grid), dim3(SM_THREADS), lds_bytes, st, d);
     else hipLaunchKernelGGL((k_smooth<1, true>), dim3(grid), dim3(SM_THREADS), lds_bytes, st, d);
@@ -2475,7 +2542,7 @@ hipError_t smooth(BatchDesc* d, int dir, bool big, int grid, size_t lds_bytes, h
   }
   return hipGetLastError();
 }
-hipError_t smooth_win(BatchDesc* d, int halo, int grid, hipStream_t st) {
+hipError_t smooth_win(const BatchDesc& d, int halo, int grid, hipStream_t st) {
   if (halo == 16) hipLaunchKernelGGL(k_smooth_win<16>, dim3(grid), dim3(SW_THREADS), 0, st, d);
   else if (halo == 24) hipLaunchKernelGGL(k_smooth_win<24>, dim3(grid), dim3(SW_THREADS), 0, st, d);
   else return hipErrorInvalidValue;
@@ -2610,7 +2677,7 @@ hipError_t from_nodes_idx(const float* vbuf, const long long* offs, int n, float
   return hipGetLastError();
 }
 
-hipError_t rigid_energy_step(BatchDesc* d, int nc, int grid, hipStream_t st) {
+hipError_t rigid_energy_step(const BatchDesc& d, int nc, int grid, hipStream_t st) {
   switch (nc) {
     case 1: hipLaunchKernelGGL((k_rigid_energy_step<1>), dim3(grid), dim3(BLOCK), 0, st, d); break;
     case 2: hipLaunchKernelGGL((k_rigid_energy_step<2>), dim3(grid), dim3(BLOCK), 0, st, d); break;
@@ -2621,11 +2688,11 @@ hipError_t rigid_energy_step(BatchDesc* d, int nc, int grid, hipStream_t st) {
   }
   return hipGetLastError();
 }
-hipError_t rigid_grad(BatchDesc* d, int grid, hipStream_t st) {
+hipError_t rigid_grad(const BatchDesc& d, int grid, hipStream_t st) {
   hipLaunchKernelGGL(k_rigid_grad, dim3(grid), dim3(BLOCK), 0, st, d);
   return hipGetLastError();
 }
-hipError_t rigid_grad_fin(BatchDesc* d, int grid, hipStream_t st) {
+hipError_t rigid_grad_fin(const BatchDesc& d, int grid, hipStream_t st) {
   hipLaunchKernelGGL(k_rigid_grad_fin, dim3(grid), dim3(BLOCK), 0, st, d);
   return hipGetLastError();
 }

@@ -38,8 +38,9 @@ enum { WK_PROLONG = 0, WK_EVAL = 1, WK_GRAD = 2, WK_SMY = 3, WK_SMX = 4, WK_LADD
 #define BLOCK 256
 #define MAX_CAND 7      // 2K+1 with K <= 3
 
-// Per-slot state, in device memory. All floating-point scalars are FP64.
-struct SlotState {
+// Per-slot state, in device memory. All floating-point scalars are FP64. What an item needs of
+// it lies in its first two cache lines.
+struct alignas(128) SlotState {
   int phase;
   int level;     // current absolute level
   int ub;        // which of the two u buffers of the current level holds u
@@ -52,6 +53,8 @@ struct SlotState {
   int rung;      // index, within its group of 2K+1 steps, of the pending pass's first step
   int op;        // row of the registration in the call's decision log (BatchDesc::dlog)
   int eval_only; // probe: evaluate the start energy on the start level, then stop
+  long long roff, toff;  // BatchDesc::frame_off of the reference and the template on the level
+                         // the slot works on (level + 1 in PROLONG)
   double E;      // energy at the accepted u (= u[ub] - tau_pend d)
   double ncc;
   double mean;   // quadrature mean of the warped template at the accepted u
@@ -62,6 +65,7 @@ struct SlotState {
   double tau_pend;  // accepted step not yet applied to u[ub]
   double gtd;
   double dmax;
+  double rs;     // BatchDesc::rsum of the reference on the level (from its start energy on)
   double rp[3];  // rigid variant: alpha, t0, t1 (domain units) of phi(x) = R(alpha) x + t
   double rd[3];  // rigid variant: search direction in the parameters
   int iters[PPRS_MAXL];
@@ -80,11 +84,15 @@ struct LevelGeom {
   int sw_tiles;     // windowed metric solve: tiles per axis (max(1, (n-1) / SW_T))
 };
 
-// Per-kind item list built by the planning kernel each step.
-struct WorkList {
-  int n_slots;   // slots in the list
-  int total;     // total items
+// Per-kind item list built by the planning kernel each step: an array of entries of which the
+// first is the head (off: total items, slot: slots in the list), the next ones the list's slots
+// in order with the offsets of their items, and one more holds the total as an offset. Readers
+// fetch the head and the first 64 entries together, so a list is LIST_PAD entries longer.
+struct ListEntry {
+  int off;
+  int slot;
 };
+#define LIST_PAD 66
 
 // Everything the per-step kernels need; lives in device memory, pointers fixed per context.
 // Row pitch (floats) of a level's gradient and metric-solve buffers: rows start on 128-byte
@@ -128,10 +136,7 @@ struct BatchDesc {
   long long* node_count;   // [slot][WK_COUNT] grid nodes processed per kind (statistics)
   // smoother coefficients: inv_den[i], cprime[i] per level (float)
   float* coef;
-  // per-step item lists
-  int* list_slots;         // [WK_COUNT][max_slots]
-  int* list_off;           // [WK_COUNT][max_slots + 1]
-  WorkList* lists;         // [WK_COUNT]
+  ListEntry* lists;        // per-step item lists: [WK_COUNT][max_slots + LIST_PAD]
   int max_slots;
   // decision log (optional, caller's device buffer): row op, entry k = ladder position J of the
   // op's k-th accepted step (levels in order), the step being top 2^-J of its iteration
@@ -139,7 +144,7 @@ struct BatchDesc {
   int dlog_cap;
   float* tcoef;            // per pyramid node (same offsets x 4): v, v(+x) - v, v(+y) - v,
                            // v(+x+y) - v(+y) - v(+x) + v (0 past the last row / column)
-  int active;              // written by the plan kernel
+  int* active;             // slots not done, written by the plan kernel
   int* active_host;        // mapped host word the plan kernel writes too (may be null)
 };
 

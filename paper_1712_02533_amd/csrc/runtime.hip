@@ -112,18 +112,16 @@ struct StepGrid {
 };
 
 // A captured group of steps: every launch's kernel and arguments follow from these values (the
-// batch descriptor's contents lie on the device and are read at replay).
+// batch descriptor is an argument of every launch, so all of it counts).
 struct StepGraph {
   StepGrid grid;
-  const void* desc;
-  int steps, nc, variant, halo, rigid;
-  bool big;
+  BatchDesc desc;
+  int steps, nc, variant;
   size_t lds[2];
   hipGraphExec_t exec;
   bool same(const StepGraph& o) const {
-    return grid == o.grid && desc == o.desc && steps == o.steps && nc == o.nc &&
-           variant == o.variant && halo == o.halo && rigid == o.rigid && big == o.big &&
-           lds[0] == o.lds[0] && lds[1] == o.lds[1];
+    return grid == o.grid && steps == o.steps && nc == o.nc && variant == o.variant &&
+           lds[0] == o.lds[0] && lds[1] == o.lds[1] && !memcmp(&desc, &o.desc, sizeof desc);
   }
 };
 
@@ -137,8 +135,8 @@ struct pprs_ctx {
   DevBuf frames, frame_off, rsum, fr_ms, fr_part, tcoef;
   std::vector<long long> frame_off_host;
   // slots
-  DevBuf state, ubuf, dbuf, gbuf, zbuf, partial, nodecount, coef, list_slots, list_off,
-      lists, desc, opidx;
+  DevBuf state, ubuf, dbuf, gbuf, zbuf, partial, nodecount, coef, lists, desc,
+      opidx;
   // scan elements [M][2][nL^2] and staging
   DevBuf elems;
   int* active_host = nullptr;        // mapped host word: slots active in the last planned step
@@ -181,7 +179,7 @@ struct pprs_ctx {
   // every workspace buffer (for pprs_workspace_bytes; each frees itself with the context)
   std::vector<const DevBuf*> all_bufs() const {
     return {&frames, &frame_off, &rsum, &fr_ms, &fr_part, &tcoef, &state, &ubuf, &dbuf, &gbuf, &zbuf,
-            &partial, &nodecount, &coef, &list_slots, &list_off, &lists, &desc, &opidx,
+            &partial, &nodecount, &coef, &lists, &desc, &opidx,
             &elems, &cnn_in, &cnn_out, &tmp, &badflags, &warm_stage, &avg_stage, &pool_pack};
   }
 };
@@ -333,8 +331,7 @@ int window_halo(double beta) {
 // Bytes of the per-slot workspace for `cap` slots on levels m0..L (fields: the per-slot u, d,
 // G and z buffers; the rigid variant has none).
 struct SlotBytes {
-  size_t state, ubuf, dbuf, gbuf, zbuf, partial, nodecount, coef, list_slots, list_off, lists,
-      desc, opidx;
+  size_t state, ubuf, dbuf, gbuf, zbuf, partial, nodecount, coef, lists, desc, opidx;
 };
 
 // Lays out the slot geometry of levels m0..L in hd (level geometry, u offsets, strides) and
@@ -371,9 +368,8 @@ SlotBytes slot_layout(BatchDesc& hd, int cap, int L, int m0, bool fields) {
   b.partial = sizeof(double) * hd.part_slot_stride * cap;
   b.nodecount = sizeof(long long) * WK_COUNT * cap;
   b.coef = sizeof(float) * coef_off;
-  b.list_slots = sizeof(int) * WK_COUNT * cap;
-  b.list_off = sizeof(int) * WK_COUNT * (cap + 1);
-  b.lists = sizeof(WorkList) * WK_COUNT;
+  // the lists, and the active count behind them
+  b.lists = sizeof(ListEntry) * (WK_COUNT * ((size_t)cap + LIST_PAD) + 1);
   b.desc = sizeof(BatchDesc);
   b.opidx = sizeof(int) * 3 * cap;
   return b;
@@ -397,8 +393,6 @@ pprs_status ensure_slots(pprs_ctx* c, int cap, int L, int m0, double beta, bool 
     STCHK(ensure(c->partial, b.partial));
     STCHK(ensure(c->nodecount, b.nodecount));
     STCHK(ensure(c->coef, b.coef));
-    STCHK(ensure(c->list_slots, b.list_slots));
-    STCHK(ensure(c->list_off, b.list_off));
     STCHK(ensure(c->lists, b.lists));
     STCHK(ensure(c->desc, b.desc));
     STCHK(ensure(c->opidx, b.opidx));
@@ -410,9 +404,8 @@ pprs_status ensure_slots(pprs_ctx* c, int cap, int L, int m0, double beta, bool 
     hd.partial = P<double>(c->partial);
     hd.node_count = P<long long>(c->nodecount);
     hd.coef = P<float>(c->coef);
-    hd.list_slots = P<int>(c->list_slots);
-    hd.list_off = P<int>(c->list_off);
-    hd.lists = P<WorkList>(c->lists);
+    hd.lists = P<ListEntry>(c->lists);
+    hd.active = reinterpret_cast<int*>(hd.lists + (size_t)WK_COUNT * (cap + LIST_PAD));
     hd.active_host = c->active_host;
     // the field buffers cover cap slots of this geometry only when allocated now
     c->slots_fields = fields;
@@ -665,21 +658,20 @@ StepGrid step_grid(const pprs_ctx* c, const SlotItems& items, int slots) {
 
 // One step of every active slot: plan, gradient (with the prolongations of slots that
 // finished a level), metric solve, line search.
-pprs_status launch_step(pprs_ctx* c, BatchDesc* d, int nc, const StepGrid& g) {
+pprs_status launch_step(pprs_ctx* c, int nc, const StepGrid& g) {
   size_t lds0 = c->lds_smooth[0], lds1 = c->lds_smooth[1];
-  TIMED(TK_PLAN, pprs_k::plan(d, c->stream));
-  TIMED(TK_GRAD, pprs_k::grad(d, grad_variant(c->tile_grad), g.grad, c->stream));
+  TIMED(TK_PLAN, pprs_k::plan(c->hd, c->stream));
+  TIMED(TK_GRAD, pprs_k::grad(c->hd, grad_variant(c->tile_grad), g.grad, c->stream));
   if (c->hd.smooth_halo) {
-    TIMED(TK_SMW, pprs_k::smooth_win(d, c->hd.smooth_halo, g.smooth, c->stream));
+    TIMED(TK_SMW, pprs_k::smooth_win(c->hd, c->hd.smooth_halo, g.smooth, c->stream));
   } else {
     bool big = level_n(c->hd.finest) > 9 * 64;  // lines longer than 9 nodes per lane
-    TIMED(TK_SMY, pprs_k::smooth(d, 0, big, g.smooth, lds0, c->stream));
-    TIMED(TK_SMX, pprs_k::smooth(d, 1, big, g.smooth, lds1, c->stream));
+    TIMED(TK_SMY, pprs_k::smooth(c->hd, 0, big, g.smooth, lds0, c->stream));
+    TIMED(TK_SMX, pprs_k::smooth(c->hd, 1, big, g.smooth, lds1, c->stream));
   }
-  TIMED(TK_FIN, pprs_k::smooth_fin(d, g.fin, c->stream));
   // start energies of the slots that begin a level and the line-search passes, one launch
-  TIMED(TK_LADDER, pprs_k::energy_step(d, nc, g.energy, c->stream));
-  TIMED(TK_FIN, pprs_k::energy_step_fin(d, nc, g.fin, c->stream));
+  TIMED(TK_LADDER, pprs_k::energy_step(c->hd, nc, g.energy, c->stream));
+  TIMED(TK_FIN, pprs_k::energy_step_fin(c->hd, nc, g.fin, c->stream));
   return PPRS_OK;
 }
 
@@ -687,33 +679,32 @@ pprs_status launch_step(pprs_ctx* c, BatchDesc* d, int nc, const StepGrid& g) {
 // the start energies of the slots that begin a level and the line-search passes (a slot that
 // begins a level iterates from the next step on, as the plan lists it), and the finaliser the
 // field path uses.
-pprs_status launch_step_rigid(pprs_ctx* c, BatchDesc* d, int nc, const StepGrid& g) {
-  TIMED(TK_PLAN, pprs_k::plan(d, c->stream));
-  TIMED(TK_GRAD, pprs_k::rigid_grad(d, g.grad, c->stream));
-  TIMED(TK_FIN, pprs_k::rigid_grad_fin(d, g.fin, c->stream));
+pprs_status launch_step_rigid(pprs_ctx* c, int nc, const StepGrid& g) {
+  TIMED(TK_PLAN, pprs_k::plan(c->hd, c->stream));
+  TIMED(TK_GRAD, pprs_k::rigid_grad(c->hd, g.grad, c->stream));
+  TIMED(TK_FIN, pprs_k::rigid_grad_fin(c->hd, g.fin, c->stream));
   // start energies of the slots that begin a level and the line-search passes, one launch
-  TIMED(TK_LADDER, pprs_k::rigid_energy_step(d, nc, g.energy, c->stream));
-  TIMED(TK_FIN, pprs_k::energy_step_fin(d, nc, g.fin, c->stream));
+  TIMED(TK_LADDER, pprs_k::rigid_energy_step(c->hd, nc, g.energy, c->stream));
+  TIMED(TK_FIN, pprs_k::energy_step_fin(c->hd, nc, g.fin, c->stream));
   return PPRS_OK;
 }
 
-// Runs `steps` steps of the batch descriptor's slots. They always launch the same kernels with
-// the same arguments (all per-slot state lives on the device), so a group is captured once and
+// Runs `steps` steps of the context's slots. They always launch the same kernels with the same
+// arguments (all per-slot state lives on the device), so a group is captured once and
 // replayed, in this call and in later ones of the same launch shape (a context keeps at most
 // kMaxStepGraphs groups); with per-launch timing events, or in a context that must not
 // allocate, the steps launch one by one.
-pprs_status run_steps(pprs_ctx* c, BatchDesc* d, int steps, int nc, const StepGrid& g) {
+pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
   const bool rigid = c->hd.rigid != 0;
   auto launch = [&]() -> pprs_status {
     for (int k = 0; k < steps; ++k)
-      STCHK(rigid ? launch_step_rigid(c, d, nc, g) : launch_step(c, d, nc, g));
+      STCHK(rigid ? launch_step_rigid(c, nc, g) : launch_step(c, nc, g));
     return PPRS_OK;
   };
   if (c->timing || c->eager) return launch();
-  StepGraph key{g, d, steps, nc, grad_variant(c->tile_grad), c->hd.smooth_halo,
-                rigid ? 1 : 0, level_n(c->hd.finest) > 9 * 64,
+  StepGraph key{g, c->hd, steps, nc, grad_variant(c->tile_grad),
                 {c->lds_smooth[0], c->lds_smooth[1]}, nullptr};
-  if (rigid) key.variant = key.halo = key.big = 0, key.lds[0] = key.lds[1] = 0;
+  if (rigid) key.variant = 0, key.lds[0] = key.lds[1] = 0;
   for (const StepGraph& e : c->graphs)
     if (e.same(key)) {
       HIPCHK(hipGraphLaunch(e.exec, c->stream));
@@ -745,15 +736,15 @@ pprs_status run_steps(pprs_ctx* c, BatchDesc* d, int steps, int nc, const StepGr
 // Runs groups of steps until no slot is active: 8 steps, then 8, 16 and 32 at a time, each
 // followed by one wait (the plan of every step writes the number of active slots to a mapped
 // host word, or the host copies it where there is none).
-pprs_status run_until_done(pprs_ctx* c, BatchDesc* d, int nc, const StepGrid& g,
+pprs_status run_until_done(pprs_ctx* c, int nc, const StepGrid& g,
                            long long max_steps, long long* done_steps) {
   const int kGroup = 8;
   for (int reps = 1, polls = 0;; ++polls) {
-    for (int k = 0; k < reps; ++k) STCHK(run_steps(c, d, kGroup, nc, g));
+    for (int k = 0; k < reps; ++k) STCHK(run_steps(c, kGroup, nc, g));
     *done_steps += (long long)reps * kGroup;
     int active = 0;
     if (!c->active_host)
-      HIPCHK(hipMemcpyAsync(&active, &d->active, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+      HIPCHK(hipMemcpyAsync(&active, c->hd.active, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     if (c->active_host) active = *(volatile int*)c->active_host;
     if (c->timing) STCHK(tk_collect(c));
@@ -810,6 +801,8 @@ pprs_status run_batch(pprs_ctx* c, int n, const int* ref, const int* tmpl, InitK
     st[s].tau_prev = INFINITY;
     st[s].op = s;
     st[s].flags = extra_flags ? extra_flags[s] : 0;
+    st[s].roff = c->frame_off_host[(size_t)ref[s] * PPRS_MAXL + lv];
+    st[s].toff = c->frame_off_host[(size_t)tmpl[s] * PPRS_MAXL + lv];
   }
   HIPCHK(hipMemcpyAsync(hd.state, st.data(), sizeof(SlotState) * n, hipMemcpyHostToDevice,
                         c->stream));
@@ -852,7 +845,7 @@ pprs_status run_batch(pprs_ctx* c, int n, const int* ref, const int* tmpl, InitK
   items.energy *= n;
   items.grad *= n;
   items.smooth *= n;
-  STCHK(run_until_done(c, d, nc, step_grid(c, items, n), max_steps, &done_steps));
+  STCHK(run_until_done(c, nc, step_grid(c, items, n), max_steps, &done_steps));
   HIPCHK(pprs_k::finish(d, didx + 2 * n, elems, est, (long long)n * est, c->stream));
   if (c->log) {
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -1187,6 +1180,8 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
       x.tau_prev = INFINITY;
       x.op = i;
       x.flags = o.flags;
+      x.roff = c->frame_off_host[(size_t)o.ref * PPRS_MAXL + o.start];
+      x.toff = c->frame_off_host[(size_t)o.tmpl * PPRS_MAXL + o.start];
       x.eval_only = o.eval_only;
       if (o.init == INIT_RESUME) {
         // continues a level-(start - 1) result, prolongated to the start level by the state
@@ -1280,7 +1275,7 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
       items.smooth += m.smooth;
       ++busy;
     }
-    STCHK(run_steps(c, d, G, nc, step_grid(c, items, busy)));
+    STCHK(run_steps(c, G, nc, step_grid(c, items, busy)));
     done_steps += G;
     // 3. poll: retire finished slots, release their dependents
     HIPCHK(hipMemcpyAsync(st.data(), hd.state, sizeof(SlotState) * S, hipMemcpyDeviceToHost,
@@ -1453,7 +1448,7 @@ struct SeriesWs {
     return frames.frames + frames.frame_off + frames.rsum + frames.fr_part + frames.fr_ms +
            frames.tcoef + elems + pool_pack + tmp + slots.state + slots.ubuf +
            slots.dbuf + slots.gbuf + slots.zbuf + slots.partial + slots.nodecount +
-           slots.coef + slots.list_slots + slots.list_off + slots.lists + slots.desc +
+           slots.coef + slots.lists + slots.desc +
            slots.opidx;
   }
 };
@@ -1552,7 +1547,7 @@ size_t pair_scratch_bytes(int H, int W, int L, int m0) {
   memset(&hd, 0, sizeof hd);
   SlotBytes b = slot_layout(hd, 1, L, m0, true);
   for (size_t x : {b.state, b.ubuf, b.dbuf, b.gbuf, b.zbuf, b.partial, b.nodecount, b.coef,
-                   b.list_slots, b.list_off, b.lists, b.desc, b.opidx})
+                   b.lists, b.desc, b.opidx})
     t += align_up(x);
   return t;
 }
@@ -1842,6 +1837,8 @@ pprs_status run_batch_rigid(pprs_ctx* c, int n, const int* ref, const int* tmpl,
     st[s].coarsest = m0;
     st[s].tau_prev = INFINITY;
     st[s].op = s;
+    st[s].roff = c->frame_off_host[(size_t)ref[s] * PPRS_MAXL + m0];
+    st[s].toff = c->frame_off_host[(size_t)tmpl[s] * PPRS_MAXL + m0];
     for (int k = 0; k < 3; ++k) st[s].rp[k] = p0 ? p0[3 * s + k] : 0.0;
   }
   HIPCHK(hipMemcpyAsync(hd.state, st.data(), sizeof(SlotState) * n, hipMemcpyHostToDevice,
@@ -1855,7 +1852,7 @@ pprs_status run_batch_rigid(pprs_ctx* c, int n, const int* ref, const int* tmpl,
   items.energy *= n;
   items.grad *= n;
   items.smooth = 0;
-  pprs_status rs = run_until_done(c, d, nc, step_grid(c, items, n), max_steps, &done_steps);
+  pprs_status rs = run_until_done(c, nc, step_grid(c, items, n), max_steps, &done_steps);
   hd.rigid = 0;
   STCHK(rs);
   HIPCHK(hipMemcpyAsync(st.data(), hd.state, sizeof(SlotState) * n, hipMemcpyDeviceToHost,
