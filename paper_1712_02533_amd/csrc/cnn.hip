@@ -9,9 +9,9 @@
 //   L6 [up2(L5), input] 66->2 (128^2, linear)
 // Activations are NHWC. Weights are [Cout][Kp] with k = (dy * 3 + dx) * Cin + ci, Kp = 9 Cin
 // rounded up to 32 (L1 to 64), padded with zeros. L2-L5 run as fused implicit-GEMM
-// convolutions on MFMAs (v_mfma_f32_16x16x32_bf16); L1 (2 input channels) and L6 (2 output
-// channels, its upsampled input folded into the weights) as direct FP32 kernels. The backward
-// pass uses im2col + MFMA GEMMs for the weight gradients.
+// convolutions on MFMAs (v_mfma_f32_16x16x32_bf16), L6 (2 output channels, its upsampled input
+// folded into the weights) on MFMAs with the FP32 folded weights in three exact BF16 parts, L1 (2
+// input channels) as a direct FP32 kernel. The backward pass uses im2col + MFMA GEMMs for the weight gradients.
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 #include <ctype.h>
@@ -111,175 +111,218 @@ __global__ void __launch_bounds__(256) k_gemm(const bf16* __restrict__ A, int ld
 // ------------------------------------------------------------------------------------------
 // Fused 3x3 convolution (implicit GEMM) for layers whose input channels come in multiples of
 // 64: out[m][n] = relu(bias[n] + sum_k A(m,k) W[n][k]) as bf16, with m = (b, oy, ox) and
-// k = tap * Cin + c. A(m,k) is read straight from the NHWC input (no im2col copy): channels
-// [0, C0) from src0 (at half resolution when UP, i.e. the nearest 2x upsampling of the decoder),
-// channels [C0, C0 + C1) from src1 (the skip connection), zero outside the frame.
-// Tiles: 128 pixels x BN output channels x 64-deep K chunks (one tap, one source per chunk),
-// 4 wavefronts in 2 x 2, each owning 64 x BN/2 with 16x16x32 MFMAs; the next chunk is fetched
-// into registers while the current one is multiplied out of LDS (double buffer).
-// Requires C0 % 64 == 0, C1 % 64 == 0, BN | Cout, (B * Hout^2) % 128 == 0, Kp % 8 == 0.
-
-constexpr int CV_BM = 128, CV_BK = 64, CV_LD = CV_BK + 8;
-
+// k = tap * C0 + c. A(m,k) is read straight from the NHWC input (no im2col copy), zero outside
+// the frame.
 // DGRAD: the same product for a data gradient (input dZ, weights flipped and transposed):
 // no bias or ReLU, FP32 output (`out` is then a float*).
-// FOLD (with UP): the upsampled source is read at its own resolution. Output pixel
-// (2Y + py, 2X + px) sees through its 3x3 taps only the 2 x 2 source pixels
-// (Y - 1 + py + i, X - 1 + px + j), so the taps landing on one source pixel are summed into
+// FOLD: a decoder layer, channels [0, C0) from src0 at half resolution (nearest 2x upsampling),
+// channels [C0, C0 + C1) from src1 (the skip connection). The upsampled source is read at its own
+// resolution: output pixel (2Y + py, 2X + px) sees through its 3x3 taps only the 2 x 2 source
+// pixels (Y - 1 + py + i, X - 1 + px + j), so the taps landing on one source pixel are summed into
 // folded weights, one matrix per output parity (k_fold_weights: [4][Cout][Kp'], k' = (2i + j) C0
 // + c for the upsampled part, then 4 C0 + tap C1 + c for the skip part, Kp' = 4 C0 + 9 C1).
-// The pixels of a 128-row tile share one parity: m = ((parity B + b) (H/2) + Y) (H/2) + X.
-template <int BN, bool UP, bool DGRAD = false, bool FOLD = false>
+// The pixels of a tile share one parity: m = ((parity B + b) (H/2) + Y) (H/2) + X.
+//
+// A workgroup computes 64 MT pixels x BN output channels in 64-deep K chunks (one tap, one source
+// per chunk). Each of its four wavefronts owns 16 MT pixels and all BN channels, so a pixel's
+// values are used by one wavefront only and go from memory straight into its MFMA operands (a
+// lane's 8 consecutive channels of one pixel: one 16-byte load), the next chunk's in flight during
+// the current one; the weights, which all four share, go through LDS (double buffer). Row offsets
+// are 32-bit and change only with the tap; a pixel outside the frame takes an offset beyond the
+// buffer, which reads zero. With both operands through LDS and 64-bit addresses per chunk the
+// pass spent more on addresses than on MFMAs (511 pairs, executed
+// TFLOP/s: L2 330, L3 260, L4 345, L5 245; now 610, 430, 730, 435: the values' nine reads through
+// the first-level cache bound it).
+// The product is formed transposed (channels as rows), so that a lane ends with 4 consecutive
+// channels of a pixel and stores them together.
+// Requires C0 % 64 == 0, C1 % 64 == 0, BN | Cout, (pixels of a parity) % (64 MT) == 0,
+// Kp % 8 == 0, Hin a power of two.
+
+constexpr int CV_BK = 64, CV_LD = CV_BK + 8;
+
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+
+template <int MT, int BN, bool DGRAD, bool FOLD>
 __global__ void __launch_bounds__(256, 2) k_conv_fwd(
     const bf16* __restrict__ src0, int C0, const bf16* __restrict__ src1, int C1, int Hin,
     int stride, const bf16* __restrict__ Wt, int Kp, const float* __restrict__ bias, int Cout,
     void* __restrict__ out_) {
-  static_assert(!FOLD || (UP && !DGRAD), "folding is for the upsampling layers' forward");
-  constexpr int WN = BN / 2;          // columns per wave
-  constexpr int TN = WN / 16;         // 16-wide MFMA tiles per wave along n
-  constexpr int B_PIECES = BN * 8 / 256;
-  __shared__ __attribute__((aligned(16))) bf16 sA[2][CV_BM * CV_LD];
+  static_assert(!(FOLD && DGRAD), "folding is for the upsampling layers' forward");
+  constexpr int BM = 64 * MT, TN = BN / 16, B_PIECES = BN * 8 / 256;
+  constexpr unsigned OUTSIDE = 0x80000000u;  // beyond every buffer: reads zero
   __shared__ __attribute__((aligned(16))) bf16 sB[2][BN * CV_LD];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int Cin = C0 + C1, Hout = Hin / stride;
-  const int K = FOLD ? 4 * C0 + 9 * C1 : 9 * Cin, nchunks = K / CV_BK;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Hout = Hin / stride, Hs0 = FOLD ? Hin / 2 : Hin;
+  const int nchunks = (FOLD ? 4 * C0 + 9 * C1 : 9 * C0) / CV_BK;
   const int n0 = blockIdx.y * BN;
-  const int Hs0 = UP ? Hin / 2 : Hin;
-  // FOLD: the tile's parity and its pixels' half-resolution coordinates
-  const long long tiles_per_par = FOLD ? (long long)gridDim.x / 4 : 1;
-  const int par = FOLD ? (int)(blockIdx.x / tiles_per_par) : 0;
+  const int tiles_per_par = FOLD ? gridDim.x / 4 : 1;
+  const int par = FOLD ? blockIdx.x / tiles_per_par : 0;
   const int py = par >> 1, px = par & 1;
-  const long long m0 = FOLD ? (blockIdx.x - par * tiles_per_par) * CV_BM
-                            : (long long)blockIdx.x * CV_BM;
+  const long long m0 = (long long)(FOLD ? blockIdx.x - par * tiles_per_par : blockIdx.x) * BM;
   if (FOLD) Wt += (size_t)par * Cout * Kp;
-  // this thread's 4 A rows (pixels) and its 16-byte piece within a 64-wide chunk; FOLD: the
-  // rows hold (b, Y, X) on the half-resolution grid
-  const int a_piece = tid & 7;
-  const int Hm = FOLD ? Hout / 2 : Hout;
-  int a_b[4], a_oy[4], a_ox[4];
+  const int Hm = FOLD ? Hout / 2 : Hout, lh = __builtin_ctz(Hm);
+  // the tile's first sample: 64-bit bases here, 32-bit offsets from here on
+  const long long bs = m0 >> (2 * lh);
+  const bf16* const base0 = src0 + (size_t)bs * Hs0 * Hs0 * C0;
+  const bf16* const base1 = FOLD ? src1 + (size_t)bs * Hin * Hin * C1 : base0;
+  // this lane's pixels: byte offsets of their centre (FOLD: of (Y, X) in src0 and of the output
+  // pixel in src1) plus the lane's channels, and which taps lie inside the frame
+  const int row16 = lane & 15, kq = lane >> 4;
+  unsigned off0[MT], off1[MT], inside[MT];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    long long m = m0 + (tid >> 3) + 32 * r;
-    a_ox[r] = (int)(m % Hm);
-    a_oy[r] = (int)((m / Hm) % Hm);
-    a_b[r] = (int)(m / ((long long)Hm * Hm));
-  }
-  uint4 ra[4], rb[B_PIECES];
-  auto fetch = [&](int chunk) {
-    int k0 = chunk * CV_BK;
-    bool first;
-    int dy, dx, c0;
+  for (int i = 0; i < MT; ++i) {
+    const long long m = m0 + wave * 16 * MT + 16 * i + row16;
+    const int ox = (int)m & (Hm - 1), oy = (int)(m >> lh) & (Hm - 1);
+    const unsigned rb = (unsigned)((m >> (2 * lh)) - bs);
+    const int y0 = FOLD ? oy : oy * stride, x0 = FOLD ? ox : ox * stride;
+    off0[i] = (((rb * Hs0 + y0) * Hs0 + x0) * C0 + 8 * kq) * 2;
+    off1[i] = 0;
+    unsigned in = 0;
     if (FOLD) {
-      first = k0 < 4 * C0;
-      if (first) {
-        int ij = k0 / C0;
-        c0 = k0 - ij * C0;
-        dy = (ij >> 1) - 1 + py;  // source row offset from Y
-        dx = (ij & 1) - 1 + px;
-      } else {
-        int r = k0 - 4 * C0, tap = r / C1;
-        c0 = C0 + (r - tap * C1);
-        dy = tap / 3 - 1;
-        dx = tap % 3 - 1;
+      const int y = 2 * oy + py, x = 2 * ox + px;
+      off1[i] = (((rb * Hin + y) * Hin + x) * C1 + 8 * kq) * 2;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int sy = oy - 1 + py + (t >> 1), sx = ox - 1 + px + (t & 1);
+        in |= (unsigned)(sy >= 0 && sy < Hs0 && sx >= 0 && sx < Hs0) << t;
+      }
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const int iy = y + t / 3 - 1, ix = x + t % 3 - 1;
+        in |= (unsigned)(iy >= 0 && iy < Hin && ix >= 0 && ix < Hin) << (4 + t);
       }
     } else {
-      int tap = k0 / Cin;
-      c0 = k0 - tap * Cin;
-      dy = tap / 3 - 1;
-      dx = tap % 3 - 1;
-      first = c0 < C0;
-    }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (FOLD && first) {
-        int sy = a_oy[r] + dy, sx = a_ox[r] + dx;
-        if (sy >= 0 && sy < Hs0 && sx >= 0 && sx < Hs0)
-          v = *(const uint4*)(src0 + (((size_t)a_b[r] * Hs0 + sy) * Hs0 + sx) * C0 + c0 +
-                              a_piece * 8);
-      } else {
-        int oy = FOLD ? 2 * a_oy[r] + py : a_oy[r], ox = FOLD ? 2 * a_ox[r] + px : a_ox[r];
-        int iy = oy * stride + dy, ix = ox * stride + dx;
-        if (iy >= 0 && iy < Hin && ix >= 0 && ix < Hin) {
-          const bf16* p;
-          if (first) {
-            int sy = UP ? iy >> 1 : iy, sx = UP ? ix >> 1 : ix;
-            p = src0 + (((size_t)a_b[r] * Hs0 + sy) * Hs0 + sx) * C0 + c0;
-          } else {
-            p = src1 + (((size_t)a_b[r] * Hin + iy) * Hin + ix) * C1 + (c0 - C0);
-          }
-          v = *(const uint4*)(p + a_piece * 8);
-        }
+      for (int t = 0; t < 9; ++t) {
+        const int iy = y0 + t / 3 - 1, ix = x0 + t % 3 - 1;
+        in |= (unsigned)(iy >= 0 && iy < Hin && ix >= 0 && ix < Hin) << t;
       }
-      ra[r] = v;
     }
+    inside[i] = in;
+  }
+  // position of the next chunk to fetch: tap (FOLD: 0-3 source pixels, 4-12 skip taps), channel
+  int tap = 0, c = 0;
+  unsigned voff[MT];
+  auto set_tap = [&] {
+    const bool skip = FOLD && tap >= 4;
+    int dy, dx, C, H;
+    if (FOLD && !skip) {
+      dy = (tap >> 1) - 1 + py;
+      dx = (tap & 1) - 1 + px;
+      C = C0;
+      H = Hs0;
+    } else {
+      const int t = FOLD ? tap - 4 : tap;
+      dy = t / 3 - 1;
+      dx = t % 3 - 1;
+      C = FOLD ? C1 : C0;
+      H = Hin;
+    }
+    const unsigned d = (unsigned)((dy * H + dx) * C * 2);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      if (FOLD && tap == 4) off0[i] = off1[i];  // on to the skip taps
+      voff[i] = (inside[i] >> tap) & 1u ? off0[i] + d : OUTSIDE;
+    }
+  };
+  set_tap();
+  u32x4 a[2][MT][2], rb[B_PIECES];
+  int chunk_f = 0;
+  auto fetch = [&](u32x4 (&fa)[MT][2]) {
+    const bool skip = FOLD && tap >= 4;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(skip ? base1 : base0), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        fa[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff[i] + 64 * h, c * 2, 0);
 #pragma unroll
     for (int r = 0; r < B_PIECES; ++r) {
-      int e = tid + 256 * r;
-      int n = e >> 3, pc = e & 7;
-      rb[r] = *(const uint4*)(Wt + (size_t)(n0 + n) * Kp + k0 + pc * 8);
+      const int e = tid + 256 * r;
+      rb[r] = *(const u32x4*)(Wt + (size_t)(n0 + (e >> 3)) * Kp + chunk_f * CV_BK + (e & 7) * 8);
+    }
+    ++chunk_f;
+    c += CV_BK;
+    if (c == (skip ? C1 : C0)) {
+      c = 0;
+      ++tap;
+      set_tap();
     }
   };
   auto stash = [&](int buf) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      *(uint4*)&sA[buf][((tid >> 3) + 32 * r) * CV_LD + a_piece * 8] = ra[r];
-#pragma unroll
     for (int r = 0; r < B_PIECES; ++r) {
-      int e = tid + 256 * r;
-      *(uint4*)&sB[buf][(e >> 3) * CV_LD + (e & 7) * 8] = rb[r];
+      const int e = tid + 256 * r;
+      *(u32x4*)&sB[buf][(e >> 3) * CV_LD + (e & 7) * 8] = rb[r];
     }
   };
-  f32x4 acc[4][TN];
+  f32x4 acc[MT][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  const int wm = (wave >> 1) * 64, wn = (wave & 1) * WN;
-  fetch(0);
+  // the weights' operands are read two steps ahead (the barriers keep the compiler from reading a
+  // whole chunk's at once, which would not leave registers for the accumulators)
+  auto multiply = [&](const u32x4 (&fa)[MT][2], int buf) {
+    auto weights = [&](int t) {
+      return *(const bf16x8*)&sB[buf][(16 * (t % TN) + row16) * CV_LD + 32 * (t / TN) + 8 * kq];
+    };
+    bf16x8 b[3];
+    b[0] = weights(0);
+    b[1] = weights(1);
+#pragma unroll
+    for (int t = 0; t < 2 * TN; ++t) {
+      if (t + 2 < 2 * TN) b[(t + 2) % 3] = weights(t + 2);
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+        acc[i][t % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            b[t % 3], __builtin_bit_cast(bf16x8, fa[i][t / TN]), acc[i][t % TN], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  fetch(a[0]);
   stash(0);
   __syncthreads();
-  for (int chunk = 0; chunk < nchunks; ++chunk) {
-    int buf = chunk & 1;
-    if (chunk + 1 < nchunks) fetch(chunk + 1);
-#pragma unroll
-    for (int ks = 0; ks < CV_BK; ks += 32) {
-      bf16x8 a[4], b[TN];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a[i] = *(const bf16x8*)&sA[buf][(wm + 16 * i + (lane & 15)) * CV_LD + ks + 8 * (lane >> 4)];
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        b[j] = *(const bf16x8*)&sB[buf][(wn + 16 * j + (lane & 15)) * CV_LD + ks + 8 * (lane >> 4)];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (chunk + 1 < nchunks) stash(buf ^ 1);
+  // two chunks per round, one operand set each; the last of an odd count follows
+  for (int chunk = 0; chunk + 2 <= nchunks; chunk += 2) {
+    fetch(a[1]);
+    multiply(a[0], 0);
+    stash(1);
+    __syncthreads();
+    if (chunk + 2 < nchunks) fetch(a[0]);
+    multiply(a[1], 1);
+    stash(0);  // nothing reads it where no chunk follows
     __syncthreads();
   }
-  // epilogue: bias, ReLU, bf16 NHWC (forward) or the plain FP32 sums (data gradient)
+  if (nchunks & 1) multiply(a[0], 0);
+  // epilogue: bias, ReLU, bf16 NHWC (forward) or the plain FP32 sums (data gradient); lane: pixel
+  // row16 of each 16, channels 4 kq .. 4 kq + 3 of each 16
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    int col = n0 + wn + 16 * j + (lane & 15);
-    float bv = DGRAD ? 0.f : bias[col];
+  for (int i = 0; i < MT; ++i) {
+    long long row = m0 + wave * 16 * MT + 16 * i + row16;
+    if (FOLD) {  // (b, Y, X) -> the output pixel (b, 2Y + py, 2X + px)
+      const long long X = row & (Hm - 1), Y = (row >> lh) & (Hm - 1), bb = row >> (2 * lh);
+      row = (bb * Hout + 2 * Y + py) * Hout + 2 * X + px;
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + 16 * j + 4 * kq;
+      if (DGRAD) {
+        *(f32x4*)((float*)out_ + row * Cout + col) = acc[i][j];
+      } else {
+        const f32x4 bv = *(const f32x4*)(bias + col);
+        unsigned int h[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        long long row = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-        if (FOLD) {  // (b, Y, X) -> the output pixel (b, 2Y + py, 2X + px)
-          long long X = row % Hm, t = row / Hm, Y = t % Hm, bb = t / Hm;
-          row = (bb * Hout + 2 * Y + py) * Hout + 2 * X + px;
+        for (int r = 0; r < 4; ++r) {
+          const float v = acc[i][j][r] + bv[r];
+          h[r] = __builtin_bit_cast(unsigned short, (bf16)(v > 0.f ? v : 0.f));
         }
-        float v = acc[i][j][r] + bv;
-        if (DGRAD)
-          ((float*)out_)[row * Cout + col] = v;
-        else
-          ((bf16*)out_)[row * Cout + col] = (bf16)(v > 0.f ? v : 0.f);
+        *(uint2*)((bf16*)out_ + row * Cout + col) =
+            make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
       }
+    }
   }
 }
 
@@ -515,89 +558,137 @@ __global__ void k_f32_to_bf16(const float* __restrict__ x, long long count,
 // Last layer (66 -> 2 channels, stride 1), FP32 direct kernels. W6 is [2][9][66] fp32 (from the
 // bf16 copy), bias b6[2].
 
-// Last layer read straight from its sources. Channels 0..63 are the nearest 2x upsampling of
-// the L5 output a5 [B][64][64][64]: output pixel (2Y + py, 2X + px) sees through its 3x3 taps
-// only the 2 x 2 source pixels (Y - 1 + py + i, X - 1 + px + j), i, j in {0, 1} (tap rows
+// Last layer read straight from its sources, on MFMAs. Channels 0..63 are the nearest 2x
+// upsampling of the L5 output a5 [B][64][64][64]: output pixel (2Y + py, 2X + px) sees through its
+// 3x3 taps only the 2 x 2 source pixels (Y - 1 + py + i, X - 1 + px + j), i, j in {0, 1} (tap rows
 // {0} and {1, 2} land on source rows Y - 1 and Y when py = 0, {0, 1} and {2} on Y and Y + 1
 // when py = 1; columns alike), so the taps that land on one source pixel are summed into the
-// folded weights W6f [parity py px][i][j][output][64] (k_w6_prep): 4 source pixels of 64
-// channels instead of 9. Channels 64, 65 are the network input x0 [B][128][128][2] (9 taps,
-// weights W6 [2][9][66]). Eight lanes share an output pixel, lane g taking channels 8g .. 8g + 7
-// (one 16-byte piece of each source pixel, so a source pixel is one 128-byte line per 8 lanes)
-// and x0 tap g (and tap 8 on lane 0); the 8 partial sums are then added across the lanes.
-// One workgroup per (sample, parity, 32 source pixels of a row): a wave's parity is uniform.
-__global__ void __launch_bounds__(256) k_l6_fused(const bf16* __restrict__ a5,
-                                                  const bf16* __restrict__ x0,
-                                                  const float* __restrict__ W6,
-                                                  const float* __restrict__ W6f,
-                                                  const float* __restrict__ b6, int Bn,
-                                                  float* __restrict__ Y) {
-  constexpr int C = 66;
-  __shared__ __attribute__((aligned(16))) float wf[4 * 2 * 2 * 2 * 64];
-  for (int e = threadIdx.x; e < 4 * 2 * 2 * 2 * 64; e += blockDim.x) wf[e] = W6f[e];
+// folded weights W6f [parity py px][i][j][output][64] (FP32, k_w6_prep). Channels 64, 65 are the
+// network input x0 [B][128][128][2] (9 taps).
+// All four parities of a source pixel are computed together, 8 outputs from its 3 x 3 source
+// neighbours (18 steps of 32 channels) and its 4 x 4 input pixels (one step). The FP32 folded
+// weights are the exact sum of three BF16 numbers (8 significant bits each, cut off toward
+// zero), which take three rows of the product each: nothing is rounded, the products are exact
+// and their sums FP32. Rows of the two 16-row weight tiles: 4 parity + {0, 1: the outputs' first
+// part, 2, 3: their second}; 4 parity + {0, 1: the third}. So a lane ends with one output pixel's
+// parts. Every value
+// is read from memory once but nine times through the first-level cache, which bounds the pass
+// (511 pairs: 279 us; the 368 MB from and to memory take 75); in FP32 on the ALUs, a parity at a
+// time, it took 400 us.
+// A wavefront takes 16 MT source pixels of a row; the weights (W6m, in operand order) sit in LDS.
+constexpr int L6_STEPS = 19;
+template <int MT>
+__global__ void __launch_bounds__(256, 2) k_l6_fused(const bf16* __restrict__ a5,
+                                                     const bf16* __restrict__ x0,
+                                                     const bf16* __restrict__ W6m,
+                                                     const float* __restrict__ b6, int Bn,
+                                                     float* __restrict__ Y) {
+  constexpr unsigned OUTSIDE = 0x80000000u;  // beyond every buffer: reads zero
+  __shared__ __attribute__((aligned(16))) bf16 sw[L6_STEPS * 2 * 64 * 8];
+  for (int e = threadIdx.x; e < L6_STEPS * 2 * 64; e += 256)
+    ((uint4*)sw)[e] = ((const uint4*)W6m)[e];
   __syncthreads();
-  const int g = threadIdx.x & 7;  // channel group
-  const int nblk = Bn * 4 * 64 * 2;  // (sample, parity, source row, half row)
-  for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const int half = blk & 1, ys = (blk >> 1) & 63, par = (blk >> 7) & 3, b = blk >> 9;
-    const int py = par >> 1, px = par & 1;
-    const int xs = half * 32 + (threadIdx.x >> 3);
-    const int y = 2 * ys + py, x = 2 * xs + px;
-    float s0 = g == 0 ? b6[0] : 0.f, s1 = g == 0 ? b6[1] : 0.f;
+  const int lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const float bias0 = b6[0], bias1 = b6[1];
+  const int units = Bn * 64 * (4 / MT);  // 16 MT source pixels each
+  for (int un = blockIdx.x * 4 + wave; un < units; un += gridDim.x * 4) {
+    const int part = un & (4 / MT - 1), row = un / (4 / MT), ys = row & 63, bb = row >> 6;
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a5 + (size_t)bb * 64 * 64 * 64), 0, 64 * 64 * 64 * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(x0 + (size_t)bb * 128 * 128 * 2), 0, 128 * 128 * 2 * 2, 0x00020000);
+    f32x4 acc[MT][2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int sy = ys - 1 + py + i;
-      if (sy < 0 || sy >= 64) continue;  // uniform over the workgroup (one source row)
+    for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto step = [&](int t, const u32x4 (&v)[MT]) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int sx = xs - 1 + px + j;
-        const bool ok = sx >= 0 && sx < 64;
-        uint4 v = ok ? *(const uint4*)(a5 + (((size_t)b * 64 + sy) * 64 + sx) * 64 + 8 * g)
-                     : make_uint4(0u, 0u, 0u, 0u);
-        const float* w0 = wf + (((par * 2 + i) * 2 + j) * 2) * 64 + 8 * g;
-        const f32x4 wa = *(const f32x4*)w0, wb = *(const f32x4*)(w0 + 4);
-        const f32x4 wc = *(const f32x4*)(w0 + 64), wd = *(const f32x4*)(w0 + 68);
-        const unsigned int h[4] = {v.x, v.y, v.z, v.w};
+      for (int n = 0; n < 2; ++n) {
+        const bf16x8 w = *(const bf16x8*)&sw[((t * 2 + n) * 64 + lane) * 8];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float lo = __uint_as_float(h[k] << 16), hi = __uint_as_float(h[k] & 0xffff0000u);
-          const float w0lo = k < 2 ? wa[2 * k] : wb[2 * k - 4];
-          const float w0hi = k < 2 ? wa[2 * k + 1] : wb[2 * k - 3];
-          const float w1lo = k < 2 ? wc[2 * k] : wd[2 * k - 4];
-          const float w1hi = k < 2 ? wc[2 * k + 1] : wd[2 * k - 3];
-          s0 = fmaf(w0lo, lo, s0);
-          s1 = fmaf(w1lo, lo, s1);
-          s0 = fmaf(w0hi, hi, s0);
-          s1 = fmaf(w1hi, hi, s1);
+        for (int i = 0; i < MT; ++i)
+          acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              w, __builtin_bit_cast(bf16x8, v[i]), acc[i][n], 0, 0, 0);
+      }
+    };
+    // the input pixels (2 ys - 1 + kq, 2 xs - 1 .. 2 xs + 2)
+    u32x4 vx[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int xs = (part * MT + i) * 16 + col, yy = 2 * ys - 1 + kq;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int xx = 2 * xs - 1 + e;
+        const unsigned o = yy >= 0 && yy < 128 && xx >= 0 && xx < 128
+                               ? (unsigned)((yy * 128 + xx) * 4) : OUTSIDE;
+        vx[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, o, 0, 0);
+      }
+    }
+    // the source rows, the next one's loads in flight during a row's products
+    u32x4 v[2][6][MT];
+    auto fetch = [&](int r, u32x4 (&d)[6][MT]) {
+#pragma unroll
+      for (int k = 0; k < 6; ++k)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const int xs = (part * MT + i) * 16 + col + k / 2 - 1, yy = ys + r - 1;
+          const unsigned o = yy >= 0 && yy < 64 && xs >= 0 && xs < 64
+                                 ? (unsigned)(((yy * 64 + xs) * 64 + 8 * kq) * 2) : OUTSIDE;
+          d[k][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, o + 64 * (k & 1), 0, 0);
         }
-      }
-    }
-    // x0 channels: lane g takes tap g, lane 0 also tap 8
+    };
+    // the weights are read from LDS for every unit: in registers across units they would leave
+    // none for the loads in flight
+    asm volatile("" ::: "memory");
+    fetch(0, v[0]);
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int tap = t == 0 ? g : 8;
-      if (t == 1 && g != 0) break;
-      const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
-      if (yy >= 0 && yy < 128 && xx >= 0 && xx < 128) {
-        const unsigned int v = *(const unsigned int*)(x0 + (((size_t)b * 128 + yy) * 128 + xx) * 2);
-        const float f0 = __uint_as_float(v << 16), f1 = __uint_as_float(v & 0xffff0000u);
-        s0 = fmaf(W6[tap * C + 64], f0, s0);
-        s1 = fmaf(W6[9 * C + tap * C + 64], f0, s1);
-        s0 = fmaf(W6[tap * C + 65], f1, s0);
-        s1 = fmaf(W6[9 * C + tap * C + 65], f1, s1);
-      }
-    }
-    // the 8 channel groups' partial sums (lanes 8p .. 8p + 7), fixed order
+    for (int r = 0; r < 3; ++r) {
+      if (r < 2) fetch(r + 1, v[(r + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int m = 1; m < 8; m <<= 1) {
-      s0 += __shfl_xor(s0, m, 64);
-      s1 += __shfl_xor(s1, m, 64);
+      for (int k = 0; k < 6; ++k) step(6 * r + k, v[r & 1][k]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (g == 0) {
-      const size_t o = (((size_t)b * 128 + y) * 128 + x) * 2;
-      Y[o] = s0;
-      Y[o + 1] = s1;
+    step(18, vx);
+    // lane: output pixel of parity kq at source column xs
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int xs = (part * MT + i) * 16 + col;
+      float* o = Y + (((size_t)bb * 128 + 2 * ys + (kq >> 1)) * 128 + 2 * xs + (kq & 1)) * 2;
+      *(float2*)o = make_float2(bias0 + (acc[i][0][0] + (acc[i][0][2] + acc[i][1][0])),
+                                bias1 + (acc[i][0][1] + (acc[i][0][3] + acc[i][1][1])));
     }
+  }
+}
+
+// The weights of k_l6_fused in operand order, from W6 [2][9][66] and W6f: step t, tile n, lane l,
+// element e. Each FP32 folded weight in three BF16 parts that sum to it exactly.
+__global__ void k_w6_mfma(const float* __restrict__ W6, const float* __restrict__ W6f,
+                          bf16* __restrict__ W6m) {
+  constexpr int C = 66;
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < L6_STEPS * 2 * 64 * 8;
+       q += gridDim.x * blockDim.x) {
+    const int e = q & 7, l = (q >> 3) & 63, n = (q >> 9) & 1, t = q >> 10;
+    const int rowi = l & 15, kq = l >> 4, par = rowi >> 2, slot = rowi & 3;
+    const int py = par >> 1, px = par & 1, o = slot & 1;
+    const int piece = n == 0 ? slot >> 1 : slot < 2 ? 2 : 3;  // 3: an empty row
+    float w = 0.f;
+    if (t < 18) {
+      const int nb = t >> 1, i = nb / 3 - py, j = nb % 3 - px;  // dy + 1 - py, dx + 1 - px
+      if (i >= 0 && i < 2 && j >= 0 && j < 2)
+        w = W6f[(((par * 2 + i) * 2 + j) * 2 + o) * 64 + 32 * (t & 1) + 8 * kq + e];
+    } else {
+      const int ty = kq - py, tx = (e >> 1) - px;
+      if (ty >= 0 && ty < 3 && tx >= 0 && tx < 3)
+        w = W6[o * 9 * C + (ty * 3 + tx) * C + 64 + (e & 1)];
+    }
+    // the part's 8 leading bits, cut off; what is not finite stays in the first part
+    float part = 0.f;
+    for (int k = 0; k <= piece && piece < 3; ++k) {
+      part = __uint_as_float(__float_as_uint(w) & 0xffff0000u);
+      w = isfinite(w) ? w - part : 0.f;
+    }
+    W6m[q] = __builtin_bit_cast(bf16, (unsigned short)(__float_as_uint(part) >> 16));
   }
 }
 
@@ -627,21 +718,15 @@ __global__ void __launch_bounds__(256) k_w6_prep(const bf16* __restrict__ wb6,
 
 // First layer (2 -> 64 channels, stride 2, 128^2 -> 64^2) straight from the input x0
 // [B][128][128][2]: one thread per output pixel holds its 18 inputs (k = tap * 2 + c); the
-// weights (FP32 from the BF16 copy, [k][64]) and the bias sit in LDS, read four channels at a
-// time at one address per wave; FP32 sums in k order, then bias and ReLU; the 64 BF16 outputs
-// leave as eight 16-byte stores (NHWC).
+// weights W1 (k_w1_prep: [channels 4g .. 4g + 3][k][4], FP32) and the bias are the same for every
+// lane and come through the scalar cache; FP32 sums in k order, then bias and ReLU; the 64 BF16
+// outputs leave as eight 16-byte stores (NHWC). 1,152 products per pixel: bound by the ALUs (511
+// pairs: 62 us of products) and the 268 MB it writes. With the weights in LDS the pass waited
+// on 288 16-byte LDS reads per wavefront: 276 us, now 135.
 __global__ void __launch_bounds__(256) k_l1_direct(const bf16* __restrict__ x0,
-                                                   const bf16* __restrict__ W, int Kp,
+                                                   const float* __restrict__ W1,
                                                    const float* __restrict__ bias, int Bn,
                                                    bf16* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) float ws[18][64];
-  __shared__ __attribute__((aligned(16))) float bs[64];
-  for (int e = threadIdx.x; e < 18 * 64; e += blockDim.x) {
-    const int co = e / 18, k = e - co * 18;
-    ws[k][co] = (float)W[co * Kp + k];
-  }
-  if (threadIdx.x < 64) bs[threadIdx.x] = bias[threadIdx.x];
-  __syncthreads();
   const long long total = (long long)Bn * 64 * 64;
   for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < total;
        p += (long long)gridDim.x * blockDim.x) {
@@ -656,27 +741,35 @@ __global__ void __launch_bounds__(256) k_l1_direct(const bf16* __restrict__ x0,
       in[2 * tap] = __uint_as_float(v << 16);
       in[2 * tap + 1] = __uint_as_float(v & 0xffff0000u);
     }
-    uint2* dst = (uint2*)(out + p * 64);
+    uint4* dst = (uint4*)(out + p * 64);
 #pragma unroll 1
-    for (int g = 0; g < 16; ++g) {  // output channels 4g .. 4g + 3
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int g2 = 0; g2 < 8; ++g2) {  // output channels 8 g2 .. 8 g2 + 7
+      unsigned int h[8];
 #pragma unroll
-      for (int k = 0; k < 18; ++k) {
-        const f32x4 w = *(const f32x4*)&ws[k][4 * g];
-        acc[0] = fmaf(w[0], in[k], acc[0]);
-        acc[1] = fmaf(w[1], in[k], acc[1]);
-        acc[2] = fmaf(w[2], in[k], acc[2]);
-        acc[3] = fmaf(w[3], in[k], acc[3]);
-      }
-      const f32x4 bb = *(const f32x4*)&bs[4 * g];
-      unsigned int h[4];
+      for (int gg = 0; gg < 2; ++gg) {
+        const float* w = W1 + (2 * g2 + gg) * 72;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = acc[r] + bb[r];
-        h[r] = __builtin_bit_cast(unsigned short, (bf16)(v > 0.f ? v : 0.f));
+        for (int k = 0; k < 18; ++k)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[r] = fmaf(w[4 * k + r], in[k], acc[r]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float v = acc[r] + bias[8 * g2 + 4 * gg + r];
+          h[4 * gg + r] = __builtin_bit_cast(unsigned short, (bf16)(v > 0.f ? v : 0.f));
+        }
       }
-      dst[g] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+      dst[g2] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
+                           h[6] | (h[7] << 16));
     }
+  }
+}
+
+// FP32 copy of the first layer's BF16 weights in k_l1_direct's order.
+__global__ void k_w1_prep(const bf16* __restrict__ W, int Kp, float* __restrict__ W1) {
+  for (int e = threadIdx.x; e < 18 * 64; e += blockDim.x) {
+    const int g = e / 72, k = e % 72 / 4, r = e & 3;
+    W1[e] = (float)W[(4 * g + r) * Kp + k];
   }
 }
 
@@ -925,7 +1018,8 @@ struct Model {
   bf16 *x0 = nullptr, *a[5] = {nullptr}, *u4 = nullptr, *u5 = nullptr,
        *col = nullptr, *dzb = nullptr;
   float *z = nullptr, *y = nullptr, *dy = nullptr, *dcol = nullptr, *du = nullptr,
-        *da[5] = {nullptr}, *part = nullptr, *w6 = nullptr, *w6f = nullptr;
+        *da[5] = {nullptr}, *part = nullptr, *w6 = nullptr, *w6f = nullptr, *w1 = nullptr;
+  bf16* w6m = nullptr;  // the last layer's weights as MFMA operands
   double* lpart = nullptr;
   size_t part_floats = 0;
 };
@@ -1056,6 +1150,39 @@ static pprs_status alloc_batch(Model& M, int B) {
   return PPRS_OK;
 }
 
+// Launches k_conv_fwd over `pix` output pixels. The tile is the largest that still gives the 256
+// compute units two workgroups each: 256 pixels x 64 channels or 128 x 128 (64 accumulator
+// registers a lane; 256 x 128 takes 128 and leaves one wavefront per SIMD: L4 of 511 pairs 435
+// us against 401; 128 x 64 for L5 693 us against 668), and fewer pixels where the batch is small
+// (one pair: L3 is 256 pixels in all; forward of one pair 97 us with 64 pixels, 202 us before).
+template <bool DGRAD, bool FOLD>
+static pprs_status conv_launch(Model& M, const bf16* s0, int c0, const bf16* s1, int c1, int hin,
+                               int stride, const bf16* w, int kp, const float* b, int cout,
+                               long long pix, void* out) {
+  const int bn = cout % 128 == 0 ? 128 : 64;
+  const long long unit = FOLD ? pix / 4 : pix;  // pixels that a tile may not straddle
+  if (unit % 64 || c0 % 64 || c1 % 64 || kp % 8 || cout % bn || (hin & (hin - 1)))
+    return cfail(PPRS_EINVAL, "convolution of %d + %d to %d channels does not fit its tiles", c0, c1,
+                 cout);
+  int mt = bn == 128 ? 2 : 4;
+  while (mt > 1 && (unit % (64 * mt) || pix / (64 * mt) * (cout / bn) < 512)) mt /= 2;
+  dim3 grid((unsigned)(pix / (64 * mt)), cout / bn);
+#define CONV(MT, BN)                                                                           \
+  hipLaunchKernelGGL((k_conv_fwd<MT, BN, DGRAD, FOLD>), grid, dim3(256), 0, M.stream, s0, c0, s1, \
+                     c1, hin, stride, w, kp, b, cout, out)
+  if (bn == 128) {
+    if (mt == 2) CONV(2, 128);
+    else CONV(1, 128);
+  } else {
+    if (mt == 4) CONV(4, 64);
+    else if (mt == 2) CONV(2, 64);
+    else CONV(1, 64);
+  }
+#undef CONV
+  CHK(hipGetLastError());
+  return PPRS_OK;
+}
+
 // Fused convolution of layer l (L2..L5) into M.a[l].
 static pprs_status conv_fused(Model& M, int l, int B) {
   const Layer& y = M.L[l];
@@ -1063,30 +1190,14 @@ static pprs_status conv_fused(Model& M, int l, int B) {
   const bf16* s1 = l == 3 ? M.a[1] : l == 4 ? M.a[0] : nullptr;
   int c0 = l == 1 ? 64 : l == 2 ? 128 : l == 3 ? 256 : 128;
   int c1 = y.cin - c0;
-  bool up = l >= 3;
   long long pix = (long long)B * y.hout * y.hout;
-  if (pix % CV_BM || c0 % 64 || c1 % 64 || y.kp != 9 * y.cin)
-    return cfail(PPRS_EINVAL, "layer %d does not fit the fused convolution", l + 1);
-  int bn = y.cout % 128 == 0 ? 128 : 64;
-  dim3 grid((unsigned)(pix / CV_BM), y.cout / bn);
-  const bf16* w = M.wb + y.woff;
   const float* b = M.w + y.boff;
-  if (up) {
+  if (l >= 3)
     // folded upsampling: per output parity, 4 C0 + 9 C1 deep (pixels of one parity per tile)
-    const int kf = 4 * c0 + 9 * c1;
-    if ((pix / 4) % CV_BM) return cfail(PPRS_EINVAL, "layer %d does not fit the folded convolution", l + 1);
-    const bf16* wf = M.wfold[l - 3];
-    if (bn == 128)
-      hipLaunchKernelGGL((k_conv_fwd<128, true, false, true>), grid, dim3(256), 0, M.stream, s0, c0, s1, c1, y.hin, y.stride, wf, kf, b, y.cout, M.a[l]);
-    else
-      hipLaunchKernelGGL((k_conv_fwd<64, true, false, true>), grid, dim3(256), 0, M.stream, s0, c0, s1, c1, y.hin, y.stride, wf, kf, b, y.cout, M.a[l]);
-  } else if (bn == 128) {
-    hipLaunchKernelGGL((k_conv_fwd<128, false>), grid, dim3(256), 0, M.stream, s0, c0, s1, c1, y.hin, y.stride, w, y.kp, b, y.cout, M.a[l]);
-  } else {
-    hipLaunchKernelGGL((k_conv_fwd<64, false>), grid, dim3(256), 0, M.stream, s0, c0, s1, c1, y.hin, y.stride, w, y.kp, b, y.cout, M.a[l]);
-  }
-  CHK(hipGetLastError());
-  return PPRS_OK;
+    return conv_launch<false, true>(M, s0, c0, s1, c1, y.hin, y.stride, M.wfold[l - 3],
+                                    4 * c0 + 9 * c1, b, y.cout, pix, M.a[l]);
+  return conv_launch<false, false>(M, s0, c0, s1, c1, y.hin, y.stride, M.wb + y.woff, y.kp, b,
+                                   y.cout, pix, M.a[l]);
 }
 
 // Forward pass for B samples; input x [B][128][128][2] fp32; output in M.y. With `train`, the
@@ -1099,7 +1210,7 @@ static pprs_status forward(Model& M, const float* x, int B, bool train) {
     // L1 (2 input channels): a direct kernel (18 products per output channel)
     const Layer& y = M.L[0];
     long long pix = (long long)B * y.hout * y.hout;
-    hipLaunchKernelGGL(k_l1_direct, dim3(grid1d(pix)), dim3(kBlock), 0, st, M.x0, M.wb + y.woff, y.kp, M.w + y.boff, B, M.a[0]);
+    hipLaunchKernelGGL(k_l1_direct, dim3(grid1d(pix)), dim3(kBlock), 0, st, M.x0, M.w1, M.w + y.boff, B, M.a[0]);
   }
   for (int l = 1; l < 5; ++l) {
     pprs_status s = conv_fused(M, l, B);
@@ -1112,17 +1223,23 @@ static pprs_status forward(Model& M, const float* x, int B, bool train) {
   }
   // L6
   const Layer& y6 = M.L[5];
-  hipLaunchKernelGGL(k_l6_fused, dim3(std::min(B * 512, 16384)), dim3(kBlock), 0, st, M.a[4], M.x0, M.w6, M.w6f, M.w + y6.boff, B, M.y);
+  // 32 source pixels per wavefront, or 16 where that fills fewer than two workgroups per unit
+  if (B >= 16)
+    hipLaunchKernelGGL(k_l6_fused<2>, dim3(std::min(B * 32, 1024)), dim3(256), 0, st, M.a[4], M.x0, M.w6m, M.w + y6.boff, B, M.y);
+  else
+    hipLaunchKernelGGL(k_l6_fused<1>, dim3(B * 64), dim3(256), 0, st, M.a[4], M.x0, M.w6m, M.w + y6.boff, B, M.y);
   CHK(hipGetLastError());
   return PPRS_OK;
 }
 
 // fp32 view of the L6 weights from the bf16 copy (so every layer computes with bf16 weights).
-// Weight copies derived from the BF16 weights, remade whenever they change: L6's FP32 copies
+// Weight copies derived from the BF16 weights, remade whenever they change: L1's and L6's FP32 copies
 // and the folded weights of the upsampling layers L4 and L5.
 static pprs_status refresh_derived(Model& M) {
   const Layer& y6 = M.L[5];
   hipLaunchKernelGGL(k_w6_prep, dim3(1), dim3(kBlock), 0, M.stream, M.wb + y6.woff, M.w6, M.w6f);
+  hipLaunchKernelGGL(k_w6_mfma, dim3(76), dim3(kBlock), 0, M.stream, M.w6, M.w6f, M.w6m);
+  hipLaunchKernelGGL(k_w1_prep, dim3(1), dim3(kBlock), 0, M.stream, M.wb + M.L[0].woff, M.L[0].kp, M.w1);
   for (int l = 3; l < 5; ++l) {
     const Layer& y = M.L[l];
     const int c0 = l == 3 ? 256 : 128, c1 = y.cin - c0;
@@ -1179,12 +1296,9 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
       // data gradient of the stride-1 decoder layers as a convolution of dZ with the flipped,
       // transposed weights (implicit GEMM, no materialised columns): dU [pix][cin] FP32
       hipLaunchKernelGGL(k_flip_weights, dim3(grid1d((long long)y.cin * 9 * y.cout)), dim3(kBlock), 0, st, M.wb + y.woff, y.cout, y.cin, y.kp, M.wflip);
-      int bn = y.cin % 128 == 0 ? 128 : 64;
-      dim3 grid((unsigned)(pix / CV_BM), y.cin / bn);
-      if (bn == 128)
-        hipLaunchKernelGGL((k_conv_fwd<128, false, true>), grid, dim3(256), 0, st, M.dzb, y.cout, (const bf16*)nullptr, 0, y.hout, 1, M.wflip, 9 * y.cout, (const float*)nullptr, y.cin, (void*)M.du);
-      else
-        hipLaunchKernelGGL((k_conv_fwd<64, false, true>), grid, dim3(256), 0, st, M.dzb, y.cout, (const bf16*)nullptr, 0, y.hout, 1, M.wflip, 9 * y.cout, (const float*)nullptr, y.cin, (void*)M.du);
+      s = conv_launch<true, false>(M, M.dzb, y.cout, nullptr, 0, y.hout, 1, M.wflip, 9 * y.cout,
+                                   nullptr, y.cin, pix, M.du);
+      if (s != PPRS_OK) return s;
       if (l == 4)
         // input u5 = [up2(a4) 128, a1 64] at 64^2
         hipLaunchKernelGGL(k_upcat_bwd, dim3(grid1d((long long)B * 64 * 64 * 64 + (long long)B * 32 * 32 * 128)), dim3(kBlock), 0, st, M.du, 128, 64, B, 64, 64, M.da[3], M.da[0], 0);
@@ -1418,6 +1532,8 @@ pprs_status pprs_cnn_create(pprs_cnn** out, int device, void* stream, unsigned l
   if (e == hipSuccess) e = hipMalloc(&M.g, sizeof(float) * M.n_params);
   if (e == hipSuccess) e = hipMalloc(&M.wb, sizeof(bf16) * M.n_params);
   if (e == hipSuccess) e = hipMalloc(&M.w6, sizeof(float) * M.L[5].cout * M.L[5].kp);
+  if (e == hipSuccess) e = hipMalloc(&M.w6m, sizeof(bf16) * L6_STEPS * 2 * 64 * 8);
+  if (e == hipSuccess) e = hipMalloc(&M.w1, sizeof(float) * 18 * 64);
   if (e == hipSuccess) e = hipMalloc(&M.w6f, sizeof(float) * 4 * 2 * 2 * 2 * 64);
   for (int l = 3; l < 5 && e == hipSuccess; ++l) {
     const int c0 = l == 3 ? 256 : 128, c1 = M.L[l].cin - c0;
@@ -1437,7 +1553,7 @@ void pprs_cnn_destroy(pprs_cnn* c) {
   Model& M = c->M;
   (void)hipSetDevice(M.device);
   (void)hipStreamSynchronize(M.stream);
-  void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
+  void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6m, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
                   M.a[1], M.a[2], M.a[3],
                   M.a[4], M.u4, M.u5, M.col, M.dzb, M.z, M.y, M.dy, M.dcol, M.du, M.da[0],
                   M.da[1], M.da[2], M.da[3], M.da[4], M.part, M.lpart, M.wflip};

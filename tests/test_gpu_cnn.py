@@ -53,6 +53,26 @@ def _rel(a, b):
     return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-30))
 
 
+@pytest.mark.parametrize("batch", [1, 2, 7, 15, 16, 17, 65])
+def test_forward_does_not_depend_on_the_batch(batch):
+    """The convolutions' tile (64 to 256 pixels) and the last layer's follow from the batch; every
+    output is the same sum in the same order whatever they are. Each sample of a batch (sizes where
+    the tiles change, with partial last rounds) equals its own forward pass bit for bit, and the
+    first and last are held to the FP64 reference (bar of the forward test)."""
+    torch = _torch()
+    net, p = _net_with_biases(11)
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    x = torch.randn((batch, 128, 128, 2), device="cuda", generator=g)
+    y = net.forward(x)
+    for k in range(batch):
+        assert torch.equal(net.forward(x[k:k + 1].contiguous()), y[k:k + 1]), k
+    q = _bf16_params(p)
+    for k in {0, batch - 1}:
+        ref = C.forward(q, C.bf16_round(x[k:k + 1].cpu().numpy()))
+        got = y[k:k + 1].cpu().numpy()
+        assert _rel(got, ref) < 2e-2 and np.abs(got - ref).max() < 0.05 * np.abs(ref).max()
+
+
 def test_weights_blob_loaded_by_the_library():
     """pprs_cnn_load parses the shipped weights file itself (safetensors layout, one F32
     tensor): the parameters equal what a library reader of the same file returns, and
