@@ -11,7 +11,8 @@
 // rounded up to 32 (L1 to 64), padded with zeros. L2-L5 run as fused implicit-GEMM
 // convolutions on MFMAs (v_mfma_f32_16x16x32_bf16), L6 (2 output channels, its upsampled input
 // folded into the weights) on MFMAs with the FP32 folded weights in three exact BF16 parts, L1 (2
-// input channels) as a direct FP32 kernel. The backward pass uses im2col + MFMA GEMMs for the weight gradients.
+// input channels) as a direct FP32 kernel. The weight gradients of L2-L5 are contracted over pixels by
+// k_wgrad; L1's goes through im2col and a GEMM.
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 #include <ctype.h>
@@ -373,15 +374,144 @@ __global__ void k_flip_weights(const bf16* __restrict__ W, int Cout, int Cin, in
   }
 }
 
-// Sum of `splits` partial results in split order.
-__global__ void k_split_sum(const float* __restrict__ part, long long stride, int splits,
-                            float* __restrict__ out, long long count) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < count;
-       i += (long long)gridDim.x * blockDim.x) {
-    float s = 0.f;
-    for (int k = 0; k < splits; ++k) s += part[k * stride + i];
-    out[i] = s;
+// Weight gradient of a 3x3 layer (64-channel blocks of input and output):
+//   dW[co][tap Cin + c] = sum over output pixels p of dZ[p][co] X[p stride + tap][c],
+// X the layer's input: channels [0, C0) from src0 (UP: at half resolution, the decoder's nearest
+// 2x upsampling), the rest from src1. A workgroup takes 64 output channels (blockIdx.y), 64 input
+// channels (blockIdx.x) and a share of the pixels (blockIdx.z) for all nine taps: dZ and the
+// input's halo of 64 output pixels (2^LW wide) are staged in LDS once for the nine products, the
+// next 64 pixels' loads in flight meanwhile. The contraction runs over pixels, but both operands
+// lie channel-fastest: the LDS transpose reads (ds_read_b64_tr_b16: a 16-lane group reads 4 rows
+// of 16 and each lane gets a column's 4) hand the MFMAs 8 pixels of one channel per lane. Each
+// wavefront owns 16 input channels: 36 accumulator tiles. Partials [split][Cout][9 Cin], summed in
+// split order by k_split_sum. The columns written out (906 MB for L5 of 64 samples), read back and
+// transposed into LDS by 2-byte stores took 1.9 ms of the 3.9 ms gradients of 64 samples; the four
+// launches of this kernel take 0.23 ms (590 TFLOP/s).
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+template <int STR, int LW, bool UP>
+__global__ void __launch_bounds__(256, 2) k_wgrad(const bf16* __restrict__ dZ, int Cout,
+                                                  const bf16* __restrict__ src0, int C0,
+                                                  const bf16* __restrict__ src1, int C1, int units,
+                                                  int per_split, float* __restrict__ part) {
+  constexpr int W = 1 << LW, R = 64 >> LW, H = W * STR;  // output width, rows per unit, input side
+  constexpr int HR = (R - 1) * STR + 3, HC = (W - 1) * STR + 3, HP = HR * HC;
+  constexpr int LD = 72;  // LDS row of 64 channels plus 8
+  constexpr int XP = (HP * 8 + 255) / 256;
+  __shared__ __attribute__((aligned(16))) short sX[HP * LD];
+  __shared__ __attribute__((aligned(16))) short sZ[64 * LD];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, kq = lane >> 4;
+  const int Cin = C0 + C1, cb = blockIdx.x * 64, co0 = blockIdx.y * 64;
+  const bool first = cb < C0;
+  const bool up = UP && first;
+  const bf16* src = first ? src0 + cb : src1 + (cb - C0);
+  const int Cs = first ? C0 : C1, Hs = up ? H / 2 : H;
+  const int u0 = blockIdx.z * per_split, u1 = min(u0 + per_split, units);
+  uint4 rx[XP], rz[2];
+  auto fetch = [&](int u) {
+    const int b = u / (W / R), y0 = (u & (W / R - 1)) * R;
+#pragma unroll
+    for (int q = 0; q < XP; ++q) {
+      const int e = tid + 256 * q, px = e >> 3;
+      const int iy = y0 * STR - 1 + px / HC, ix = px % HC - 1;
+      uint4 v = make_uint4(0u, 0u, 0u, 0u);
+      if (px < HP && iy >= 0 && iy < H && ix >= 0 && ix < H) {
+        const int sy = up ? iy >> 1 : iy, sx = up ? ix >> 1 : ix;
+        v = *(const uint4*)(src + (((size_t)b * Hs + sy) * Hs + sx) * Cs + (e & 7) * 8);
+      }
+      rx[q] = v;
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int e = tid + 256 * q;
+      rz[q] = *(const uint4*)(dZ + ((size_t)u * 64 + (e >> 3)) * Cout + co0 + (e & 7) * 8);
+    }
+  };
+  auto stash = [&] {
+#pragma unroll
+    for (int q = 0; q < XP; ++q) {
+      const int e = tid + 256 * q;
+      if ((e >> 3) < HP) *(uint4*)&sX[(e >> 3) * LD + (e & 7) * 8] = rx[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int e = tid + 256 * q;
+      *(uint4*)&sZ[(e >> 3) * LD + (e & 7) * 8] = rz[q];
+    }
+  };
+#define LDS_TR(p) \
+  __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p))
+  auto operand = [&](s16x4 lo, s16x4 hi) {  // pixels 8 kq .. 8 kq + 7 of the lane's channel
+    typedef __attribute__((ext_vector_type(8))) short s16x8;
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  // this lane's share of the transpose reads: rows (pixels) 8 kq + j / 4 and 4 more, 4 channels
+  int zoff[2], xoff[2][2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int p0 = 32 * ks + 8 * kq + (j >> 2);
+    zoff[ks] = p0 * LD + 4 * (j & 3);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int p = p0 + 4 * h;
+      xoff[ks][h] =
+          ((p >> LW) * STR * HC + (p & (W - 1)) * STR) * LD + 16 * wave + 4 * (j & 3);
+    }
   }
+  f32x4 acc[9][4];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[t][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  if (u0 < u1) fetch(u0);
+  for (int u = u0; u < u1; ++u) {
+    __syncthreads();
+    stash();
+    __syncthreads();
+    if (u + 1 < u1) fetch(u + 1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8 a[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        a[m] = operand(LDS_TR(sZ + zoff[ks] + 16 * m), LDS_TR(sZ + zoff[ks] + 4 * LD + 16 * m));
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const int d = (t / 3 * HC + t % 3) * LD;
+        const bf16x8 b = operand(LDS_TR(sX + xoff[ks][0] + d), LDS_TR(sX + xoff[ks][1] + d));
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+          acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[t][m], 0, 0, 0);
+      }
+    }
+  }
+#undef LDS_TR
+  float* out = part + (size_t)blockIdx.z * Cout * 9 * Cin;
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[(size_t)(co0 + 16 * m + 4 * kq + r) * 9 * Cin + t * Cin + cb + 16 * wave + j] =
+            acc[t][m][r];
+}
+
+// Sum of `splits` partial results, count a multiple of 64: 64 consecutive results per workgroup, a
+// quarter of the splits (each fourth) per wavefront in order, then the quarters in order.
+__global__ void __launch_bounds__(256) k_split_sum(const float* __restrict__ part,
+                                                   long long stride, int splits,
+                                                   float* __restrict__ out) {
+  __shared__ float red[4][64];
+  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const float* p = part + blockIdx.x * 64LL + lane;
+  float s = 0.f;
+#pragma unroll 8
+  for (int k = q; k < splits; k += 4) s += p[k * stride];
+  red[q][lane] = s;
+  __syncthreads();
+  if (q == 0) out[blockIdx.x * 64LL + lane] = ((s + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -405,30 +535,6 @@ __global__ void k_im2col(const bf16* __restrict__ X, int Bn, int H, int W, int C
       if (y >= 0 && y < H && x >= 0 && x < W) v = X[(((size_t)b * H + y) * W + x) * C + c];
     }
     col[i] = v;
-  }
-}
-
-// The same columns 8 at a time (C and Kp multiples of 8, so 8 consecutive columns share one
-// tap): one 16-byte load and store per thread, 32-bit index arithmetic (Bn Ho Wo Kp / 8 < 2^31).
-__global__ void k_im2col8(const bf16* __restrict__ X, int Bn, int H, int W, int C, int s,
-                          int Kp, bf16* __restrict__ col) {
-  const int Ho = H / s, Wo = W / s, KV = Kp / 8;
-  const unsigned total = (unsigned)((long long)Bn * Ho * Wo * KV);
-  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total;
-       i += gridDim.x * blockDim.x) {
-    unsigned p = i / KV;
-    int k = (int)(i - p * KV) * 8;
-    int ox = (int)(p % Wo);
-    unsigned q = p / Wo;
-    int oy = (int)(q % Ho), b = (int)(q / Ho);
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (k < 9 * C) {
-      int tap = k / C, c = k - tap * C;
-      int y = oy * s + tap / 3 - 1, x = ox * s + tap % 3 - 1;
-      if (y >= 0 && y < H && x >= 0 && x < W)
-        v = *(const uint4*)(X + (((size_t)b * H + y) * W + x) * C + c);
-    }
-    *(uint4*)(col + (size_t)p * Kp + k) = v;
   }
 }
 
@@ -460,22 +566,8 @@ __global__ void k_col2im(const float* __restrict__ dcol, int Bn, int H, int W, i
   }
 }
 
-// U = [up2(lo) (C1 channels), skip (C2 channels)] at H x W (lo is H/2 x W/2).
-__global__ void k_upcat(const bf16* __restrict__ lo, int C1, const bf16* __restrict__ skip,
-                        int C2, int Bn, int H, int W, bf16* __restrict__ U) {
-  int C = C1 + C2;
-  long long total = (long long)Bn * H * W * C;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    int c = (int)(i % C);
-    long long p = i / C;
-    int x = (int)(p % W), y = (int)((p / W) % H), b = (int)(p / ((long long)W * H));
-    U[i] = c < C1 ? lo[(((size_t)b * (H / 2) + y / 2) * (W / 2) + x / 2) * C1 + c]
-                  : skip[(((size_t)b * H + y) * W + x) * C2 + (c - C1)];
-  }
-}
-
-// Backward of k_upcat: d_lo = 2x2 sums of the first C1 channels; d_skip (+)= the rest.
+// A decoder layer's input gradient dU [H][W][C1 + C2] to its sources: d_lo = 2x2 sums of the first
+// C1 channels (the upsampling's adjoint); d_skip (+)= the rest.
 __global__ void k_upcat_bwd(const float* __restrict__ dU, int C1, int C2, int Bn, int H, int W,
                             float* __restrict__ dlo, float* __restrict__ dskip,
                             int skip_accumulate) {
@@ -504,30 +596,37 @@ __global__ void k_upcat_bwd(const float* __restrict__ dU, int C1, int C2, int Bn
   }
 }
 
-// dZ = dA * (A > 0) as bf16 (A is the layer's ReLU output).
-__global__ void k_relu_bwd(const float* __restrict__ dA, const bf16* __restrict__ A,
-                           long long count, bf16* __restrict__ dZ) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < count;
-       i += (long long)gridDim.x * blockDim.x)
-    dZ[i] = (bf16)((float)A[i] > 0.f ? dA[i] : 0.f);
-}
-
-// Column sums of a bf16 matrix [M][N] (bias gradients): per (column, chunk) partials.
-__global__ void k_colsum_part(const bf16* __restrict__ G, long long M, int N, int chunks,
-                              float* __restrict__ part) {
-  __shared__ float red[kBlock];
-  int n = blockIdx.x, ch = blockIdx.y;
-  long long rows = (M + chunks - 1) / chunks;
-  long long r0 = ch * rows, r1 = r0 + rows < M ? r0 + rows : M;
-  float s = 0.f;
-  for (long long r = r0 + threadIdx.x; r < r1; r += blockDim.x) s += (float)G[r * N + n];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
+// dZ = dA * (A > 0) as bf16 (A is the layer's ReLU output), [M][N] with N a multiple of 8 that
+// divides 2048, and the column sums of dZ (the bias gradient) per workgroup: part[block][N]. A
+// thread keeps 8 columns: two 16-byte loads of dA and one of A per row.
+__global__ void __launch_bounds__(kBlock) k_relu_bwd(const float* __restrict__ dA,
+                                                     const bf16* __restrict__ A, long long M,
+                                                     int N, bf16* __restrict__ dZ,
+                                                     float* __restrict__ part) {
+  __shared__ float red[kBlock][8];
+  const int per_row = N / 8, c8 = threadIdx.x % per_row, rows = kBlock / per_row;
+  float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (long long r = (long long)blockIdx.x * rows + threadIdx.x / per_row; r < M;
+       r += (long long)gridDim.x * rows) {
+    const long long i = r * N + 8 * c8;
+    const f32x4 d0 = *(const f32x4*)(dA + i), d1 = *(const f32x4*)(dA + i + 4);
+    const bf16x8 a = *(const bf16x8*)(A + i);
+    bf16x8 z;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      z[k] = (bf16)((float)a[k] > 0.f ? (k < 4 ? d0[k & 3] : d1[k & 3]) : 0.f);
+      sum[k] += (float)z[k];
+    }
+    *(bf16x8*)(dZ + i) = z;
   }
-  if (threadIdx.x == 0) part[(size_t)ch * N + n] = red[0];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) red[threadIdx.x][k] = sum[k];
+  __syncthreads();
+  for (int n = threadIdx.x; n < N; n += kBlock) {
+    float t = 0.f;
+    for (int q = 0; q < rows; ++q) t += red[q * per_row + n / 8][n & 7];
+    part[(size_t)blockIdx.x * N + n] = t;
+  }
 }
 
 // Column sums of per-chunk partials [chunks][N]: one workgroup (kBlock threads) per column;
@@ -1015,8 +1114,7 @@ struct Model {
   long long step = 0;
   int cap_b = 0;
   // activations and workspaces (sized for cap_b)
-  bf16 *x0 = nullptr, *a[5] = {nullptr}, *u4 = nullptr, *u5 = nullptr,
-       *col = nullptr, *dzb = nullptr;
+  bf16 *x0 = nullptr, *a[5] = {nullptr}, *col = nullptr, *dzb = nullptr;
   float *z = nullptr, *y = nullptr, *dy = nullptr, *dcol = nullptr, *du = nullptr,
         *da[5] = {nullptr}, *part = nullptr, *w6 = nullptr, *w6f = nullptr, *w1 = nullptr;
   bf16* w6m = nullptr;  // the last layer's weights as MFMA operands
@@ -1073,8 +1171,8 @@ static pprs_status gemm(Model& M, bool ak, bool bk, const bf16* A, int lda, cons
   else hipLaunchKernelGGL((k_gemm<true, true>), grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
   CHK(hipGetLastError());
   if (splits > 1) {
-    hipLaunchKernelGGL(k_split_sum, dim3(grid1d(stride)), dim3(kBlock), 0, M.stream, M.part,
-                       stride, splits, C, stride);
+    hipLaunchKernelGGL(k_split_sum, dim3((unsigned)(stride / 64)), dim3(256), 0, M.stream, M.part,
+                       stride, splits, C);
     CHK(hipGetLastError());
   }
   return PPRS_OK;
@@ -1103,7 +1201,7 @@ static void define_layers(Model& M) {
 
 static pprs_status alloc_batch(Model& M, int B) {
   if (B <= M.cap_b) return PPRS_OK;
-  void* ptrs[] = {M.x0, M.a[0], M.a[1], M.a[2], M.a[3], M.a[4], M.u4, M.u5, M.col, M.dzb,
+  void* ptrs[] = {M.x0, M.a[0], M.a[1], M.a[2], M.a[3], M.a[4], M.col, M.dzb,
                   M.z, M.y, M.dy, M.dcol, M.du, M.da[0], M.da[1], M.da[2], M.da[3], M.da[4],
                   M.part, M.lpart, M.wflip};
   for (void* p : ptrs)
@@ -1112,7 +1210,7 @@ static pprs_status alloc_batch(Model& M, int B) {
   long long col_max = 0, z_max = 0, dcol_max = 0;
   for (int l = 0; l < 5; ++l) {
     long long pix = (long long)B * M.L[l].hout * M.L[l].hout;
-    col_max = std::max(col_max, pix * M.L[l].kp);
+    if (l == 0) col_max = pix * M.L[l].kp;  // the first layer's weight gradient
     z_max = std::max(z_max, pix * (long long)M.L[l].cout);
     if (l == 1 || l == 2) dcol_max = std::max(dcol_max, pix * M.L[l].kp);  // via col2im
   }
@@ -1122,8 +1220,6 @@ static pprs_status alloc_batch(Model& M, int B) {
   CHK(hipMalloc(&M.a[2], sizeof(bf16) * P16 * 256));
   CHK(hipMalloc(&M.a[3], sizeof(bf16) * P32 * 128));
   CHK(hipMalloc(&M.a[4], sizeof(bf16) * P64 * 64));
-  CHK(hipMalloc(&M.u4, sizeof(bf16) * P32 * 384));
-  CHK(hipMalloc(&M.u5, sizeof(bf16) * P64 * 192));
   long long wf = 0;
   for (int l = 3; l < 5; ++l) wf = std::max(wf, (long long)M.L[l].cin * 9 * M.L[l].cout);
   CHK(hipMalloc(&M.wflip, sizeof(bf16) * wf));
@@ -1200,9 +1296,8 @@ static pprs_status conv_fused(Model& M, int l, int B) {
                                    y.cout, pix, M.a[l]);
 }
 
-// Forward pass for B samples; input x [B][128][128][2] fp32; output in M.y. With `train`, the
-// decoder inputs (upsampled + concatenated) are also kept for the weight gradients.
-static pprs_status forward(Model& M, const float* x, int B, bool train) {
+// Forward pass for B samples; input x [B][128][128][2] fp32; output in M.y.
+static pprs_status forward(Model& M, const float* x, int B) {
   hipStream_t st = M.stream;
   long long P128 = (long long)B * 128 * 128;
   hipLaunchKernelGGL(k_f32_to_bf16, dim3(grid1d(P128 * 2)), dim3(kBlock), 0, st, x, P128 * 2, M.x0);
@@ -1215,11 +1310,6 @@ static pprs_status forward(Model& M, const float* x, int B, bool train) {
   for (int l = 1; l < 5; ++l) {
     pprs_status s = conv_fused(M, l, B);
     if (s != PPRS_OK) return s;
-  }
-  if (train) {
-    long long p32 = (long long)B * 32 * 32, p64 = (long long)B * 64 * 64;
-    hipLaunchKernelGGL(k_upcat, dim3(grid1d(p32 * 384)), dim3(kBlock), 0, st, M.a[2], 256, M.a[1], 128, B, 32, 32, M.u4);
-    hipLaunchKernelGGL(k_upcat, dim3(grid1d(p64 * 192)), dim3(kBlock), 0, st, M.a[3], 128, M.a[0], 64, B, 64, 64, M.u5);
   }
   // L6
   const Layer& y6 = M.L[5];
@@ -1249,6 +1339,33 @@ static pprs_status refresh_derived(Model& M) {
   return PPRS_OK;
 }
 
+// Weight gradient of layer l (L2..L5) into M.g: enough pixel shares for two workgroups per compute
+// unit, as far as the partials' workspace and 64-pixel units go round.
+static pprs_status wgrad(Model& M, int l, int B) {
+  const Layer& y = M.L[l];
+  const bf16* s0 = l == 1 ? M.a[0] : l == 2 ? M.a[1] : l == 3 ? M.a[2] : M.a[3];
+  const bf16* s1 = l == 3 ? M.a[1] : l == 4 ? M.a[0] : nullptr;
+  const int c0 = l == 1 ? 64 : l == 2 ? 128 : l == 3 ? 256 : 128, c1 = y.cin - c0;
+  const int units = B * y.hout * y.hout / 64;
+  const long long size = (long long)y.cout * 9 * y.cin;
+  const int blocks = (y.cin / 64) * (y.cout / 64);
+  int splits = std::max(1, std::min({512 / blocks, units, (int)(M.part_floats / size)}));
+  const int per = (units + splits - 1) / splits;
+  splits = (units + per - 1) / per;
+  float* out = splits > 1 ? M.part : M.g + y.woff;
+  dim3 grid(y.cin / 64, y.cout / 64, splits);
+  if (l == 1) hipLaunchKernelGGL((k_wgrad<2, 5, false>), grid, dim3(256), 0, M.stream, M.dzb, y.cout, s0, c0, s1, c1, units, per, out);
+  else if (l == 2) hipLaunchKernelGGL((k_wgrad<2, 4, false>), grid, dim3(256), 0, M.stream, M.dzb, y.cout, s0, c0, s1, c1, units, per, out);
+  else if (l == 3) hipLaunchKernelGGL((k_wgrad<1, 5, true>), grid, dim3(256), 0, M.stream, M.dzb, y.cout, s0, c0, s1, c1, units, per, out);
+  else hipLaunchKernelGGL((k_wgrad<1, 6, true>), grid, dim3(256), 0, M.stream, M.dzb, y.cout, s0, c0, s1, c1, units, per, out);
+  CHK(hipGetLastError());
+  if (splits > 1) {
+    hipLaunchKernelGGL(k_split_sum, dim3((unsigned)(size / 64)), dim3(256), 0, M.stream, M.part, size, splits, M.g + y.woff);
+    CHK(hipGetLastError());
+  }
+  return PPRS_OK;
+}
+
 // Loss and full gradient into M.g (uses M.y from forward). Returns the mean squared error.
 static pprs_status backward(Model& M, const float* target, int B, int margin, double* loss) {
   hipStream_t st = M.stream;
@@ -1272,24 +1389,24 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
   }
   CHK(hipGetLastError());
   // L5 .. L1
-  const bf16* in[5] = {M.x0, M.a[0], M.a[1], M.u4, M.u5};
   for (int l = 4; l >= 0; --l) {
     const Layer& y = M.L[l];
     long long pix = (long long)B * y.hout * y.hout;
-    // dZ = dA * relu'(A)
-    hipLaunchKernelGGL(k_relu_bwd, dim3(grid1d(pix * y.cout)), dim3(kBlock), 0, st, M.da[l], M.a[l], pix * y.cout, M.dzb);
-    // bias gradient
-    int chunks = 64;
-    hipLaunchKernelGGL(k_colsum_part, dim3(y.cout, chunks), dim3(kBlock), 0, st, M.dzb, pix, y.cout, chunks, M.part);
-    hipLaunchKernelGGL(k_colsum_final, dim3(y.cout), dim3(kBlock), 0, st, M.part, y.cout, chunks, M.g + y.boff);
+    // dZ = dA * relu'(A) and the bias gradient
+    const int blocks_z = 1024;
+    hipLaunchKernelGGL(k_relu_bwd, dim3(blocks_z), dim3(kBlock), 0, st, M.da[l], M.a[l], pix, y.cout, M.dzb, M.part);
+    hipLaunchKernelGGL(k_colsum_final, dim3(y.cout), dim3(kBlock), 0, st, M.part, y.cout, blocks_z, M.g + y.boff);
+    CHK(hipGetLastError());
     // weight gradient: dW[co][k] = sum_pix dZ[pix][co] col[pix][k]
-    if (y.cin % 8 == 0 && y.kp % 8 == 0 && pix * (y.kp / 8) < (1LL << 31))
-      hipLaunchKernelGGL(k_im2col8, dim3(grid1d(pix * y.kp / 8)), dim3(kBlock), 0, st, in[l], B, y.hin, y.hin, y.cin, y.stride, y.kp, M.col);
-    else
-      hipLaunchKernelGGL(k_im2col, dim3(grid1d(pix * y.kp)), dim3(kBlock), 0, st, in[l], B, y.hin, y.hin, y.cin, y.stride, y.kp, M.col);
-    int splits = (int)std::min<long long>(64, pix / 256);
-    if (splits < 1) splits = 1;
-    pprs_status s = gemm(M, true, true, M.dzb, y.cout, M.col, y.kp, M.g + y.woff, y.kp, y.cout, y.kp, (int)pix, splits);
+    pprs_status s;
+    if (l > 0) {
+      s = wgrad(M, l, B);
+    } else {
+      hipLaunchKernelGGL(k_im2col, dim3(grid1d(pix * y.kp)), dim3(kBlock), 0, st, M.x0, B, y.hin, y.hin, y.cin, y.stride, y.kp, M.col);
+      // one 64 x 64 result: the splits alone fill the GPU (64 of them: 129 us for 64 samples)
+      int splits = (int)std::max<long long>(1, std::min<long long>(512, pix / 256));
+      s = gemm(M, true, true, M.dzb, y.cout, M.col, y.kp, M.g + y.woff, y.kp, y.cout, y.kp, (int)pix, splits);
+    }
     if (s != PPRS_OK) return s;
     if (l == 0) break;
     if (l == 4 || l == 3) {
@@ -1555,7 +1672,7 @@ void pprs_cnn_destroy(pprs_cnn* c) {
   (void)hipStreamSynchronize(M.stream);
   void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6m, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
                   M.a[1], M.a[2], M.a[3],
-                  M.a[4], M.u4, M.u5, M.col, M.dzb, M.z, M.y, M.dy, M.dcol, M.du, M.da[0],
+                  M.a[4], M.col, M.dzb, M.z, M.y, M.dy, M.dcol, M.du, M.da[0],
                   M.da[1], M.da[2], M.da[3], M.da[4], M.part, M.lpart, M.wflip};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -1630,7 +1747,7 @@ pprs_status pprs_cnn_forward(pprs_cnn* c, const float* x, int B, float* y) {
   CHK(hipSetDevice(M.device));
   pprs_status s = alloc_batch(M, B);
   if (s != PPRS_OK) return s;
-  s = forward(M, x, B, false);
+  s = forward(M, x, B);
   if (s != PPRS_OK) return s;
   CHK(hipMemcpyAsync(y, M.y, sizeof(float) * (size_t)B * 128 * 128 * 2, hipMemcpyDeviceToDevice, M.stream));
   CHK(hipStreamSynchronize(M.stream));
@@ -1645,7 +1762,7 @@ pprs_status pprs_cnn_gradients(pprs_cnn* c, const float* x, const float* target,
   CHK(hipSetDevice(M.device));
   pprs_status s = alloc_batch(M, B);
   if (s != PPRS_OK) return s;
-  if ((s = forward(M, x, B, true)) != PPRS_OK) return s;
+  if ((s = forward(M, x, B)) != PPRS_OK) return s;
   if ((s = backward(M, target, B, margin, loss)) != PPRS_OK) return s;
   if (grad_host) {
     CHK(hipMemcpyAsync(grad_host, M.g, sizeof(float) * M.n_params, hipMemcpyDeviceToHost, M.stream));

@@ -179,6 +179,28 @@ def test_gradients_match_fp64_reference():
         assert ew < 5e-2 and eb < 5e-2 and cos > 0.998
 
 
+@pytest.mark.parametrize("batch", [1, 3, 9])
+def test_gradients_of_small_batches(batch):
+    """The weight gradients' pixel shares follow from the batch (one sample of layer 3 is four units
+    of 64 pixels, three and nine leave uneven shares). Held to the FP64 reference per layer, bars of
+    the test above."""
+    torch = _torch()
+    net, p = _net_with_biases(13)
+    rng = np.random.default_rng(batch)
+    x = C.bf16_round(rng.normal(size=(batch, 128, 128, 2)).astype(np.float32))
+    t = rng.normal(0, 1.0, size=(batch, 128, 128, 2)).astype(np.float32)
+    loss, g = net.gradients(torch.tensor(x, device="cuda"), torch.tensor(t, device="cuda"),
+                            margin=4)
+    rloss, rg = C.loss_and_grad(_bf16_params(p), x, t, margin=4)
+    assert abs(loss - rloss) < 1e-2 * rloss
+    for l, (w, b) in enumerate(C.layout()[0]):
+        gw, rw = g[w:b], rg[w:b]
+        ew, eb = _rel(gw, rw), _rel(g[b:b + C.COUT[l]], rg[b:b + C.COUT[l]])
+        cos = float(np.dot(gw, rw) / (np.linalg.norm(gw) * np.linalg.norm(rw) + 1e-30))
+        say("B=%d layer %d: weight rel %.3e cos %.6f, bias rel %.3e" % (batch, l + 1, ew, cos, eb))
+        assert ew < 5e-2 and eb < 5e-2 and cos > 0.998
+
+
 def test_train_steps_reduce_loss():
     torch = _torch()
     import paper_1712_02533_amd as P
