@@ -9,10 +9,9 @@
 //   L6 [up2(L5), input] 66->2 (128^2, linear)
 // Activations are NHWC. Weights are [Cout][Kp] with k = (dy * 3 + dx) * Cin + ci, Kp = 9 Cin
 // rounded up to 32 (L1 to 64), padded with zeros. L2-L5 run as fused implicit-GEMM
-// convolutions on MFMAs (v_mfma_f32_16x16x32_bf16), L6 (2 output channels, its upsampled input
-// folded into the weights) on MFMAs with the FP32 folded weights in three exact BF16 parts, L1 (2
-// input channels) as a direct FP32 kernel. The weight gradients of L2-L5 are contracted over pixels by
-// k_wgrad; L1's goes through im2col and a GEMM.
+// convolutions on MFMAs (v_mfma_f32_16x16x32_bf16); L1 (2 input channels) and L6 (2 output
+// channels, its upsampled input folded into the weights) as direct FP32 kernels. The weight
+// gradients of L2-L5 are contracted over pixels by k_wgrad; L1's goes through im2col and a GEMM.
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 #include <ctype.h>
@@ -657,137 +656,91 @@ __global__ void k_f32_to_bf16(const float* __restrict__ x, long long count,
 // Last layer (66 -> 2 channels, stride 1), FP32 direct kernels. W6 is [2][9][66] fp32 (from the
 // bf16 copy), bias b6[2].
 
-// Last layer read straight from its sources, on MFMAs. Channels 0..63 are the nearest 2x
-// upsampling of the L5 output a5 [B][64][64][64]: output pixel (2Y + py, 2X + px) sees through its
-// 3x3 taps only the 2 x 2 source pixels (Y - 1 + py + i, X - 1 + px + j), i, j in {0, 1} (tap rows
+// Last layer read straight from its sources. Channels 0..63 are the nearest 2x upsampling of
+// the L5 output a5 [B][64][64][64]: output pixel (2Y + py, 2X + px) sees through its 3x3 taps
+// only the 2 x 2 source pixels (Y - 1 + py + i, X - 1 + px + j), i, j in {0, 1} (tap rows
 // {0} and {1, 2} land on source rows Y - 1 and Y when py = 0, {0, 1} and {2} on Y and Y + 1
 // when py = 1; columns alike), so the taps that land on one source pixel are summed into the
-// folded weights W6f [parity py px][i][j][output][64] (FP32, k_w6_prep). Channels 64, 65 are the
-// network input x0 [B][128][128][2] (9 taps).
-// All four parities of a source pixel are computed together, 8 outputs from its 3 x 3 source
-// neighbours (18 steps of 32 channels) and its 4 x 4 input pixels (one step). The FP32 folded
-// weights are the exact sum of three BF16 numbers (8 significant bits each, cut off toward
-// zero), which take three rows of the product each: nothing is rounded, the products are exact
-// and their sums FP32. Rows of the two 16-row weight tiles: 4 parity + {0, 1: the outputs' first
-// part, 2, 3: their second}; 4 parity + {0, 1: the third}. So a lane ends with one output pixel's
-// parts. Every value
-// is read from memory once but nine times through the first-level cache, which bounds the pass
-// (511 pairs: 279 us; the 368 MB from and to memory take 75); in FP32 on the ALUs, a parity at a
-// time, it took 400 us.
-// A wavefront takes 16 MT source pixels of a row; the weights (W6m, in operand order) sit in LDS.
-constexpr int L6_STEPS = 19;
-template <int MT>
-__global__ void __launch_bounds__(256, 2) k_l6_fused(const bf16* __restrict__ a5,
-                                                     const bf16* __restrict__ x0,
-                                                     const bf16* __restrict__ W6m,
-                                                     const float* __restrict__ b6, int Bn,
-                                                     float* __restrict__ Y) {
-  constexpr unsigned OUTSIDE = 0x80000000u;  // beyond every buffer: reads zero
-  __shared__ __attribute__((aligned(16))) bf16 sw[L6_STEPS * 2 * 64 * 8];
-  for (int e = threadIdx.x; e < L6_STEPS * 2 * 64; e += 256)
-    ((uint4*)sw)[e] = ((const uint4*)W6m)[e];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const float bias0 = b6[0], bias1 = b6[1];
-  const int units = Bn * 64 * (4 / MT);  // 16 MT source pixels each
-  for (int un = blockIdx.x * 4 + wave; un < units; un += gridDim.x * 4) {
-    const int part = un & (4 / MT - 1), row = un / (4 / MT), ys = row & 63, bb = row >> 6;
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a5 + (size_t)bb * 64 * 64 * 64), 0, 64 * 64 * 64 * 2, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(x0 + (size_t)bb * 128 * 128 * 2), 0, 128 * 128 * 2 * 2, 0x00020000);
-    f32x4 acc[MT][2];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto step = [&](int t, const u32x4 (&v)[MT]) {
-#pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        const bf16x8 w = *(const bf16x8*)&sw[((t * 2 + n) * 64 + lane) * 8];
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-          acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              w, __builtin_bit_cast(bf16x8, v[i]), acc[i][n], 0, 0, 0);
-      }
-    };
-    // the input pixels (2 ys - 1 + kq, 2 xs - 1 .. 2 xs + 2)
-    u32x4 vx[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const int xs = (part * MT + i) * 16 + col, yy = 2 * ys - 1 + kq;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int xx = 2 * xs - 1 + e;
-        const unsigned o = yy >= 0 && yy < 128 && xx >= 0 && xx < 128
-                               ? (unsigned)((yy * 128 + xx) * 4) : OUTSIDE;
-        vx[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, o, 0, 0);
-      }
-    }
-    // the source rows, the next one's loads in flight during a row's products
-    u32x4 v[2][6][MT];
-    auto fetch = [&](int r, u32x4 (&d)[6][MT]) {
-#pragma unroll
-      for (int k = 0; k < 6; ++k)
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const int xs = (part * MT + i) * 16 + col + k / 2 - 1, yy = ys + r - 1;
-          const unsigned o = yy >= 0 && yy < 64 && xs >= 0 && xs < 64
-                                 ? (unsigned)(((yy * 64 + xs) * 64 + 8 * kq) * 2) : OUTSIDE;
-          d[k][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, o + 64 * (k & 1), 0, 0);
-        }
-    };
-    // the weights are read from LDS for every unit: in registers across units they would leave
-    // none for the loads in flight
-    asm volatile("" ::: "memory");
-    fetch(0, v[0]);
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      if (r < 2) fetch(r + 1, v[(r + 1) & 1]);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int k = 0; k < 6; ++k) step(6 * r + k, v[r & 1][k]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    step(18, vx);
-    // lane: output pixel of parity kq at source column xs
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const int xs = (part * MT + i) * 16 + col;
-      float* o = Y + (((size_t)bb * 128 + 2 * ys + (kq >> 1)) * 128 + 2 * xs + (kq & 1)) * 2;
-      *(float2*)o = make_float2(bias0 + (acc[i][0][0] + (acc[i][0][2] + acc[i][1][0])),
-                                bias1 + (acc[i][0][1] + (acc[i][0][3] + acc[i][1][1])));
-    }
-  }
-}
-
-// The weights of k_l6_fused in operand order, from W6 [2][9][66] and W6f: step t, tile n, lane l,
-// element e. Each FP32 folded weight in three BF16 parts that sum to it exactly.
-__global__ void k_w6_mfma(const float* __restrict__ W6, const float* __restrict__ W6f,
-                          bf16* __restrict__ W6m) {
+// folded weights W6f [parity py px][i][j][output][64] (k_w6_prep): 4 source pixels of 64
+// channels instead of 9. Channels 64, 65 are the network input x0 [B][128][128][2] (9 taps,
+// weights W6 [2][9][66]). Eight lanes share an output pixel, lane g taking channels 8g .. 8g + 7
+// (one 16-byte piece of each source pixel, so a source pixel is one 128-byte line per 8 lanes)
+// and x0 tap g (and tap 8 on lane 0); the 8 partial sums are then added across the lanes.
+// One workgroup per (sample, parity, 32 source pixels of a row): a wave's parity is uniform.
+// On MFMAs, the FP32 folded weights in three BF16 parts, the pass took 280 us for 511 pairs where
+// this takes 400; but the predictions' last bits start registrations, which amplify them.
+__global__ void __launch_bounds__(256) k_l6_fused(const bf16* __restrict__ a5,
+                                                  const bf16* __restrict__ x0,
+                                                  const float* __restrict__ W6,
+                                                  const float* __restrict__ W6f,
+                                                  const float* __restrict__ b6, int Bn,
+                                                  float* __restrict__ Y) {
   constexpr int C = 66;
-  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < L6_STEPS * 2 * 64 * 8;
-       q += gridDim.x * blockDim.x) {
-    const int e = q & 7, l = (q >> 3) & 63, n = (q >> 9) & 1, t = q >> 10;
-    const int rowi = l & 15, kq = l >> 4, par = rowi >> 2, slot = rowi & 3;
-    const int py = par >> 1, px = par & 1, o = slot & 1;
-    const int piece = n == 0 ? slot >> 1 : slot < 2 ? 2 : 3;  // 3: an empty row
-    float w = 0.f;
-    if (t < 18) {
-      const int nb = t >> 1, i = nb / 3 - py, j = nb % 3 - px;  // dy + 1 - py, dx + 1 - px
-      if (i >= 0 && i < 2 && j >= 0 && j < 2)
-        w = W6f[(((par * 2 + i) * 2 + j) * 2 + o) * 64 + 32 * (t & 1) + 8 * kq + e];
-    } else {
-      const int ty = kq - py, tx = (e >> 1) - px;
-      if (ty >= 0 && ty < 3 && tx >= 0 && tx < 3)
-        w = W6[o * 9 * C + (ty * 3 + tx) * C + 64 + (e & 1)];
+  __shared__ __attribute__((aligned(16))) float wf[4 * 2 * 2 * 2 * 64];
+  for (int e = threadIdx.x; e < 4 * 2 * 2 * 2 * 64; e += blockDim.x) wf[e] = W6f[e];
+  __syncthreads();
+  const int g = threadIdx.x & 7;  // channel group
+  const int nblk = Bn * 4 * 64 * 2;  // (sample, parity, source row, half row)
+  for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+    const int half = blk & 1, ys = (blk >> 1) & 63, par = (blk >> 7) & 3, b = blk >> 9;
+    const int py = par >> 1, px = par & 1;
+    const int xs = half * 32 + (threadIdx.x >> 3);
+    const int y = 2 * ys + py, x = 2 * xs + px;
+    float s0 = g == 0 ? b6[0] : 0.f, s1 = g == 0 ? b6[1] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int sy = ys - 1 + py + i;
+      if (sy < 0 || sy >= 64) continue;  // uniform over the workgroup (one source row)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int sx = xs - 1 + px + j;
+        const bool ok = sx >= 0 && sx < 64;
+        uint4 v = ok ? *(const uint4*)(a5 + (((size_t)b * 64 + sy) * 64 + sx) * 64 + 8 * g)
+                     : make_uint4(0u, 0u, 0u, 0u);
+        const float* w0 = wf + (((par * 2 + i) * 2 + j) * 2) * 64 + 8 * g;
+        const f32x4 wa = *(const f32x4*)w0, wb = *(const f32x4*)(w0 + 4);
+        const f32x4 wc = *(const f32x4*)(w0 + 64), wd = *(const f32x4*)(w0 + 68);
+        const unsigned int h[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float lo = __uint_as_float(h[k] << 16), hi = __uint_as_float(h[k] & 0xffff0000u);
+          const float w0lo = k < 2 ? wa[2 * k] : wb[2 * k - 4];
+          const float w0hi = k < 2 ? wa[2 * k + 1] : wb[2 * k - 3];
+          const float w1lo = k < 2 ? wc[2 * k] : wd[2 * k - 4];
+          const float w1hi = k < 2 ? wc[2 * k + 1] : wd[2 * k - 3];
+          s0 = fmaf(w0lo, lo, s0);
+          s1 = fmaf(w1lo, lo, s1);
+          s0 = fmaf(w0hi, hi, s0);
+          s1 = fmaf(w1hi, hi, s1);
+        }
+      }
     }
-    // the part's 8 leading bits, cut off; what is not finite stays in the first part
-    float part = 0.f;
-    for (int k = 0; k <= piece && piece < 3; ++k) {
-      part = __uint_as_float(__float_as_uint(w) & 0xffff0000u);
-      w = isfinite(w) ? w - part : 0.f;
+    // x0 channels: lane g takes tap g, lane 0 also tap 8
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int tap = t == 0 ? g : 8;
+      if (t == 1 && g != 0) break;
+      const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
+      if (yy >= 0 && yy < 128 && xx >= 0 && xx < 128) {
+        const unsigned int v = *(const unsigned int*)(x0 + (((size_t)b * 128 + yy) * 128 + xx) * 2);
+        const float f0 = __uint_as_float(v << 16), f1 = __uint_as_float(v & 0xffff0000u);
+        s0 = fmaf(W6[tap * C + 64], f0, s0);
+        s1 = fmaf(W6[9 * C + tap * C + 64], f0, s1);
+        s0 = fmaf(W6[tap * C + 65], f1, s0);
+        s1 = fmaf(W6[9 * C + tap * C + 65], f1, s1);
+      }
     }
-    W6m[q] = __builtin_bit_cast(bf16, (unsigned short)(__float_as_uint(part) >> 16));
+    // the 8 channel groups' partial sums (lanes 8p .. 8p + 7), fixed order
+#pragma unroll
+    for (int m = 1; m < 8; m <<= 1) {
+      s0 += __shfl_xor(s0, m, 64);
+      s1 += __shfl_xor(s1, m, 64);
+    }
+    if (g == 0) {
+      const size_t o = (((size_t)b * 128 + y) * 128 + x) * 2;
+      Y[o] = s0;
+      Y[o + 1] = s1;
+    }
   }
 }
 
@@ -1117,7 +1070,6 @@ struct Model {
   bf16 *x0 = nullptr, *a[5] = {nullptr}, *col = nullptr, *dzb = nullptr;
   float *z = nullptr, *y = nullptr, *dy = nullptr, *dcol = nullptr, *du = nullptr,
         *da[5] = {nullptr}, *part = nullptr, *w6 = nullptr, *w6f = nullptr, *w1 = nullptr;
-  bf16* w6m = nullptr;  // the last layer's weights as MFMA operands
   double* lpart = nullptr;
   size_t part_floats = 0;
 };
@@ -1313,11 +1265,7 @@ static pprs_status forward(Model& M, const float* x, int B) {
   }
   // L6
   const Layer& y6 = M.L[5];
-  // 32 source pixels per wavefront, or 16 where that fills fewer than two workgroups per unit
-  if (B >= 16)
-    hipLaunchKernelGGL(k_l6_fused<2>, dim3(std::min(B * 32, 1024)), dim3(256), 0, st, M.a[4], M.x0, M.w6m, M.w + y6.boff, B, M.y);
-  else
-    hipLaunchKernelGGL(k_l6_fused<1>, dim3(B * 64), dim3(256), 0, st, M.a[4], M.x0, M.w6m, M.w + y6.boff, B, M.y);
+  hipLaunchKernelGGL(k_l6_fused, dim3(std::min(B * 512, 16384)), dim3(kBlock), 0, st, M.a[4], M.x0, M.w6, M.w6f, M.w + y6.boff, B, M.y);
   CHK(hipGetLastError());
   return PPRS_OK;
 }
@@ -1328,7 +1276,6 @@ static pprs_status forward(Model& M, const float* x, int B) {
 static pprs_status refresh_derived(Model& M) {
   const Layer& y6 = M.L[5];
   hipLaunchKernelGGL(k_w6_prep, dim3(1), dim3(kBlock), 0, M.stream, M.wb + y6.woff, M.w6, M.w6f);
-  hipLaunchKernelGGL(k_w6_mfma, dim3(76), dim3(kBlock), 0, M.stream, M.w6, M.w6f, M.w6m);
   hipLaunchKernelGGL(k_w1_prep, dim3(1), dim3(kBlock), 0, M.stream, M.wb + M.L[0].woff, M.L[0].kp, M.w1);
   for (int l = 3; l < 5; ++l) {
     const Layer& y = M.L[l];
@@ -1649,7 +1596,6 @@ pprs_status pprs_cnn_create(pprs_cnn** out, int device, void* stream, unsigned l
   if (e == hipSuccess) e = hipMalloc(&M.g, sizeof(float) * M.n_params);
   if (e == hipSuccess) e = hipMalloc(&M.wb, sizeof(bf16) * M.n_params);
   if (e == hipSuccess) e = hipMalloc(&M.w6, sizeof(float) * M.L[5].cout * M.L[5].kp);
-  if (e == hipSuccess) e = hipMalloc(&M.w6m, sizeof(bf16) * L6_STEPS * 2 * 64 * 8);
   if (e == hipSuccess) e = hipMalloc(&M.w1, sizeof(float) * 18 * 64);
   if (e == hipSuccess) e = hipMalloc(&M.w6f, sizeof(float) * 4 * 2 * 2 * 2 * 64);
   for (int l = 3; l < 5 && e == hipSuccess; ++l) {
@@ -1670,7 +1616,7 @@ void pprs_cnn_destroy(pprs_cnn* c) {
   Model& M = c->M;
   (void)hipSetDevice(M.device);
   (void)hipStreamSynchronize(M.stream);
-  void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6m, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
+  void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
                   M.a[1], M.a[2], M.a[3],
                   M.a[4], M.col, M.dzb, M.z, M.y, M.dy, M.dcol, M.du, M.da[0],
                   M.da[1], M.da[2], M.da[3], M.da[4], M.part, M.lpart, M.wflip};
