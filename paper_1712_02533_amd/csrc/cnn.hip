@@ -656,6 +656,12 @@ __global__ void k_f32_to_bf16(const float* __restrict__ x, long long count,
 // Last layer (66 -> 2 channels, stride 1), FP32 direct kernels. W6 is [2][9][66] fp32 (from the
 // bf16 copy), bias b6[2].
 
+// A float from the lane a DPP control names (all lanes have a source).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
 // Last layer read straight from its sources. Channels 0..63 are the nearest 2x upsampling of
 // the L5 output a5 [B][64][64][64]: output pixel (2Y + py, 2X + px) sees through its 3x3 taps
 // only the 2 x 2 source pixels (Y - 1 + py + i, X - 1 + px + j), i, j in {0, 1} (tap rows
@@ -666,9 +672,13 @@ __global__ void k_f32_to_bf16(const float* __restrict__ x, long long count,
 // weights W6 [2][9][66]). Eight lanes share an output pixel, lane g taking channels 8g .. 8g + 7
 // (one 16-byte piece of each source pixel, so a source pixel is one 128-byte line per 8 lanes)
 // and x0 tap g (and tap 8 on lane 0); the 8 partial sums are then added across the lanes.
-// One workgroup per (sample, parity, 32 source pixels of a row): a wave's parity is uniform.
-// On MFMAs, the FP32 folded weights in three BF16 parts, the pass took 280 us for 511 pairs where
-// this takes 400; but the predictions' last bits start registrations, which amplify them.
+// A workgroup takes one (parity, 32 source pixels of a row) of NB samples at a time: its folded
+// weights (2 KB of LDS) are read once per NB samples, and NB samples' source pixels are in flight
+// together. Bound by the FP32 ALUs (unpacking and FMAs) and those loads: for 511 pairs one sample
+// at a time with the parities' 8 KB took 400 us, NB = 4 takes 328. On MFMAs, the FP32 weights in
+// three BF16 parts, the pass took 280; but the predictions' last bits start registrations, which
+// amplify them. Lanes add up by DPP moves (pairs, pairs of pairs, the mirrored half row).
+template <int NB>
 __global__ void __launch_bounds__(256) k_l6_fused(const bf16* __restrict__ a5,
                                                   const bf16* __restrict__ x0,
                                                   const float* __restrict__ W6,
@@ -676,42 +686,61 @@ __global__ void __launch_bounds__(256) k_l6_fused(const bf16* __restrict__ a5,
                                                   const float* __restrict__ b6, int Bn,
                                                   float* __restrict__ Y) {
   constexpr int C = 66;
-  __shared__ __attribute__((aligned(16))) float wf[4 * 2 * 2 * 2 * 64];
-  for (int e = threadIdx.x; e < 4 * 2 * 2 * 2 * 64; e += blockDim.x) wf[e] = W6f[e];
-  __syncthreads();
+  __shared__ __attribute__((aligned(16))) float wf[2 * 2 * 2 * 64];
   const int g = threadIdx.x & 7;  // channel group
-  const int nblk = Bn * 4 * 64 * 2;  // (sample, parity, source row, half row)
-  for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const int half = blk & 1, ys = (blk >> 1) & 63, par = (blk >> 7) & 3, b = blk >> 9;
-    const int py = par >> 1, px = par & 1;
-    const int xs = half * 32 + (threadIdx.x >> 3);
-    const int y = 2 * ys + py, x = 2 * xs + px;
-    float s0 = g == 0 ? b6[0] : 0.f, s1 = g == 0 ? b6[1] : 0.f;
+  // the grid is a multiple of 512 workgroups: all samples of a workgroup share parity and row
+  const int half = blockIdx.x & 1, ys = (blockIdx.x >> 1) & 63, par = (blockIdx.x >> 7) & 3;
+  const int py = par >> 1, px = par & 1;
+  for (int e = threadIdx.x; e < 2 * 2 * 2 * 64; e += blockDim.x) wf[e] = W6f[par * 512 + e];
+  __syncthreads();
+  const int xs = half * 32 + (threadIdx.x >> 3);
+  const int y = 2 * ys + py, x = 2 * xs + px;
+  const int per = (Bn + NB - 1) / NB;  // samples b, b + per, ... of an iteration
+  for (int b0 = blockIdx.x >> 9; b0 < per; b0 += gridDim.x >> 9) {
+    float s0[NB], s1[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      s0[q] = g == 0 ? b6[0] : 0.f;
+      s1[q] = g == 0 ? b6[1] : 0.f;
+    }
+    uint4 v[2][2][NB];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int sy = ys - 1 + py + i, sx = xs - 1 + px + j;
+        const bool ok = sy >= 0 && sy < 64 && sx >= 0 && sx < 64;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const int b = min(b0 + q * per, Bn - 1);
+          v[i][j][q] = ok ? *(const uint4*)(a5 + (((size_t)b * 64 + sy) * 64 + sx) * 64 + 8 * g)
+                          : make_uint4(0u, 0u, 0u, 0u);
+        }
+      }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int sy = ys - 1 + py + i;
       if (sy < 0 || sy >= 64) continue;  // uniform over the workgroup (one source row)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int sx = xs - 1 + px + j;
-        const bool ok = sx >= 0 && sx < 64;
-        uint4 v = ok ? *(const uint4*)(a5 + (((size_t)b * 64 + sy) * 64 + sx) * 64 + 8 * g)
-                     : make_uint4(0u, 0u, 0u, 0u);
-        const float* w0 = wf + (((par * 2 + i) * 2 + j) * 2) * 64 + 8 * g;
+        const float* w0 = wf + (i * 2 + j) * 2 * 64 + 8 * g;
         const f32x4 wa = *(const f32x4*)w0, wb = *(const f32x4*)(w0 + 4);
         const f32x4 wc = *(const f32x4*)(w0 + 64), wd = *(const f32x4*)(w0 + 68);
-        const unsigned int h[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float lo = __uint_as_float(h[k] << 16), hi = __uint_as_float(h[k] & 0xffff0000u);
-          const float w0lo = k < 2 ? wa[2 * k] : wb[2 * k - 4];
-          const float w0hi = k < 2 ? wa[2 * k + 1] : wb[2 * k - 3];
-          const float w1lo = k < 2 ? wc[2 * k] : wd[2 * k - 4];
-          const float w1hi = k < 2 ? wc[2 * k + 1] : wd[2 * k - 3];
-          s0 = fmaf(w0lo, lo, s0);
-          s1 = fmaf(w1lo, lo, s1);
-          s0 = fmaf(w0hi, hi, s0);
-          s1 = fmaf(w1hi, hi, s1);
+        for (int q = 0; q < NB; ++q) {
+          const unsigned int h[4] = {v[i][j][q].x, v[i][j][q].y, v[i][j][q].z, v[i][j][q].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float lo = __uint_as_float(h[k] << 16), hi = __uint_as_float(h[k] & 0xffff0000u);
+            const float w0lo = k < 2 ? wa[2 * k] : wb[2 * k - 4];
+            const float w0hi = k < 2 ? wa[2 * k + 1] : wb[2 * k - 3];
+            const float w1lo = k < 2 ? wc[2 * k] : wd[2 * k - 4];
+            const float w1hi = k < 2 ? wc[2 * k + 1] : wd[2 * k - 3];
+            s0[q] = fmaf(w0lo, lo, s0[q]);
+            s1[q] = fmaf(w1lo, lo, s1[q]);
+            s0[q] = fmaf(w0hi, hi, s0[q]);
+            s1[q] = fmaf(w1hi, hi, s1[q]);
+          }
         }
       }
     }
@@ -722,24 +751,35 @@ __global__ void __launch_bounds__(256) k_l6_fused(const bf16* __restrict__ a5,
       if (t == 1 && g != 0) break;
       const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
       if (yy >= 0 && yy < 128 && xx >= 0 && xx < 128) {
-        const unsigned int v = *(const unsigned int*)(x0 + (((size_t)b * 128 + yy) * 128 + xx) * 2);
-        const float f0 = __uint_as_float(v << 16), f1 = __uint_as_float(v & 0xffff0000u);
-        s0 = fmaf(W6[tap * C + 64], f0, s0);
-        s1 = fmaf(W6[9 * C + tap * C + 64], f0, s1);
-        s0 = fmaf(W6[tap * C + 65], f1, s0);
-        s1 = fmaf(W6[9 * C + tap * C + 65], f1, s1);
+        const float wa = W6[tap * C + 64], wb = W6[9 * C + tap * C + 64];
+        const float wc = W6[tap * C + 65], wd = W6[9 * C + tap * C + 65];
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const int b = min(b0 + q * per, Bn - 1);
+          const unsigned int u =
+              *(const unsigned int*)(x0 + (((size_t)b * 128 + yy) * 128 + xx) * 2);
+          const float f0 = __uint_as_float(u << 16), f1 = __uint_as_float(u & 0xffff0000u);
+          s0[q] = fmaf(wa, f0, s0[q]);
+          s1[q] = fmaf(wb, f0, s1[q]);
+          s0[q] = fmaf(wc, f1, s0[q]);
+          s1[q] = fmaf(wd, f1, s1[q]);
+        }
       }
     }
-    // the 8 channel groups' partial sums (lanes 8p .. 8p + 7), fixed order
 #pragma unroll
-    for (int m = 1; m < 8; m <<= 1) {
-      s0 += __shfl_xor(s0, m, 64);
-      s1 += __shfl_xor(s1, m, 64);
-    }
-    if (g == 0) {
-      const size_t o = (((size_t)b * 128 + y) * 128 + x) * 2;
-      Y[o] = s0;
-      Y[o + 1] = s1;
+    for (int q = 0; q < NB; ++q) {
+      // the 8 channel groups' partial sums (lanes 8p .. 8p + 7), fixed order: lane pairs, pairs
+      // of pairs, then the mirrored half row (whose four lanes all hold the other four's sum)
+      float t0 = s0[q], t1 = s1[q];
+      t0 += dpp_f<0xb1>(t0);  // quad_perm 1, 0, 3, 2
+      t1 += dpp_f<0xb1>(t1);
+      t0 += dpp_f<0x4e>(t0);  // quad_perm 2, 3, 0, 1
+      t1 += dpp_f<0x4e>(t1);
+      t0 += dpp_f<0x141>(t0);  // row_half_mirror
+      t1 += dpp_f<0x141>(t1);
+      const int b = b0 + q * per;
+      if (g == 0 && b < Bn)
+        *(float2*)(Y + (((size_t)b * 128 + y) * 128 + x) * 2) = make_float2(t0, t1);
     }
   }
 }
@@ -1265,7 +1305,14 @@ static pprs_status forward(Model& M, const float* x, int B) {
   }
   // L6
   const Layer& y6 = M.L[5];
-  hipLaunchKernelGGL(k_l6_fused, dim3(std::min(B * 512, 16384)), dim3(kBlock), 0, st, M.a[4], M.x0, M.w6, M.w6f, M.w + y6.boff, B, M.y);
+  // four samples per workgroup where that still leaves 16 workgroups per CU (328 us for 511
+  // pairs, 400 one by one); the sums are the same
+  if (B >= 32)
+    hipLaunchKernelGGL(k_l6_fused<4>, dim3(512 * std::min((B + 3) / 4, 32)), dim3(kBlock), 0, st,
+                       M.a[4], M.x0, M.w6, M.w6f, M.w + y6.boff, B, M.y);
+  else
+    hipLaunchKernelGGL(k_l6_fused<1>, dim3(512 * B), dim3(kBlock), 0, st, M.a[4], M.x0, M.w6,
+                       M.w6f, M.w + y6.boff, B, M.y);
   CHK(hipGetLastError());
   return PPRS_OK;
 }

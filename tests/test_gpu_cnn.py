@@ -53,7 +53,7 @@ def _rel(a, b):
     return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-30))
 
 
-@pytest.mark.parametrize("batch", [1, 2, 7, 15, 16, 17, 65])
+@pytest.mark.parametrize("batch", [1, 2, 7, 15, 16, 17, 31, 32, 65, 133])
 def test_forward_does_not_depend_on_the_batch(batch):
     """The convolutions' tile (64 to 256 pixels) and the last layer's follow from the batch; every
     output is the same sum in the same order whatever they are. Each sample of a batch (sizes where
