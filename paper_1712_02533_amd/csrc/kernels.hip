@@ -51,6 +51,16 @@ __device__ __forceinline__ P* uni(P* p) {
   unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
   return (P*)(((unsigned long long)hi << 32) | lo);
 }
+// A wave-uniform value in scalar registers.
+__device__ __forceinline__ float uni_f(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ double uni_d(double v) {
+  unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+  unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 // floor(x) converted to int in one instruction (v_cvt_flr_i32_f32; 0 for NaN like a plain
 // conversion).
 __device__ __forceinline__ int cvt_flr(float x) {
@@ -88,14 +98,10 @@ __device__ __forceinline__ f32x4 ld_coef(const float* C, unsigned o) {
 }
 
 // Clamped bilinear sample of nodal g (n x n) at column bi + tx, row ai + ty (cells).
-// Returns value; writes the gradient in domain units when grad is true (zero across a
-// coordinate whose position lies outside the level). The position is clamped to the level
-// first and the cell index to n - 2, so a position on or beyond the far edge is cell n - 2 at
-// fraction 1; inside, the fraction is tx - floor(tx).
-template <bool GRAD>
+// The position is clamped to the level first and the cell index to n - 2, so a position on or
+// beyond the far edge is cell n - 2 at fraction 1; inside, the fraction is tx - floor(tx).
 __device__ __forceinline__ float sample_bil(const float* __restrict__ g, int n, int bi,
-                                            float tx, int ai, float ty, float inv_h,
-                                            float* gx, float* gy) {
+                                            float tx, int ai, float ty) {
   float cx = __builtin_amdgcn_fmed3f(tx, (float)(-bi), (float)(n - 1 - bi));
   float cy = __builtin_amdgcn_fmed3f(ty, (float)(-ai), (float)(n - 1 - ai));
   int ix = min(cvt_flr(cx), n - 2 - bi), iy = min(cvt_flr(cy), n - 2 - ai);
@@ -106,10 +112,6 @@ __device__ __forceinline__ float sample_bil(const float* __restrict__ g, int n, 
   float v00 = r0.x, v01 = r0.y, v10 = r1.x, v11 = r1.y;
   float top = fmaf(fx, v01 - v00, v00);
   float bot = fmaf(fx, v11 - v10, v10);
-  if (GRAD) {
-    *gx = cx != tx ? 0.f : fmaf(fy, (v11 - v10) - (v01 - v00), v01 - v00) * inv_h;
-    *gy = cy != ty ? 0.f : (bot - top) * inv_h;
-  }
   return fmaf(fy, bot - top, top);
 }
 
@@ -121,23 +123,41 @@ __device__ __forceinline__ float sample_bil(const float* __restrict__ g, int n, 
 // records' fourfold footprint in the caches. The cell index is clamped to the last cell (ixmax, iymax relative to the
 // node), so a position on the far edge is the last cell at fraction 1 and its gradient that
 // cell's slope; across a coordinate clamped to the level the gradient is zero.
+// In two parts, as CellSample.
+struct GradSample {
+  f32x2u r0, r1;
+  float fx, fy;
+  bool inx, iny;
+  __device__ __forceinline__ void issue(const float* T0, const float* T1, unsigned n4,
+                                        unsigned base4, float lox, float hix, float loy,
+                                        float hiy, int ixmax, int iymax, float tx, float ty) {
+    float cx = __builtin_amdgcn_fmed3f(tx, lox, hix);
+    float cy = __builtin_amdgcn_fmed3f(ty, loy, hiy);
+    int ix = min(cvt_flr(cx), ixmax), iy = min(cvt_flr(cy), iymax);
+    fx = cx - (float)ix;
+    fy = cy - (float)iy;
+    inx = cx == tx;
+    iny = cy == ty;
+    unsigned o = (unsigned)mad24(iy, (int)n4, (int)(base4 + ((unsigned)ix << 2)));
+    r0 = ld_pair(T0, o);
+    r1 = ld_pair(T1, o);
+  }
+  __device__ __forceinline__ float value(float inv_h, float* gx, float* gy) const {
+    float d0 = r0.y - r0.x, d1 = r1.y - r1.x;
+    float top = fmaf(fx, d0, r0.x);
+    float bot = fmaf(fx, d1, r1.x);
+    *gx = !inx ? 0.f : fmaf(fy, d1 - d0, d0) * inv_h;
+    *gy = !iny ? 0.f : (bot - top) * inv_h;
+    return fmaf(fy, bot - top, top);
+  }
+};
 __device__ __forceinline__ float sample_grad(const float* T0, const float* T1, unsigned n4,
                                              unsigned base4, float lox, float hix, float loy,
                                              float hiy, int ixmax, int iymax, float tx,
                                              float ty, float inv_h, float* gx, float* gy) {
-  float cx = __builtin_amdgcn_fmed3f(tx, lox, hix);
-  float cy = __builtin_amdgcn_fmed3f(ty, loy, hiy);
-  int ix = min(cvt_flr(cx), ixmax), iy = min(cvt_flr(cy), iymax);
-  float fx = cx - (float)ix, fy = cy - (float)iy;
-  unsigned o = (unsigned)mad24(iy, (int)n4, (int)(base4 + ((unsigned)ix << 2)));
-  f32x2u r0 = ld_pair(T0, o);
-  f32x2u r1 = ld_pair(T1, o);
-  float d0 = r0.y - r0.x, d1 = r1.y - r1.x;
-  float top = fmaf(fx, d0, r0.x);
-  float bot = fmaf(fx, d1, r1.x);
-  *gx = cx != tx ? 0.f : fmaf(fy, d1 - d0, d0) * inv_h;
-  *gy = cy != ty ? 0.f : (bot - top) * inv_h;
-  return fmaf(fy, bot - top, top);
+  GradSample s;
+  s.issue(T0, T1, n4, base4, lox, hix, loy, hiy, ixmax, iymax, tx, ty);
+  return s.value(inv_h, gx, gy);
 }
 
 // The two Gauss points of [0, 1] (2-point rule), as compile-time constants.
@@ -167,16 +187,29 @@ struct QuadField {
 // the level's bounds relative to that node); the cell is floor of the clamped position and the
 // fraction its remainder, so a position on the far edge takes the last node at fraction 0 (its
 // value, as with the cell before it at fraction 1). c0 + fx c1 + fy (c2 + fx c3).
+// In two parts, so that a caller can issue several samples' loads before it uses the first.
+struct CellSample {
+  f32x4 c;
+  float fx, fy;
+  __device__ __forceinline__ void issue(const float* C, unsigned n16, unsigned base16, float lox,
+                                        float hix, float loy, float hiy, float tx, float ty) {
+    float cx = __builtin_amdgcn_fmed3f(tx, lox, hix);
+    float cy = __builtin_amdgcn_fmed3f(ty, loy, hiy);
+    int ix = cvt_flr(cx), iy = cvt_flr(cy);
+    fx = __builtin_amdgcn_fractf(cx);
+    fy = __builtin_amdgcn_fractf(cy);
+    c = ld_coef(C, (unsigned)mad24(iy, (int)n16, (int)(base16 + ((unsigned)ix << 4))));
+  }
+  __device__ __forceinline__ float value() const {
+    return fmaf(fy, fmaf(fx, c.w, c.z), fmaf(fx, c.y, c.x));
+  }
+};
 __device__ __forceinline__ float sample_cells(const float* C, unsigned n16, unsigned base16,
                                               float lox, float hix, float loy, float hiy,
                                               float tx, float ty) {
-  float cx = __builtin_amdgcn_fmed3f(tx, lox, hix);
-  float cy = __builtin_amdgcn_fmed3f(ty, loy, hiy);
-  int ix = cvt_flr(cx), iy = cvt_flr(cy);
-  float fx = __builtin_amdgcn_fractf(cx), fy = __builtin_amdgcn_fractf(cy);
-  unsigned o = (unsigned)mad24(iy, (int)n16, (int)(base16 + ((unsigned)ix << 4)));
-  f32x4 c = ld_coef(C, o);
-  return fmaf(fy, fmaf(fx, c.w, c.z), fmaf(fx, c.y, c.x));
+  CellSample s;
+  s.issue(C, n16, base16, lox, hix, loy, hiy, tx, ty);
+  return s.value();
 }
 
 // One DPP step of a wave reduction on a double: each lane the row mask enables takes the value
@@ -1982,8 +2015,8 @@ __global__ void __launch_bounds__(BLOCK) k_compose(const float* elems, long long
     int a = i / n, b = i % n;
     float ux = ul[i], uy = ul[nn + i];
     float tx = ux * inv_h, ty = uy * inv_h;
-    float vx = sample_bil<false>(ur, n, b, tx, a, ty, inv_h, nullptr, nullptr);
-    float vy = sample_bil<false>(ur + nn, n, b, tx, a, ty, inv_h, nullptr, nullptr);
+    float vx = sample_bil(ur, n, b, tx, a, ty);
+    float vy = sample_bil(ur + nn, n, b, tx, a, ty);
     w[i] = ux + vx;
     w[nn + i] = uy + vy;
   }
@@ -2057,8 +2090,8 @@ __global__ void __launch_bounds__(BLOCK) k_pool_compose(BatchDesc* D, int L, con
     int a = i / n, b = i % n;
     float ux = ul[i], uy = ul[nn + i];
     float tx = ux * inv_h, ty = uy * inv_h;
-    float vx = sample_bil<false>(ur, n, b, tx, a, ty, inv_h, nullptr, nullptr);
-    float vy = sample_bil<false>(ur + nn, n, b, tx, a, ty, inv_h, nullptr, nullptr);
+    float vx = sample_bil(ur, n, b, tx, a, ty);
+    float vy = sample_bil(ur + nn, n, b, tx, a, ty);
     w[i] = ux + vx;
     w[nn + i] = uy + vy;
   }
@@ -2173,15 +2206,15 @@ __global__ void __launch_bounds__(BLOCK) k_from_nodes_idx(const float* vbuf,
 // however far the point is from the rotation centre. Per element the node's offset is taken
 // in FP64, per quadrature point the small (R - I)(xi, eta) is added in FP32.
 struct RigidMap {
-  double cm1, s, ox, oy;  // cos - 1 (as -2 sin^2(a/2)), sin, t / h (cells)
+  double cm1, s, ox, oy;  // cos - 1 (as -2 sin^2(a/2)), sin, t / h (cells); all uniform
 };
 __device__ __forceinline__ RigidMap rigid_map(double a, double t0, double t1, int n) {
   RigidMap m;
   double sh = sin(0.5 * a);
-  m.cm1 = -2.0 * sh * sh;
-  m.s = sin(a);
-  m.ox = t0 * (n - 1);
-  m.oy = t1 * (n - 1);
+  m.cm1 = uni_d(-2.0 * sh * sh);
+  m.s = uni_d(sin(a));
+  m.ox = uni_d(t0 * (n - 1));
+  m.oy = uni_d(t1 * (n - 1));
   return m;
 }
 // offset (cells) of node (a, b) under the map
@@ -2194,6 +2227,12 @@ __device__ __forceinline__ void rigid_node_offset(const RigidMap& m, int a, int 
 // Energy of the rigid parameters (MODE 0: at rp for slots starting a level; MODE 1: at
 // rp - tau_j rd for the NC steps of a line-search pass), one element tile. Partials as the
 // field energy pass's, the three regulariser columns zero.
+// Bound by the vector ALUs (about 270 operations per element at three rungs, 80% of the pass)
+// and the gathers' latency. Left to itself the compiler waited for each of an element's 4 NC
+// gathers before the next address (68% of the wavefronts' cycles waiting) and kept the maps'
+// uniform values in vector registers; a rung's four gathers in flight and the uniform values in
+// scalar registers (122 -> 91 VGPRs, five wavefronts per SIMD) take a pass of 48 slots at 1024^2
+// from 12.1 to 8.8 ps per node. Eight in flight take 127 registers and 8.9 ps.
 template <int MODE, int NC>
 __device__ __forceinline__ void rigid_energy_item(const BatchDesc* D, int s, int t, float* s_r,
                                                   double* s_stage) {
@@ -2218,6 +2257,17 @@ __device__ __forceinline__ void rigid_energy_item(const BatchDesc* D, int s, int
       mp[j] = rigid_map(stp->rp[0] - tj * stp->rd[0], stp->rp[1] - tj * stp->rd[1],
                         stp->rp[2] - tj * stp->rd[2], n);
     }
+    // (R - I)(xi, eta) of the four Gauss points, uniform
+    float qx[NC][4], qy[NC][4];
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+#pragma unroll
+      for (int pt = 0; pt < 4; ++pt) {
+        const float xi = pt & 1 ? kGP1 : kGP0, eta = pt & 2 ? kGP1 : kGP0;
+        const float cm1 = (float)mp[j].cm1, sn = (float)mp[j].s;
+        qx[j][pt] = uni_f(fmaf(cm1, xi, -sn * eta));
+        qy[j][pt] = uni_f(fmaf(sn, xi, cm1 * eta));
+      }
     int ntx = (n - 1 + ET_X - 1) / ET_X;
     int e0x = (t % ntx) * ET_X, e0y = (t / ntx) * ET_Y;
     __syncthreads();
@@ -2256,24 +2306,36 @@ __device__ __forceinline__ void rigid_energy_item(const BatchDesc* D, int s, int
       const float lox = (float)(-b), hix = (float)(n - 1 - b);
       const float loy = (float)(-a), hiy = (float)(n - 1 - a);
       const unsigned base16 = (unsigned)mad24(a, n, b) << 4;
+      float rq[4];
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
+      for (int pt = 0; pt < 4; ++pt) {
+        const float xi = pt & 1 ? kGP1 : kGP0, eta = pt & 2 ? kGP1 : kGP0;
+        float p0 = (1.f - xi) * (1.f - eta), p1 = xi * (1.f - eta), p2 = (1.f - xi) * eta, p3 = xi * eta;
+        rq[pt] = p0 * rr[0] + p1 * rr[1] + p2 * rr[2] + p3 * rr[3];
+      }
+      // the four Gauss points of a rung in flight
+      CellSample smp[4];
+      auto issue = [&](int j) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const float xi = q ? kGP1 : kGP0, eta = p ? kGP1 : kGP0;
-          float p0 = (1.f - xi) * (1.f - eta), p1 = xi * (1.f - eta), p2 = (1.f - xi) * eta, p3 = xi * eta;
-          float rq = p0 * rr[0] + p1 * rr[1] + p2 * rr[2] + p3 * rr[3];
-#pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            float cm1 = (float)mp[j].cm1, sn = (float)mp[j].s;
-            float tx = xi + (ndx[j] + fmaf(cm1, xi, -sn * eta));
-            float ty = eta + (ndy[j] + fmaf(sn, xi, cm1 * eta));
-            float tv = sample_cells(TC, n16, base16, lox, hix, loy, hiy, tx, ty);
-            es[3 * j + 0] += tv;
-            es[3 * j + 1] = fmaf(tv, tv, es[3 * j + 1]);
-            es[3 * j + 2] = fmaf(tv, rq, es[3 * j + 2]);
-          }
+        for (int pt = 0; pt < 4; ++pt) {
+          const float xi = pt & 1 ? kGP1 : kGP0, eta = pt & 2 ? kGP1 : kGP0;
+          float tx = xi + (ndx[j] + qx[j][pt]);
+          float ty = eta + (ndy[j] + qy[j][pt]);
+          smp[pt].issue(TC, n16, base16, lox, hix, loy, hiy, tx, ty);
         }
+      };
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        issue(j);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int pt = 0; pt < 4; ++pt) {
+          const float tv = smp[pt].value();
+          es[3 * j + 0] += tv;
+          es[3 * j + 1] = fmaf(tv, tv, es[3 * j + 1]);
+          es[3 * j + 2] = fmaf(tv, rq[pt], es[3 * j + 2]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     double acc[NV];
@@ -2301,7 +2363,11 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_energy_step(const BatchDesc Dv)
                     [&](int s, int t) { rigid_energy_item<1, NC>(D, s, t, s_r, s_stage); });
 }
 
-// Parameter gradient of the slots in GRAD: three FP64 partials per element tile.
+// Parameter gradient of the slots in GRAD: three FP64 partials per element tile. Bound by the
+// vector ALUs (84% of the pass): relative positions and scalar uniform values as in the field
+// gradient, an element's four samples in flight: 48 slots at 1024^2 5.9 -> 4.8 ps per node. A
+// second copy of the loop without clamping for tiles that map inside the level gives 2% more,
+// not worth it.
 __global__ void __launch_bounds__(BLOCK) k_rigid_grad(const BatchDesc Dv) {
   const BatchDesc* D = &Dv;
   constexpr int NXN = ET_X + 1, NYN = ET_Y + 1, NN = NXN * NYN;
@@ -2314,8 +2380,18 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_grad(const BatchDesc Dv) {
     int n = lvl_n(l);
     const float* R = uni(D->pyr + stp->roff);
     const float* T = uni(D->pyr + stp->toff);
+    const float* T1 = T + n;
+    const unsigned n4 = (unsigned)n << 2;
     RigidMap mp = rigid_map(stp->rp[0], stp->rp[1], stp->rp[2], n);
-    const float cm1 = (float)mp.cm1, sn = (float)mp.s, cs = (float)cos(stp->rp[0]);
+    const float cm1 = (float)mp.cm1, sn = (float)mp.s, cs = uni_f((float)cos(stp->rp[0]));
+    // (R - I)(xi, eta) of the four Gauss points, uniform
+    float qx[4], qy[4];
+#pragma unroll
+    for (int pt = 0; pt < 4; ++pt) {
+      const float xi = pt & 1 ? kGP1 : kGP0, eta = pt & 2 ? kGP1 : kGP0;
+      qx[pt] = uni_f(fmaf(cm1, xi, -sn * eta));
+      qy[pt] = uni_f(fmaf(sn, xi, cm1 * eta));
+    }
     double sg = stp->sigma;
     float inv_sig = sg > 0.0 ? (float)(1.0 / sg) : 0.f;
     float ncc = (float)stp->ncc, mean = (float)stp->mean;
@@ -2351,25 +2427,31 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_grad(const BatchDesc Dv) {
       float rr[4] = {s_r[k00], s_r[k00 + 1], s_r[k00 + NXN], s_r[k00 + NXN + 1]};
       float ndx, ndy;
       rigid_node_offset(mp, a, b, ndx, ndy);
+      const float lox = (float)(-b), hix = (float)(n - 1 - b);
+      const float loy = (float)(-a), hiy = (float)(n - 1 - a);
+      const unsigned base4 = (unsigned)mad24(a, n, b) << 2;
+      GradSample smp[4];  // the four Gauss points in flight together
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
+      for (int pt = 0; pt < 4; ++pt) {
+        const float xi = pt & 1 ? kGP1 : kGP0, eta = pt & 2 ? kGP1 : kGP0;
+        smp[pt].issue(T, T1, n4, base4, lox, hix, loy, hiy, n - 2 - b, n - 2 - a,
+                      xi + (ndx + qx[pt]), eta + (ndy + qy[pt]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const float xi = q ? kGP1 : kGP0, eta = p ? kGP1 : kGP0;
-          float p0 = (1.f - xi) * (1.f - eta), p1 = xi * (1.f - eta), p2 = (1.f - xi) * eta, p3 = xi * eta;
-          float rq = p0 * rr[0] + p1 * rr[1] + p2 * rr[2] + p3 * rr[3];
-          float tx = xi + (ndx + fmaf(cm1, xi, -sn * eta));
-          float ty = eta + (ndy + fmaf(sn, xi, cm1 * eta));
-          float gx, gy;
-          float tv = sample_bil<true>(T, n, b, tx, a, ty, inv_h, &gx, &gy);
-          float f = -w * (rq - ncc * (tv - mean) * inv_sig) * inv_sig;
-          // dphi/dalpha = R'(alpha) q in domain units
-          float qxd = ((float)b + xi) * h, qyd = ((float)a + eta) * h;
-          float dax = -sn * qxd - cs * qyd, day = cs * qxd - sn * qyd;
-          ga += f * (gx * dax + gy * day);
-          g0 += f * gx;
-          g1 += f * gy;
-        }
+      for (int pt = 0; pt < 4; ++pt) {
+        const float xi = pt & 1 ? kGP1 : kGP0, eta = pt & 2 ? kGP1 : kGP0;
+        float p0 = (1.f - xi) * (1.f - eta), p1 = xi * (1.f - eta), p2 = (1.f - xi) * eta, p3 = xi * eta;
+        float rq = p0 * rr[0] + p1 * rr[1] + p2 * rr[2] + p3 * rr[3];
+        float gx, gy;
+        float tv = smp[pt].value(inv_h, &gx, &gy);
+        float f = -w * (rq - ncc * (tv - mean) * inv_sig) * inv_sig;
+        // dphi/dalpha = R'(alpha) q in domain units
+        float qxd = ((float)b + xi) * h, qyd = ((float)a + eta) * h;
+        float dax = -sn * qxd - cs * qyd, day = cs * qxd - sn * qyd;
+        ga += f * (gx * dax + gy * day);
+        g0 += f * gx;
+        g1 += f * gy;
       }
     }
     const double acc[3] = {(double)ga, (double)g0, (double)g1};
