@@ -909,67 +909,139 @@ __global__ void __launch_bounds__(256) k_l6_bwd_a5(const float* __restrict__ dY,
   }
 }
 
-// L6 weight and bias gradients by tiles: one block per 16x16 tile of output positions of one
-// 128 x 128 image. The tile's 18x18 halo of the layer input U (zero outside the image: channels
-// 0..63 the 2x upsampled L5 output a5 [B][64][64][64], read through the halving of the
-// position; 64, 65 the network input x0 [B][128][128][2]) and its dY are staged in LDS; each
-// thread sums, over the tile's 256 positions in order, dY(p, o) U(p + tap, c) for both
-// outputs o of its (tap, c) pairs, or dY(p, o) for the bias. Per-block partials
-// [block][2 * 9 * C + 2] (weights o-major as in the layer, then the two biases), summed over
-// blocks in a fixed order by k_colsum_final. C == L6C.
-constexpr int L6T = 16, L6H = L6T + 2, L6C = 66;
-__global__ void __launch_bounds__(256) k_l6_bwd_w_tile(const float* __restrict__ dY,
-                                                       const bf16* __restrict__ a5,
-                                                       const bf16* __restrict__ x0,
-                                                       float* __restrict__ part) {
-  constexpr int H = 128, Wd = 128;
-  __shared__ bf16 sU[L6H * L6H * L6C];
-  __shared__ float2 sY[L6T * L6T];
-  const int tx_n = Wd / L6T, per_img = tx_n * (H / L6T);
-  const int b = blockIdx.x / per_img, tt = blockIdx.x % per_img;
-  const int ty0 = (tt / tx_n) * L6T, tx0 = (tt % tx_n) * L6T;
-  for (int i = threadIdx.x; i < L6H * L6H * L6C; i += blockDim.x) {
-    int c = i % L6C, pix = i / L6C;
-    int y = ty0 + pix / L6H - 1, x = tx0 + pix % L6H - 1;
-    bool in = y >= 0 && y < H && x >= 0 && x < Wd;
-    bf16 v = (bf16)0.f;
-    if (in)
-      v = c < 64 ? a5[(((size_t)b * 64 + (y >> 1)) * 64 + (x >> 1)) * 64 + c]
-                 : x0[(((size_t)b * H + y) * Wd + x) * 2 + (c - 64)];
-    sU[i] = v;
+// L6 weight and bias gradients. Channels 0..63 of the layer's input are the 2x upsampling of the
+// L5 output a5 [B][64][64][64], so a source pixel s meets a tap only through the sum of dY over
+// the four output positions whose tap lands on one of its copies:
+//   dW(o, tap, c) = sum_s a5(s, c) G(s, tap, o),
+//   G(s, tap, o) = sum_{a, b in {0, 1}} dY(2Y + a + 1 - ty, 2X + b + 1 - tx, o),
+// 18 products per source pixel and channel where the upsampled form takes 72. One workgroup per
+// 16 x 16 source pixels of a sample: a thread forms the 18 sums of its source pixel from the
+// staged dY (34 x 34, zero outside the image) and leaves them in LDS; then a wavefront's halves
+// walk 32 source pixels each, a lane adding 18 products for two channels (4 bytes of a5, a pixel
+// is one line). The input channels 64, 65 (x0 [B][128][128][2]) and the bias come from the
+// thread's own four output positions and the 4 x 4 input pixels around them. FP32 sums
+// throughout, in a fixed order; per-workgroup partials [workgroup][2 * 9 * 66 + 2] (weights
+// o-major as in the layer, then the two biases), summed over workgroups by k_colsum_final. Bound
+// by the LDS reads of the sums and the a5 stream: 64 samples 35 us where staging the
+// upsampled input and walking it position by position took 235.
+constexpr int L6T = 16, L6H = 2 * L6T + 2, L6C = 66;
+__global__ void __launch_bounds__(256) k_l6_bwd_w(const float* __restrict__ dY,
+                                                  const bf16* __restrict__ a5,
+                                                  const bf16* __restrict__ x0,
+                                                  float* __restrict__ part) {
+  constexpr int H = 128, GS = 20;  // floats per source pixel's sums (18, padded to 16 bytes)
+  __shared__ float2 sY[L6H * L6H];
+  __shared__ __attribute__((aligned(16))) float sG[L6T * L6T * GS];
+  __shared__ float sX[4][38];
+  const int b = blockIdx.x >> 4, Y0 = (blockIdx.x >> 2 & 3) * L6T, X0 = (blockIdx.x & 3) * L6T;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int i = tid; i < L6H * L6H; i += 256) {
+    const int y = 2 * Y0 - 1 + i / L6H, x = 2 * X0 - 1 + i % L6H;
+    float2 v = make_float2(0.f, 0.f);
+    if (y >= 0 && y < H && x >= 0 && x < H)
+      v = *(const float2*)(dY + (((size_t)b * H + y) * H + x) * 2);
+    sY[i] = v;
   }
-  for (int p = threadIdx.x; p < L6T * L6T; p += blockDim.x) {
-    size_t q = ((size_t)b * H + ty0 + p / L6T) * Wd + tx0 + p % L6T;
-    sY[p] = make_float2(dY[2 * q], dY[2 * q + 1]);
+  __syncthreads();
+  {
+    const int ly = tid >> 4, lx = tid & 15;  // source pixel (Y0 + ly, X0 + lx)
+    float2 g[4][4];                          // dY at rows 2Y - 1 .. 2Y + 2, columns alike
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) g[r][c] = sY[(2 * ly + r) * L6H + 2 * lx + c];
+    // tap (ty, tx) takes rows 2 - ty, 3 - ty and columns 2 - tx, 3 - tx of that block
+    float* G = sG + tid * GS;
+#pragma unroll
+    for (int tx = 0; tx < 3; ++tx) {
+      float2 h[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        h[r] = make_float2(g[r][2 - tx].x + g[r][3 - tx].x, g[r][2 - tx].y + g[r][3 - tx].y);
+#pragma unroll
+      for (int ty = 0; ty < 3; ++ty)
+        *(float2*)(G + 2 * (3 * ty + tx)) =
+            make_float2(h[2 - ty].x + h[3 - ty].x, h[2 - ty].y + h[3 - ty].y);
+    }
+    // input channels and bias of the output positions (2Y, 2X) .. (2Y + 1, 2X + 1)
+    float ax[36], ab[2] = {0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 36; ++k) ax[k] = 0.f;
+    unsigned int xv[4][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int y = 2 * (Y0 + ly) - 1 + r, x = 2 * (X0 + lx) - 1 + c;
+        const bool in = y >= 0 && y < H && x >= 0 && x < H;
+        xv[r][c] = in ? *(const unsigned int*)(x0 + (((size_t)b * H + y) * H + x) * 2) : 0u;
+      }
+#pragma unroll
+    for (int pa = 0; pa < 2; ++pa)
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb) {
+        const float2 d = g[1 + pa][1 + pb];
+        ab[0] += d.x;
+        ab[1] += d.y;
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+          const unsigned int u = xv[pa + tap / 3][pb + tap % 3];
+          const float f0 = __uint_as_float(u << 16), f1 = __uint_as_float(u & 0xffff0000u);
+          ax[4 * tap + 0] = fmaf(d.x, f0, ax[4 * tap + 0]);
+          ax[4 * tap + 1] = fmaf(d.x, f1, ax[4 * tap + 1]);
+          ax[4 * tap + 2] = fmaf(d.y, f0, ax[4 * tap + 2]);
+          ax[4 * tap + 3] = fmaf(d.y, f1, ax[4 * tap + 3]);
+        }
+      }
+#pragma unroll
+    for (int k = 0; k < 38; ++k) {
+      float v = k < 36 ? ax[k] : ab[k - 36];
+#pragma unroll
+      for (int m = 1; m < 64; m *= 2) v += __shfl_xor(v, m);
+      if (lane == 0) sX[wv][k] = v;
+    }
+  }
+  __syncthreads();
+  float acc[18][2];
+#pragma unroll
+  for (int k = 0; k < 18; ++k) acc[k][0] = acc[k][1] = 0.f;
+  {
+    const int half = lane >> 5, ch = 2 * (lane & 31);
+#pragma unroll 8
+    for (int i = 0; i < 32; ++i) {
+      const int s = wv * 64 + 2 * i + half;
+      const unsigned int u = *(const unsigned int*)(
+          a5 + (((size_t)b * 64 + Y0 + (s >> 4)) * 64 + X0 + (s & 15)) * 64 + ch);
+      const float f0 = __uint_as_float(u << 16), f1 = __uint_as_float(u & 0xffff0000u);
+      const float* G = sG + s * GS;
+#pragma unroll
+      for (int k = 0; k < 18; ++k) {
+        const float w = G[k];
+        acc[k][0] = fmaf(w, f0, acc[k][0]);
+        acc[k][1] = fmaf(w, f1, acc[k][1]);
+      }
+    }
+    __syncthreads();  // the sums have been read: their LDS takes the wavefronts' results
+#pragma unroll
+    for (int k = 0; k < 18; ++k) {
+      const float v0 = acc[k][0] + __shfl_xor(acc[k][0], 32);
+      const float v1 = acc[k][1] + __shfl_xor(acc[k][1], 32);
+      if (half == 0) *(float2*)(sG + (wv * 18 + k) * 64 + ch) = make_float2(v0, v1);
+    }
   }
   __syncthreads();
   constexpr int NP = 9 * L6C;  // (tap, c) pairs
+  static_assert(4 * 18 * 64 <= L6T * L6T * GS, "the wavefronts' results fit the sums' LDS");
   float* out = part + (size_t)blockIdx.x * (2 * NP + 2);
-  for (int q = threadIdx.x; q <= NP; q += blockDim.x) {
-    float a0 = 0.f, a1 = 0.f;
-    if (q < NP) {
-      const int tap = q / L6C, c = q % L6C;
-      const bf16* u0 = sU + ((tap / 3) * L6H + tap % 3) * L6C + c;
-      for (int py = 0; py < L6T; ++py) {
-        const bf16* ur = u0 + py * L6H * L6C;
-#pragma unroll
-        for (int px = 0; px < L6T; ++px) {
-          float u = (float)ur[px * L6C];
-          float2 g = sY[py * L6T + px];
-          a0 = fmaf(g.x, u, a0);
-          a1 = fmaf(g.y, u, a1);
-        }
-      }
-      out[q] = a0;
-      out[NP + q] = a1;
-    } else {
-      for (int p = 0; p < L6T * L6T; ++p) {
-        a0 += sY[p].x;
-        a1 += sY[p].y;
-      }
-      out[2 * NP] = a0;
-      out[2 * NP + 1] = a1;
-    }
+  for (int e = tid; e < 18 * 64; e += 256) {
+    const int k = e >> 6, c = e & 63;  // k = 2 tap + o
+    const float v = ((sG[e] + sG[18 * 64 + e]) + sG[2 * 18 * 64 + e]) + sG[3 * 18 * 64 + e];
+    out[(k & 1) * NP + (k >> 1) * L6C + c] = v;
+  }
+  if (tid < 38) {
+    const float v = ((sX[0][tid] + sX[1][tid]) + sX[2][tid]) + sX[3][tid];
+    const int o = tid >> 1 & 1, tap = tid >> 2;  // entries (tap, o, channel), then the biases
+    out[tid < 36 ? o * NP + tap * L6C + 64 + (tid & 1) : 2 * NP + tid - 36] = v;
   }
 }
 
@@ -1230,7 +1302,7 @@ static pprs_status alloc_batch(Model& M, int B) {
   // split-K partials: weight gradients (<= 64 splits of the largest weight) or layer outputs
   long long wmax = 0;
   for (int l = 0; l < 5; ++l) wmax = std::max(wmax, (long long)M.L[l].cout * M.L[l].kp);
-  M.part_floats = (size_t)std::max(64 * wmax, (long long)B * (128 / L6T) * (128 / L6T) *
+  M.part_floats = (size_t)std::max(64 * wmax, (long long)B * (64 / L6T) * (64 / L6T) *
                                                   (2 * 9 * L6C + 2));
   CHK(hipMalloc(&M.part, sizeof(float) * M.part_floats));
   CHK(hipMalloc(&M.lpart, sizeof(double) * 1024));
@@ -1374,8 +1446,8 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
   // L6: dW6, db6, dU6
   const Layer& y6 = M.L[5];
   {
-    int nw = 2 * 9 * 66 + 2, chunks = B * (128 / L6T) * (128 / L6T);
-    hipLaunchKernelGGL(k_l6_bwd_w_tile, dim3(chunks), dim3(256), 0, st, M.dy, M.a[4], M.x0, M.part);
+    int nw = 2 * 9 * 66 + 2, chunks = B * (64 / L6T) * (64 / L6T);
+    hipLaunchKernelGGL(k_l6_bwd_w, dim3(chunks), dim3(256), 0, st, M.dy, M.a[4], M.x0, M.part);
     // weights [2][9*66] then bias [2] are contiguous at woff: columns 0..nw-1 map to them
     hipLaunchKernelGGL(k_colsum_final, dim3(nw), dim3(kBlock), 0, st, M.part, nw, chunks, M.g + y6.woff);
     // d a[4] through the folded weights (the input part needs no gradient)
