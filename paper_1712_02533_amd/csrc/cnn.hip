@@ -516,52 +516,57 @@ __global__ void __launch_bounds__(256) k_split_sum(const float* __restrict__ par
 // ------------------------------------------------------------------------------------------
 // Layout kernels
 
-// col[(b, oy, ox)][(dy * 3 + dx) * C + c] = X[b][oy*s + dy - 1][ox*s + dx - 1][c] (0 outside),
-// zero for k >= 9 C up to Kp.
-__global__ void k_im2col(const bf16* __restrict__ X, int Bn, int H, int W, int C, int s,
-                         int Kp, bf16* __restrict__ col) {
-  int Ho = H / s, Wo = W / s;
-  long long total = (long long)Bn * Ho * Wo * Kp;
+// Columns of a layer with two input channels: col[(b, oy, ox)][(dy * 3 + dx) * 2 + c] =
+// X[b][oy*s + dy - 1][ox*s + dx - 1][c] (0 outside), zero for k >= 18 up to Kp (a multiple of 8).
+// A thread takes 8 entries, four taps of 4 bytes, and stores them together: bound by the stores
+// (one entry a thread took 60 us for the 34 MB of 64 samples, this 14).
+__global__ void k_im2col2(const bf16* __restrict__ X, int Bn, int H, int W, int s, int Kp,
+                          bf16* __restrict__ col) {
+  const int Ho = H / s, Wo = W / s, G = Kp / 8;
+  const long long total = (long long)Bn * Ho * Wo * G;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
        i += (long long)gridDim.x * blockDim.x) {
-    int k = (int)(i % Kp);
-    long long p = i / Kp;
-    int ox = (int)(p % Wo), oy = (int)((p / Wo) % Ho), b = (int)(p / ((long long)Wo * Ho));
-    bf16 v = (bf16)0.f;
-    if (k < 9 * C) {
-      int tap = k / C, c = k - tap * C;
-      int y = oy * s + tap / 3 - 1, x = ox * s + tap % 3 - 1;
-      if (y >= 0 && y < H && x >= 0 && x < W) v = X[(((size_t)b * H + y) * W + x) * C + c];
+    const int g = (int)(i % G);
+    const long long p = i / G;
+    const int ox = (int)(p % Wo), oy = (int)((p / Wo) % Ho);
+    const long long b = p / ((long long)Wo * Ho);
+    unsigned int v[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int tap = 4 * g + t, y = oy * s + tap / 3 - 1, x = ox * s + tap % 3 - 1;
+      const bool in = tap < 9 && y >= 0 && y < H && x >= 0 && x < W;
+      v[t] = in ? *(const unsigned int*)(X + ((b * H + y) * W + x) * 2) : 0u;
     }
-    col[i] = v;
+    *(uint4*)(col + i * 8) = make_uint4(v[0], v[1], v[2], v[3]);
   }
 }
 
-// dX[b][y][x][c] = sum of dcol over the output positions whose patch covers (y, x).
-__global__ void k_col2im(const float* __restrict__ dcol, int Bn, int H, int W, int C, int s,
-                         int ldk, float* __restrict__ dX, int accumulate) {
-  int Ho = H / s, Wo = W / s;
-  long long total = (long long)Bn * H * W * C;
+// dX[b][y][x][c] += sum of dcol over the output positions whose patch covers (y, x), for a layer
+// of stride 2 with C input channels and side 2^LW: an even row lies in the patch of one output row
+// (its middle tap), an odd one in those of two. Four channels a thread, indexes by shifts; bound
+// by memory (0.33 GB for both layers of 64 samples: one channel a thread took 212 us, this 73).
+template <int C, int LW>
+__global__ void k_col2im(const float* __restrict__ dcol, int Bn, int ldk, float* __restrict__ dX) {
+  constexpr int W = 1 << LW, Wo = W / 2, C4 = C / 4;
+  const long long total = (long long)Bn * W * W * C4;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
        i += (long long)gridDim.x * blockDim.x) {
-    int c = (int)(i % C);
-    long long p = i / C;
-    int x = (int)(p % W), y = (int)((p / W) % H), b = (int)(p / ((long long)W * H));
-    float sum = 0.f;
-    for (int dy = 0; dy < 3; ++dy) {
-      int ty = y + 1 - dy;
-      if (ty < 0 || ty % s) continue;
-      int oy = ty / s;
-      if (oy >= Ho) continue;
-      for (int dx = 0; dx < 3; ++dx) {
-        int tx = x + 1 - dx;
-        if (tx < 0 || tx % s) continue;
-        int ox = tx / s;
+    const int c = 4 * (int)(i % C4);
+    const long long p = i / C4;
+    const int x = (int)p & (W - 1), y = (int)(p >> LW) & (W - 1);
+    const long long b = p >> (2 * LW);
+    f32x4 sum = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int dy = 1 - (y & 1); dy < 3; dy += 2) {
+      const int oy = (y + 1 - dy) >> 1;
+      if (oy >= Wo) continue;
+      for (int dx = 1 - (x & 1); dx < 3; dx += 2) {
+        const int ox = (x + 1 - dx) >> 1;
         if (ox >= Wo) continue;
-        sum += dcol[(((size_t)b * Ho + oy) * Wo + ox) * ldk + (dy * 3 + dx) * C + c];
+        sum += *(const f32x4*)(dcol + ((b * Wo + oy) * Wo + ox) * ldk + (dy * 3 + dx) * C + c);
       }
     }
-    dX[i] = accumulate ? dX[i] + sum : sum;
+    f32x4* d = (f32x4*)(dX + 4 * i);
+    *d = *d + sum;
   }
 }
 
@@ -869,43 +874,63 @@ __global__ void k_w1_prep(const bf16* __restrict__ W, int Kp, float* __restrict_
 // (the adjoint of k_l6_fused's folded product, which also sums the four upsampled copies):
 // source pixel (Y, X) feeds the outputs (2 Ys + py, 2 Xs + px) with Ys = Y + 1 - py - i and
 // Xs = X + 1 - px - j through W6f[py px][i][j][o][c] (the output rows 2Y - 1 .. 2Y + 2 and the
-// columns alike, 2 outputs each). One wave per source pixel, one lane per channel: the dY
-// values of a wave are the same for every lane; the weights sit in LDS.
+// columns alike, 2 outputs each). One workgroup per 16 x 16 source pixels of a sample: dY staged
+// in LDS (34 x 34, zero outside the image), a wavefront's halves walk 32 source pixels each, a lane
+// taking two channels with its 64 weights in registers. Bound by the LDS reads of dY: 64 samples
+// 24 us; one pixel a wavefront with the weights in LDS took 76.
+constexpr int L6T = 16, L6H = 2 * L6T + 2, L6C = 66;
+__device__ __forceinline__ void l6_stage_dy(const float* __restrict__ dY, int b, int Y0, int X0,
+                                            float2* sY) {
+  for (int i = threadIdx.x; i < L6H * L6H; i += 256) {
+    const int y = 2 * Y0 - 1 + i / L6H, x = 2 * X0 - 1 + i % L6H;
+    float2 v = make_float2(0.f, 0.f);
+    if (y >= 0 && y < 128 && x >= 0 && x < 128)
+      v = *(const float2*)(dY + (((size_t)b * 128 + y) * 128 + x) * 2);
+    sY[i] = v;
+  }
+}
 __global__ void __launch_bounds__(256) k_l6_bwd_a5(const float* __restrict__ dY,
-                                                   const float* __restrict__ W6f, int Bn,
+                                                   const float* __restrict__ W6f,
                                                    float* __restrict__ dA5) {
-  __shared__ float w[4 * 2 * 2 * 2 * 64];
-  for (int e = threadIdx.x; e < 4 * 2 * 2 * 2 * 64; e += blockDim.x) w[e] = W6f[e];
+  __shared__ __attribute__((aligned(16))) float2 sY[L6H * L6H];
+  const int b = blockIdx.x >> 4, Y0 = (blockIdx.x >> 2 & 3) * L6T, X0 = (blockIdx.x & 3) * L6T;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, half = lane >> 5, ch = 2 * (lane & 31);
+  float2 w[4][2][2][2];  // [py px][i][j][output]
+#pragma unroll
+  for (int k = 0; k < 32; ++k)
+    w[k >> 3][k >> 2 & 1][k >> 1 & 1][k & 1] = *(const float2*)(W6f + k * 64 + ch);
+  l6_stage_dy(dY, b, Y0, X0, sY);
   __syncthreads();
-  const int c = threadIdx.x & 63;
-  const long long npix = (long long)Bn * 64 * 64;
-  const long long step = ((long long)gridDim.x * blockDim.x) >> 6;
-  for (long long p = (blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6; p < npix;
-       p += step) {
-    // one source pixel per wave: its index in scalar registers, so the dY reads are scalar
-    const int pu = __builtin_amdgcn_readfirstlane((int)p);
-    const int X = pu & 63, Y = (pu >> 6) & 63;
-    const long long b = pu >> 12;
-    float s = 0.f;
+#pragma unroll 2
+  for (int it = 0; it < 32; ++it) {
+    const int p = wv * 64 + 2 * it + half, ly = p >> 4, lx = p & 15;
+    float2 g[4][4];  // dY at rows 2Y - 1 .. 2Y + 2, columns alike
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const f32x4* row = (const f32x4*)(sY + (2 * ly + r) * L6H + 2 * lx);
+      const f32x4 lo = row[0], hi = row[1];
+      g[r][0] = make_float2(lo[0], lo[1]);
+      g[r][1] = make_float2(lo[2], lo[3]);
+      g[r][2] = make_float2(hi[0], hi[1]);
+      g[r][3] = make_float2(hi[2], hi[3]);
+    }
+    float s0 = 0.f, s1 = 0.f;
 #pragma unroll
     for (int py = 0; py < 2; ++py)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int y = 2 * (Y + 1 - py - i) + py;
-        if (y < 0 || y >= 128) continue;
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int px = 0; px < 2; ++px)
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
-            const int x = 2 * (X + 1 - px - j) + px;
-            if (x < 0 || x >= 128) continue;
-            const float* g = dY + ((b * 128 + y) * 128 + x) * 2;
-            const float* wp = w + ((((py * 2 + px) * 2 + i) * 2 + j) * 2) * 64 + c;
-            s = fmaf(wp[0], g[0], s);
-            s = fmaf(wp[64], g[1], s);
+            const float2 d = g[3 - py - 2 * i][3 - px - 2 * j];
+            const float2(&wo)[2] = w[2 * py + px][i][j];
+            s0 = fmaf(wo[0].x, d.x, s0);
+            s1 = fmaf(wo[0].y, d.x, s1);
+            s0 = fmaf(wo[1].x, d.y, s0);
+            s1 = fmaf(wo[1].y, d.y, s1);
           }
-      }
-    dA5[p * 64 + c] = s;
+    *(float2*)(dA5 + (((size_t)b * 64 + Y0 + ly) * 64 + X0 + lx) * 64 + ch) = make_float2(s0, s1);
   }
 }
 
@@ -924,7 +949,6 @@ __global__ void __launch_bounds__(256) k_l6_bwd_a5(const float* __restrict__ dY,
 // o-major as in the layer, then the two biases), summed over workgroups by k_colsum_final. Bound
 // by the LDS reads of the sums and the a5 stream: 64 samples 35 us where staging the
 // upsampled input and walking it position by position took 235.
-constexpr int L6T = 16, L6H = 2 * L6T + 2, L6C = 66;
 __global__ void __launch_bounds__(256) k_l6_bwd_w(const float* __restrict__ dY,
                                                   const bf16* __restrict__ a5,
                                                   const bf16* __restrict__ x0,
@@ -935,13 +959,7 @@ __global__ void __launch_bounds__(256) k_l6_bwd_w(const float* __restrict__ dY,
   __shared__ float sX[4][38];
   const int b = blockIdx.x >> 4, Y0 = (blockIdx.x >> 2 & 3) * L6T, X0 = (blockIdx.x & 3) * L6T;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int i = tid; i < L6H * L6H; i += 256) {
-    const int y = 2 * Y0 - 1 + i / L6H, x = 2 * X0 - 1 + i % L6H;
-    float2 v = make_float2(0.f, 0.f);
-    if (y >= 0 && y < H && x >= 0 && x < H)
-      v = *(const float2*)(dY + (((size_t)b * H + y) * H + x) * 2);
-    sY[i] = v;
-  }
+  l6_stage_dy(dY, b, Y0, X0, sY);
   __syncthreads();
   {
     const int ly = tid >> 4, lx = tid & 15;  // source pixel (Y0 + ly, X0 + lx)
@@ -1435,7 +1453,6 @@ static pprs_status wgrad(Model& M, int l, int B) {
 // Loss and full gradient into M.g (uses M.y from forward). Returns the mean squared error.
 static pprs_status backward(Model& M, const float* target, int B, int margin, double* loss) {
   hipStream_t st = M.stream;
-  long long P128 = (long long)B * 128 * 128;
   int interior = 128 - 2 * margin;
   float inv_count = 1.f / ((float)B * interior * interior * 2);
   int blocks = 1024;
@@ -1451,7 +1468,7 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
     // weights [2][9*66] then bias [2] are contiguous at woff: columns 0..nw-1 map to them
     hipLaunchKernelGGL(k_colsum_final, dim3(nw), dim3(kBlock), 0, st, M.part, nw, chunks, M.g + y6.woff);
     // d a[4] through the folded weights (the input part needs no gradient)
-    hipLaunchKernelGGL(k_l6_bwd_a5, dim3(grid1d(P128 / 4 * 64)), dim3(kBlock), 0, st, M.dy, M.w6f, B, M.da[4]);
+    hipLaunchKernelGGL(k_l6_bwd_a5, dim3(chunks), dim3(256), 0, st, M.dy, M.w6f, M.da[4]);
   }
   CHK(hipGetLastError());
   // L5 .. L1
@@ -1468,7 +1485,7 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
     if (l > 0) {
       s = wgrad(M, l, B);
     } else {
-      hipLaunchKernelGGL(k_im2col, dim3(grid1d(pix * y.kp)), dim3(kBlock), 0, st, M.x0, B, y.hin, y.hin, y.cin, y.stride, y.kp, M.col);
+      hipLaunchKernelGGL(k_im2col2, dim3(grid1d(pix * y.kp / 8)), dim3(kBlock), 0, st, M.x0, B, y.hin, y.hin, y.stride, y.kp, M.col);
       // one 64 x 64 result: the splits alone fill the GPU (64 of them: 129 us for 64 samples)
       int splits = (int)std::max<long long>(1, std::min<long long>(512, pix / 256));
       s = gemm(M, true, true, M.dzb, y.cout, M.col, y.kp, M.g + y.woff, y.kp, y.cout, y.kp, (int)pix, splits);
@@ -1496,10 +1513,10 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
     if (s != PPRS_OK) return s;
     if (l == 2) {
       // input a2 (32^2 x 128), stride 2; a2 already holds the skip gradient from L4
-      hipLaunchKernelGGL(k_col2im, dim3(grid1d((long long)B * 32 * 32 * 128)), dim3(kBlock), 0, st, M.dcol, B, 32, 32, 128, 2, y.kp, M.da[1], 1);
+      hipLaunchKernelGGL((k_col2im<128, 5>), dim3(grid1d((long long)B * 32 * 32 * 32)), dim3(kBlock), 0, st, M.dcol, B, y.kp, M.da[1]);
     } else if (l == 1) {
       // input a1 (64^2 x 64), stride 2; a1 already holds the skip gradient from L5
-      hipLaunchKernelGGL(k_col2im, dim3(grid1d((long long)B * 64 * 64 * 64)), dim3(kBlock), 0, st, M.dcol, B, 64, 64, 64, 2, y.kp, M.da[0], 1);
+      hipLaunchKernelGGL((k_col2im<64, 6>), dim3(grid1d((long long)B * 64 * 64 * 16)), dim3(kBlock), 0, st, M.dcol, B, y.kp, M.da[0]);
     }
     CHK(hipGetLastError());
   }
