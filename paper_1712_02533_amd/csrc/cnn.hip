@@ -109,12 +109,23 @@ __global__ void __launch_bounds__(256) k_gemm(const bf16* __restrict__ A, int ld
 }
 
 // ------------------------------------------------------------------------------------------
+// A float from the lane a DPP control names (all lanes have a source).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
 // Fused 3x3 convolution (implicit GEMM) for layers whose input channels come in multiples of
 // 64: out[m][n] = relu(bias[n] + sum_k A(m,k) W[n][k]) as bf16, with m = (b, oy, ox) and
 // k = tap * C0 + c. A(m,k) is read straight from the NHWC input (no im2col copy), zero outside
 // the frame.
-// DGRAD: the same product for a data gradient (input dZ, weights flipped and transposed):
-// no bias or ReLU, FP32 output (`out` is then a float*).
+// DGRAD: the same product for the data gradient of a decoder layer (input dZ, weights flipped and
+// transposed; no bias or ReLU, FP32). Its first C1 channels belong to the upsampled source, whose
+// gradient is the sum over the four pixels of an upsampled one: the pixels of a tile are taken in
+// 2x2 quads, m = 4 ((b H/2 + Y) H/2 + X) + (2 dy + dx), a quad's four lanes add up and one stores
+// to `out` [H/2][H/2][C1]; the rest go to `out2` [H][H][Cout - C1], the skip connection's. Written
+// out whole and summed by another kernel the gradient of 64 samples' two layers took 323 us,
+// this way 212 (the product is what is left of it).
 // FOLD: a decoder layer, channels [0, C0) from src0 at half resolution (nearest 2x upsampling),
 // channels [C0, C0 + C1) from src1 (the skip connection). The upsampled source is read at its own
 // resolution: output pixel (2Y + py, 2X + px) sees through its 3x3 taps only the 2 x 2 source
@@ -135,7 +146,7 @@ __global__ void __launch_bounds__(256) k_gemm(const bf16* __restrict__ A, int ld
 // the first-level cache bound it).
 // The product is formed transposed (channels as rows), so that a lane ends with 4 consecutive
 // channels of a pixel and stores them together.
-// Requires C0 % 64 == 0, C1 % 64 == 0, BN | Cout, (pixels of a parity) % (64 MT) == 0,
+// Requires C0 % 64 == 0, C1 % 64 == 0, BN | Cout (DGRAD: BN | C1), (pixels of a parity) % (64 MT) == 0,
 // Kp % 8 == 0, Hin a power of two.
 
 constexpr int CV_BK = 64, CV_LD = CV_BK + 8;
@@ -146,7 +157,7 @@ template <int MT, int BN, bool DGRAD, bool FOLD>
 __global__ void __launch_bounds__(256, 2) k_conv_fwd(
     const bf16* __restrict__ src0, int C0, const bf16* __restrict__ src1, int C1, int Hin,
     int stride, const bf16* __restrict__ Wt, int Kp, const float* __restrict__ bias, int Cout,
-    void* __restrict__ out_) {
+    void* __restrict__ out_, float* __restrict__ out2) {
   static_assert(!(FOLD && DGRAD), "folding is for the upsampling layers' forward");
   constexpr int BM = 64 * MT, TN = BN / 16, B_PIECES = BN * 8 / 256;
   constexpr unsigned OUTSIDE = 0x80000000u;  // beyond every buffer: reads zero
@@ -173,7 +184,11 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const long long m = m0 + wave * 16 * MT + 16 * i + row16;
-    const int ox = (int)m & (Hm - 1), oy = (int)(m >> lh) & (Hm - 1);
+    int ox = (int)m & (Hm - 1), oy = (int)(m >> lh) & (Hm - 1);
+    if (DGRAD) {  // quads: X, Y from m / 4
+      ox = 2 * ((int)(m >> 2) & (Hm / 2 - 1)) + ((int)m & 1);
+      oy = 2 * ((int)(m >> (lh + 1)) & (Hm / 2 - 1)) + ((int)m >> 1 & 1);
+    }
     const unsigned rb = (unsigned)((m >> (2 * lh)) - bs);
     const int y0 = FOLD ? oy : oy * stride, x0 = FOLD ? ox : ox * stride;
     off0[i] = (((rb * Hs0 + y0) * Hs0 + x0) * C0 + 8 * kq) * 2;
@@ -310,7 +325,19 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
     for (int j = 0; j < TN; ++j) {
       const int col = n0 + 16 * j + 4 * kq;
       if (DGRAD) {
-        *(f32x4*)((float*)out_ + row * Cout + col) = acc[i][j];
+        f32x4 v = acc[i][j];
+        if (n0 < C1) {  // uniform: BN divides C1
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            v[r] += dpp_f<0xb1>(v[r]);  // quad_perm 1, 0, 3, 2
+            v[r] += dpp_f<0x4e>(v[r]);  // quad_perm 2, 3, 0, 1
+          }
+          if ((row16 & 3) == 0) *(f32x4*)((float*)out_ + (row >> 2) * C1 + col) = v;
+        } else {
+          const long long X = (row >> 2) & (Hm / 2 - 1), Y = (row >> (lh + 1)) & (Hm / 2 - 1);
+          const long long q = ((row >> (2 * lh)) * Hm + 2 * Y + (row >> 1 & 1)) * Hm + 2 * X + (row & 1);
+          *(f32x4*)(out2 + q * (Cout - C1) + (col - C1)) = v;
+        }
       } else {
         const f32x4 bv = *(const f32x4*)(bias + col);
         unsigned int h[4];
@@ -570,36 +597,6 @@ __global__ void k_col2im(const float* __restrict__ dcol, int Bn, int ldk, float*
   }
 }
 
-// A decoder layer's input gradient dU [H][W][C1 + C2] to its sources: d_lo = 2x2 sums of the first
-// C1 channels (the upsampling's adjoint); d_skip (+)= the rest.
-__global__ void k_upcat_bwd(const float* __restrict__ dU, int C1, int C2, int Bn, int H, int W,
-                            float* __restrict__ dlo, float* __restrict__ dskip,
-                            int skip_accumulate) {
-  int C = C1 + C2;
-  long long nlo = (long long)Bn * (H / 2) * (W / 2) * C1;
-  long long nsk = dskip ? (long long)Bn * H * W * C2 : 0;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < nlo + nsk;
-       i += (long long)gridDim.x * blockDim.x) {
-    if (i < nlo) {
-      int c = (int)(i % C1);
-      long long p = i / C1;
-      int X = (int)(p % (W / 2)), Y = (int)((p / (W / 2)) % (H / 2));
-      int b = (int)(p / ((long long)(W / 2) * (H / 2)));
-      float s = 0.f;
-      for (int dy = 0; dy < 2; ++dy)
-        for (int dx = 0; dx < 2; ++dx)
-          s += dU[(((size_t)b * H + 2 * Y + dy) * W + 2 * X + dx) * C + c];
-      dlo[i] = s;
-    } else {
-      long long j = i - nlo;
-      int c = (int)(j % C2);
-      long long p = j / C2;
-      float v = dU[p * C + C1 + c];
-      dskip[j] = skip_accumulate ? dskip[j] + v : v;
-    }
-  }
-}
-
 // dZ = dA * (A > 0) as bf16 (A is the layer's ReLU output), [M][N] with N a multiple of 8 that
 // divides 2048, and the column sums of dZ (the bias gradient) per workgroup: part[block][N]. A
 // thread keeps 8 columns: two 16-byte loads of dA and one of A per row.
@@ -660,12 +657,6 @@ __global__ void k_f32_to_bf16(const float* __restrict__ x, long long count,
 // ------------------------------------------------------------------------------------------
 // Last layer (66 -> 2 channels, stride 1), FP32 direct kernels. W6 is [2][9][66] fp32 (from the
 // bf16 copy), bias b6[2].
-
-// A float from the lane a DPP control names (all lanes have a source).
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
-}
 
 // Last layer read straight from its sources. Channels 0..63 are the nearest 2x upsampling of
 // the L5 output a5 [B][64][64][64]: output pixel (2Y + py, 2X + px) sees through its 3x3 taps
@@ -1198,7 +1189,7 @@ struct Model {
   int cap_b = 0;
   // activations and workspaces (sized for cap_b)
   bf16 *x0 = nullptr, *a[5] = {nullptr}, *col = nullptr, *dzb = nullptr;
-  float *z = nullptr, *y = nullptr, *dy = nullptr, *dcol = nullptr, *du = nullptr,
+  float *z = nullptr, *y = nullptr, *dy = nullptr, *dcol = nullptr,
         *da[5] = {nullptr}, *part = nullptr, *w6 = nullptr, *w6f = nullptr, *w1 = nullptr;
   double* lpart = nullptr;
   size_t part_floats = 0;
@@ -1284,7 +1275,7 @@ static void define_layers(Model& M) {
 static pprs_status alloc_batch(Model& M, int B) {
   if (B <= M.cap_b) return PPRS_OK;
   void* ptrs[] = {M.x0, M.a[0], M.a[1], M.a[2], M.a[3], M.a[4], M.col, M.dzb,
-                  M.z, M.y, M.dy, M.dcol, M.du, M.da[0], M.da[1], M.da[2], M.da[3], M.da[4],
+                  M.z, M.y, M.dy, M.dcol, M.da[0], M.da[1], M.da[2], M.da[3], M.da[4],
                   M.part, M.lpart, M.wflip};
   for (void* p : ptrs)
     if (p) CHK(hipFree(p));
@@ -1311,7 +1302,6 @@ static pprs_status alloc_batch(Model& M, int B) {
   CHK(hipMalloc(&M.y, sizeof(float) * P128 * 2));
   CHK(hipMalloc(&M.dy, sizeof(float) * P128 * 2));
   CHK(hipMalloc(&M.dcol, sizeof(float) * dcol_max));
-  CHK(hipMalloc(&M.du, sizeof(float) * P128 * 66));
   CHK(hipMalloc(&M.da[0], sizeof(float) * P64 * 64));
   CHK(hipMalloc(&M.da[1], sizeof(float) * P32 * 128));
   CHK(hipMalloc(&M.da[2], sizeof(float) * P16 * 256));
@@ -1336,10 +1326,11 @@ static pprs_status alloc_batch(Model& M, int B) {
 template <bool DGRAD, bool FOLD>
 static pprs_status conv_launch(Model& M, const bf16* s0, int c0, const bf16* s1, int c1, int hin,
                                int stride, const bf16* w, int kp, const float* b, int cout,
-                               long long pix, void* out) {
+                               long long pix, void* out, float* out2 = nullptr) {
   const int bn = cout % 128 == 0 ? 128 : 64;
   const long long unit = FOLD ? pix / 4 : pix;  // pixels that a tile may not straddle
-  if (unit % 64 || c0 % 64 || c1 % 64 || kp % 8 || cout % bn || (hin & (hin - 1)))
+  if (unit % 64 || c0 % 64 || c1 % 64 || kp % 8 || cout % bn || (hin & (hin - 1)) ||
+      (DGRAD && c1 % bn))
     return cfail(PPRS_EINVAL, "convolution of %d + %d to %d channels does not fit its tiles", c0, c1,
                  cout);
   int mt = bn == 128 ? 2 : 4;
@@ -1347,7 +1338,7 @@ static pprs_status conv_launch(Model& M, const bf16* s0, int c0, const bf16* s1,
   dim3 grid((unsigned)(pix / (64 * mt)), cout / bn);
 #define CONV(MT, BN)                                                                           \
   hipLaunchKernelGGL((k_conv_fwd<MT, BN, DGRAD, FOLD>), grid, dim3(256), 0, M.stream, s0, c0, s1, \
-                     c1, hin, stride, w, kp, b, cout, out)
+                     c1, hin, stride, w, kp, b, cout, out, out2)
   if (bn == 128) {
     if (mt == 2) CONV(2, 128);
     else CONV(1, 128);
@@ -1494,17 +1485,13 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
     if (l == 0) break;
     if (l == 4 || l == 3) {
       // data gradient of the stride-1 decoder layers as a convolution of dZ with the flipped,
-      // transposed weights (implicit GEMM, no materialised columns): dU [pix][cin] FP32
+      // transposed weights (implicit GEMM, no materialised columns), straight to its two sources
       hipLaunchKernelGGL(k_flip_weights, dim3(grid1d((long long)y.cin * 9 * y.cout)), dim3(kBlock), 0, st, M.wb + y.woff, y.cout, y.cin, y.kp, M.wflip);
-      s = conv_launch<true, false>(M, M.dzb, y.cout, nullptr, 0, y.hout, 1, M.wflip, 9 * y.cout,
-                                   nullptr, y.cin, pix, M.du);
+      // input [up2(a[l - 1]), a[4 - l]]: u5 = [a4 128, a1 64] at 64^2, u4 = [a3 256, a2 128] at 32^2
+      const int up = M.L[l - 1].cout;
+      s = conv_launch<true, false>(M, M.dzb, y.cout, nullptr, up, y.hout, 1, M.wflip, 9 * y.cout,
+                                   nullptr, y.cin, pix, M.da[l - 1], M.da[4 - l]);
       if (s != PPRS_OK) return s;
-      if (l == 4)
-        // input u5 = [up2(a4) 128, a1 64] at 64^2
-        hipLaunchKernelGGL(k_upcat_bwd, dim3(grid1d((long long)B * 64 * 64 * 64 + (long long)B * 32 * 32 * 128)), dim3(kBlock), 0, st, M.du, 128, 64, B, 64, 64, M.da[3], M.da[0], 0);
-      else
-        // input u4 = [up2(a3) 256, a2 128] at 32^2
-        hipLaunchKernelGGL(k_upcat_bwd, dim3(grid1d((long long)B * 16 * 16 * 256 + (long long)B * 32 * 32 * 128)), dim3(kBlock), 0, st, M.du, 256, 128, B, 32, 32, M.da[2], M.da[1], 0);
       CHK(hipGetLastError());
       continue;
     }
@@ -1754,7 +1741,7 @@ void pprs_cnn_destroy(pprs_cnn* c) {
   (void)hipStreamSynchronize(M.stream);
   void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
                   M.a[1], M.a[2], M.a[3],
-                  M.a[4], M.col, M.dzb, M.z, M.y, M.dy, M.dcol, M.du, M.da[0],
+                  M.a[4], M.col, M.dzb, M.z, M.y, M.dy, M.dcol, M.da[0],
                   M.da[1], M.da[2], M.da[3], M.da[4], M.part, M.lpart, M.wflip};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
