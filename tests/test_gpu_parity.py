@@ -575,3 +575,27 @@ def test_series_batch_equals_each_series_alone(scan, workers):
         assert st.n_ops_a == st1.n_ops_a and st.n_ops_b == st1.n_ops_b
         assert st.node_steps == st1.node_steps
     assert all(x > 0 for x in lat)
+
+
+@pytest.mark.parametrize("count", [1, 2, 63, 64, 65, 130, 512])
+def test_pairs_do_not_depend_on_the_batch(count):
+    """The step kernels' work lists (searched 63 slots at a time), the planner (one wavefront up to
+    64 slots) and the launch grids follow from the number of registrations; each pair of a batch
+    equals the pair alone bit for bit, also when the same launch shape is used again."""
+    torch = _torch()
+    import paper_1712_02533_amd as P
+    frames = torch.tensor(make_series(SeriesSpec(6, 64, 3.0, 1.0, 10.0, 77)).frames, device="cuda")
+    params = _gpu_params(3)
+    ref = np.arange(count) % 5
+    tmpl = (ref + 1 + np.arange(count) // 5 % (5 - ref))
+    say("pairs", count)
+    u, st = P.register_pairs(frames, ref, tmpl, params=params)
+    alone = {}
+    for k in range(count):
+        key = (int(ref[k]), int(tmpl[k]))
+        if key not in alone:
+            alone[key] = P.register_pairs(frames, [key[0]], [key[1]], params=params)
+        u1, s1 = alone[key]
+        assert torch.equal(u[k], u1[0]), (k, key)
+        assert list(st[k].iters) == list(s1[0].iters) and st[k].energy == s1[0].energy
+    assert torch.equal(P.register_pairs(frames, ref, tmpl, params=params)[0], u)
