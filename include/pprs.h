@@ -258,9 +258,9 @@ pprs_status pprs_set_metric_solve(pprs_ctx* ctx, int mode);
 typedef struct {
   int pool_slots;    /* concurrent registrations of a series (default 512, at most 65536) */
   int pool_group;    /* steps between polls of the slot pool (default 16, at most 1024) */
-  int grid_energy;   /* workgroups of the energy kernels (default 8192) */
-  int grid_grad;     /* workgroups of the gradient kernel (default 8192) */
-  int grid_smooth;   /* workgroups of the metric-solve kernels (default 8192) */
+  int grid_energy;   /* most workgroups of an energy launch (default 8192) */
+  int grid_grad;     /* most workgroups of a gradient launch (default 8192) */
+  int grid_smooth;   /* most workgroups of a metric-solve launch (default 8192) */
   int grid_prolong;  /* unused: the prolongations run inside the gradient launch */
   int tile_grad;     /* gradient tile shape: 0 = default (64x8), 1 = 64x8, 2 = 128x4,
                         3 = 64x16, 4 = 32x16 nodes */

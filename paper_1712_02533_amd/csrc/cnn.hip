@@ -40,12 +40,12 @@ int grid1d(long long work, int cap = 16384) {
 
 // ------------------------------------------------------------------------------------------
 // GEMM: C[m][n] = sum_k A(m,k) B(n,k), bf16 operands, fp32 result.
-// A(m,k) = AK ? A[k * lda + m] : A[m * lda + k]; B(n,k) = BK ? B[k * ldb + n] : B[n * ldb + k].
+// A(m,k) = AK ? A[k * lda + m] : A[m * lda + k]; B(n,k) = B[k * ldb + n].
 // 64 x 64 tiles, 32-deep K steps, 4 wavefronts each owning a 32 x 32 quarter (2 x 2 MFMA).
 // Requires M % 64 == 0, N % 64 == 0, (K range of a split) % 32 == 0, lda, ldb % 8 == 0.
 // blockIdx.z selects a K split; split s writes C + s * split_stride.
 
-template <bool AK, bool BK>
+template <bool AK>
 __global__ void __launch_bounds__(256) k_gemm(const bf16* __restrict__ A, int lda,
                                               const bf16* __restrict__ B, int ldb,
                                               float* __restrict__ C, int ldc, int K,
@@ -71,10 +71,7 @@ __global__ void __launch_bounds__(256) k_gemm(const bf16* __restrict__ A, int ld
 #pragma unroll
       for (int i = 0; i < 8; ++i) sA[(mm + i) * PADK + kk] = e[i];
     }
-    if (!BK) {
-      int n = tid >> 2, kk = (tid & 3) * 8;
-      *(uint4*)&sB[n * PADK + kk] = *(const uint4*)&B[(size_t)(n0 + n) * ldb + k0 + kk];
-    } else {
+    {
       int kk = tid >> 3, nn = (tid & 7) * 8;
       uint4 v = *(const uint4*)&B[(size_t)(k0 + kk) * ldb + n0 + nn];
       const bf16* e = (const bf16*)&v;
@@ -546,7 +543,7 @@ __global__ void __launch_bounds__(256) k_split_sum(const float* __restrict__ par
 // Columns of a layer with two input channels: col[(b, oy, ox)][(dy * 3 + dx) * 2 + c] =
 // X[b][oy*s + dy - 1][ox*s + dx - 1][c] (0 outside), zero for k >= 18 up to Kp (a multiple of 8).
 // A thread takes 8 entries, four taps of 4 bytes, and stores them together: bound by the stores
-// (one entry a thread took 60 us for the 34 MB of 64 samples, this 14).
+// (one entry a thread took 60 us for the 34 MB of 64 samples, this 16).
 __global__ void k_im2col2(const bf16* __restrict__ X, int Bn, int H, int W, int s, int Kp,
                           bf16* __restrict__ col) {
   const int Ho = H / s, Wo = W / s, G = Kp / 8;
@@ -1224,8 +1221,8 @@ static pprs_status cfail(pprs_status s, const char* fmt, ...) {
                    __LINE__);                                                         \
   } while (0)
 
-static pprs_status gemm(Model& M, bool ak, bool bk, const bf16* A, int lda, const bf16* B,
-                        int ldb, float* C, int ldc, int Mr, int Nc, int K, int splits) {
+static pprs_status gemm(Model& M, bool ak, const bf16* A, int lda, const bf16* B, int ldb,
+                         float* C, int ldc, int Mr, int Nc, int K, int splits) {
   if (Mr % 64 || Nc % 64 || K % 32 || lda % 8 || ldb % 8)
     return cfail(PPRS_EINVAL, "gemm shape %d x %d x %d not tileable", Mr, Nc, K);
   int kps = ((K / 32 + splits - 1) / splits) * 32;
@@ -1238,10 +1235,10 @@ static pprs_status gemm(Model& M, bool ak, bool bk, const bf16* A, int lda, cons
     out = M.part;
   }
   dim3 grid(Nc / 64, Mr / 64, splits);
-  if (!ak && !bk) hipLaunchKernelGGL((k_gemm<false, false>), grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
-  else if (!ak && bk) hipLaunchKernelGGL((k_gemm<false, true>), grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
-  else if (ak && !bk) hipLaunchKernelGGL((k_gemm<true, false>), grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
-  else hipLaunchKernelGGL((k_gemm<true, true>), grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
+  if (ak)
+    hipLaunchKernelGGL(k_gemm<true>, grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
+  else
+    hipLaunchKernelGGL(k_gemm<false>, grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
   CHK(hipGetLastError());
   if (splits > 1) {
     hipLaunchKernelGGL(k_split_sum, dim3((unsigned)(stride / 64)), dim3(256), 0, M.stream, M.part,
@@ -1479,7 +1476,7 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
       hipLaunchKernelGGL(k_im2col2, dim3(grid1d(pix * y.kp / 8)), dim3(kBlock), 0, st, M.x0, B, y.hin, y.hin, y.stride, y.kp, M.col);
       // one 64 x 64 result: the splits alone fill the GPU (64 of them: 129 us for 64 samples)
       int splits = (int)std::max<long long>(1, std::min<long long>(512, pix / 256));
-      s = gemm(M, true, true, M.dzb, y.cout, M.col, y.kp, M.g + y.woff, y.kp, y.cout, y.kp, (int)pix, splits);
+      s = gemm(M, true, M.dzb, y.cout, M.col, y.kp, M.g + y.woff, y.kp, y.cout, y.kp, (int)pix, splits);
     }
     if (s != PPRS_OK) return s;
     if (l == 0) break;
@@ -1496,7 +1493,7 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
       continue;
     }
     // data gradient: dcol[pix][k] = sum_co dZ[pix][co] W[co][k]; then col2im into the input
-    s = gemm(M, false, true, M.dzb, y.cout, M.wb + y.woff, y.kp, M.dcol, y.kp, (int)pix, y.kp, y.cout, 1);
+    s = gemm(M, false, M.dzb, y.cout, M.wb + y.woff, y.kp, M.dcol, y.kp, (int)pix, y.kp, y.cout, 1);
     if (s != PPRS_OK) return s;
     if (l == 2) {
       // input a2 (32^2 x 128), stride 2; a2 already holds the skip gradient from L4

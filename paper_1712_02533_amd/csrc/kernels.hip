@@ -10,7 +10,8 @@
 //   k_smooth   - metric solve d = (S1^-1 (x) S1^-1) G, one direction per launch
 //   k_*_fin    - per-slot finalisers, launched after a pass: sum the pass's FP64 tile partials
 //                in tile order and advance the slot's state (the kernel boundary orders them
-//                after every tile; no fences or tickets inside a pass)
+//                after every tile; no fences or tickets inside a pass). The metric solve has no
+//                launch of its own for it: the energy pass forms the first step size
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include "pprs_internal.h"
