@@ -40,12 +40,11 @@ int grid1d(long long work, int cap = 16384) {
 
 // ------------------------------------------------------------------------------------------
 // GEMM: C[m][n] = sum_k A(m,k) B(n,k), bf16 operands, fp32 result.
-// A(m,k) = AK ? A[k * lda + m] : A[m * lda + k]; B(n,k) = B[k * ldb + n].
+// A(m,k) = A[k * lda + m]; B(n,k) = B[k * ldb + n].
 // 64 x 64 tiles, 32-deep K steps, 4 wavefronts each owning a 32 x 32 quarter (2 x 2 MFMA).
 // Requires M % 64 == 0, N % 64 == 0, (K range of a split) % 32 == 0, lda, ldb % 8 == 0.
 // blockIdx.z selects a K split; split s writes C + s * split_stride.
 
-template <bool AK>
 __global__ void __launch_bounds__(256) k_gemm(const bf16* __restrict__ A, int lda,
                                               const bf16* __restrict__ B, int ldb,
                                               float* __restrict__ C, int ldc, int K,
@@ -61,10 +60,7 @@ __global__ void __launch_bounds__(256) k_gemm(const bf16* __restrict__ A, int ld
   for (int i = 0; i < 2; ++i)
     for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
   for (int k0 = kb; k0 < ke; k0 += 32) {
-    if (!AK) {
-      int m = tid >> 2, kk = (tid & 3) * 8;
-      *(uint4*)&sA[m * PADK + kk] = *(const uint4*)&A[(size_t)(m0 + m) * lda + k0 + kk];
-    } else {
+    {
       int kk = tid >> 3, mm = (tid & 7) * 8;
       uint4 v = *(const uint4*)&A[(size_t)(k0 + kk) * lda + m0 + mm];
       const bf16* e = (const bf16*)&v;
@@ -123,6 +119,10 @@ __device__ __forceinline__ float dpp_f(float v) {
 // to `out` [H/2][H/2][C1]; the rest go to `out2` [H][H][Cout - C1], the skip connection's. Written
 // out whole and summed by another kernel the gradient of 64 samples' two layers took 323 us,
 // this way 212 (the product is what is left of it).
+// S2: the data gradient of a stride-2 layer (input dZ [H][H][C0], the same flipped weights), added to
+// `out` [2H][2H][Cout]: pixel (2Y + py, 2X + px) meets 1, 2, 2 or 4 of the nine taps by its parity,
+// m = (b H + Y) H + X within a parity. By a product into columns (0.23 GB for the two layers of
+// 64 samples) and another kernel gathering them the two took 175 us, this way 73.
 // FOLD: a decoder layer, channels [0, C0) from src0 at half resolution (nearest 2x upsampling),
 // channels [C0, C0 + C1) from src1 (the skip connection). The upsampled source is read at its own
 // resolution: output pixel (2Y + py, 2X + px) sees through its 3x3 taps only the 2 x 2 source
@@ -150,24 +150,26 @@ constexpr int CV_BK = 64, CV_LD = CV_BK + 8;
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-template <int MT, int BN, bool DGRAD, bool FOLD>
+template <int MT, int BN, bool DGRAD, bool FOLD, bool S2>
 __global__ void __launch_bounds__(256, 2) k_conv_fwd(
     const bf16* __restrict__ src0, int C0, const bf16* __restrict__ src1, int C1, int Hin,
     int stride, const bf16* __restrict__ Wt, int Kp, const float* __restrict__ bias, int Cout,
     void* __restrict__ out_, float* __restrict__ out2) {
-  static_assert(!(FOLD && DGRAD), "folding is for the upsampling layers' forward");
+  static_assert(FOLD + DGRAD + S2 <= 1, "one of the three");
+  constexpr bool PAR = FOLD || S2;  // the pixels of a tile share an output parity
   constexpr int BM = 64 * MT, TN = BN / 16, B_PIECES = BN * 8 / 256;
   constexpr unsigned OUTSIDE = 0x80000000u;  // beyond every buffer: reads zero
   __shared__ __attribute__((aligned(16))) bf16 sB[2][BN * CV_LD];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int Hout = Hin / stride, Hs0 = FOLD ? Hin / 2 : Hin;
-  const int nchunks = (FOLD ? 4 * C0 + 9 * C1 : 9 * C0) / CV_BK;
   const int n0 = blockIdx.y * BN;
-  const int tiles_per_par = FOLD ? gridDim.x / 4 : 1;
-  const int par = FOLD ? blockIdx.x / tiles_per_par : 0;
+  const int tiles_per_par = PAR ? gridDim.x / 4 : 1;
+  const int quarter = PAR ? blockIdx.x / tiles_per_par : 0;
+  const int par = S2 ? 3 - quarter : quarter;  // S2: the parity of four taps first
   const int py = par >> 1, px = par & 1;
-  const long long m0 = (long long)(FOLD ? blockIdx.x - par * tiles_per_par : blockIdx.x) * BM;
+  const int nchunks = (FOLD ? 4 * C0 + 9 * C1 : S2 ? (1 + py) * (1 + px) * C0 : 9 * C0) / CV_BK;
+  const long long m0 = (long long)(PAR ? blockIdx.x - quarter * tiles_per_par : blockIdx.x) * BM;
   if (FOLD) Wt += (size_t)par * Cout * Kp;
   const int Hm = FOLD ? Hout / 2 : Hout, lh = __builtin_ctz(Hm);
   // the tile's first sample: 64-bit bases here, 32-bit offsets from here on
@@ -178,6 +180,13 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
   // pixel in src1) plus the lane's channels, and which taps lie inside the frame
   const int row16 = lane & 15, kq = lane >> 4;
   unsigned off0[MT], off1[MT], inside[MT];
+  // S2: tap k of this parity, its offset in dZ and its place in the 3x3 window
+  auto s2_tap = [&](int k, int& dy, int& dx) {
+    const int ky = px ? k >> 1 : k, kx = px ? k & 1 : 0;
+    dy = py ? 1 - ky : 0;
+    dx = px ? 1 - kx : 0;
+    return (py ? 2 * ky : 1) * 3 + (px ? 2 * kx : 1);
+  };
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const long long m = m0 + wave * 16 * MT + 16 * i + row16;
@@ -204,6 +213,13 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
         const int iy = y + t / 3 - 1, ix = x + t % 3 - 1;
         in |= (unsigned)(iy >= 0 && iy < Hin && ix >= 0 && ix < Hin) << (4 + t);
       }
+    } else if (S2) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        int dy, dx;
+        s2_tap(t, dy, dx);
+        in |= (unsigned)(t < (1 + py) * (1 + px) && oy + dy < Hin && ox + dx < Hin) << t;
+      }
     } else {
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
@@ -215,6 +231,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
   }
   // position of the next chunk to fetch: tap (FOLD: 0-3 source pixels, 4-12 skip taps), channel
   int tap = 0, c = 0;
+  int wtap = 0;  // S2: first column of the tap's weights
   unsigned voff[MT];
   auto set_tap = [&] {
     const bool skip = FOLD && tap >= 4;
@@ -224,6 +241,10 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
       dx = (tap & 1) - 1 + px;
       C = C0;
       H = Hs0;
+    } else if (S2) {
+      wtap = (8 - s2_tap(tap, dy, dx)) * C0;
+      C = C0;
+      H = Hin;
     } else {
       const int t = FOLD ? tap - 4 : tap;
       dy = t / 3 - 1;
@@ -253,7 +274,8 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
 #pragma unroll
     for (int r = 0; r < B_PIECES; ++r) {
       const int e = tid + 256 * r;
-      rb[r] = *(const u32x4*)(Wt + (size_t)(n0 + (e >> 3)) * Kp + chunk_f * CV_BK + (e & 7) * 8);
+      rb[r] = *(const u32x4*)(Wt + (size_t)(n0 + (e >> 3)) * Kp +
+                              (S2 ? wtap + c : chunk_f * CV_BK) + (e & 7) * 8);
     }
     ++chunk_f;
     c += CV_BK;
@@ -314,14 +336,17 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     long long row = m0 + wave * 16 * MT + 16 * i + row16;
-    if (FOLD) {  // (b, Y, X) -> the output pixel (b, 2Y + py, 2X + px)
+    if (PAR) {  // (b, Y, X) -> the output pixel (b, 2Y + py, 2X + px)
       const long long X = row & (Hm - 1), Y = (row >> lh) & (Hm - 1), bb = row >> (2 * lh);
-      row = (bb * Hout + 2 * Y + py) * Hout + 2 * X + px;
+      row = (bb * 2 * Hm + 2 * Y + py) * 2 * Hm + 2 * X + px;
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int col = n0 + 16 * j + 4 * kq;
-      if (DGRAD) {
+      if (S2) {
+        f32x4* d = (f32x4*)((float*)out_ + row * Cout + col);
+        *d = *d + acc[i][j];
+      } else if (DGRAD) {
         f32x4 v = acc[i][j];
         if (n0 < C1) {  // uniform: BN divides C1
 #pragma unroll
@@ -562,35 +587,6 @@ __global__ void k_im2col2(const bf16* __restrict__ X, int Bn, int H, int W, int 
       v[t] = in ? *(const unsigned int*)(X + ((b * H + y) * W + x) * 2) : 0u;
     }
     *(uint4*)(col + i * 8) = make_uint4(v[0], v[1], v[2], v[3]);
-  }
-}
-
-// dX[b][y][x][c] += sum of dcol over the output positions whose patch covers (y, x), for a layer
-// of stride 2 with C input channels and side 2^LW: an even row lies in the patch of one output row
-// (its middle tap), an odd one in those of two. Four channels a thread, indexes by shifts; bound
-// by memory (0.33 GB for both layers of 64 samples: one channel a thread took 212 us, this 73).
-template <int C, int LW>
-__global__ void k_col2im(const float* __restrict__ dcol, int Bn, int ldk, float* __restrict__ dX) {
-  constexpr int W = 1 << LW, Wo = W / 2, C4 = C / 4;
-  const long long total = (long long)Bn * W * W * C4;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int c = 4 * (int)(i % C4);
-    const long long p = i / C4;
-    const int x = (int)p & (W - 1), y = (int)(p >> LW) & (W - 1);
-    const long long b = p >> (2 * LW);
-    f32x4 sum = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (int dy = 1 - (y & 1); dy < 3; dy += 2) {
-      const int oy = (y + 1 - dy) >> 1;
-      if (oy >= Wo) continue;
-      for (int dx = 1 - (x & 1); dx < 3; dx += 2) {
-        const int ox = (x + 1 - dx) >> 1;
-        if (ox >= Wo) continue;
-        sum += *(const f32x4*)(dcol + ((b * Wo + oy) * Wo + ox) * ldk + (dy * 3 + dx) * C + c);
-      }
-    }
-    f32x4* d = (f32x4*)(dX + 4 * i);
-    *d = *d + sum;
   }
 }
 
@@ -1186,7 +1182,7 @@ struct Model {
   int cap_b = 0;
   // activations and workspaces (sized for cap_b)
   bf16 *x0 = nullptr, *a[5] = {nullptr}, *col = nullptr, *dzb = nullptr;
-  float *z = nullptr, *y = nullptr, *dy = nullptr, *dcol = nullptr,
+  float *z = nullptr, *y = nullptr, *dy = nullptr,
         *da[5] = {nullptr}, *part = nullptr, *w6 = nullptr, *w6f = nullptr, *w1 = nullptr;
   double* lpart = nullptr;
   size_t part_floats = 0;
@@ -1221,7 +1217,7 @@ static pprs_status cfail(pprs_status s, const char* fmt, ...) {
                    __LINE__);                                                         \
   } while (0)
 
-static pprs_status gemm(Model& M, bool ak, const bf16* A, int lda, const bf16* B, int ldb,
+static pprs_status gemm(Model& M, const bf16* A, int lda, const bf16* B, int ldb,
                          float* C, int ldc, int Mr, int Nc, int K, int splits) {
   if (Mr % 64 || Nc % 64 || K % 32 || lda % 8 || ldb % 8)
     return cfail(PPRS_EINVAL, "gemm shape %d x %d x %d not tileable", Mr, Nc, K);
@@ -1235,10 +1231,7 @@ static pprs_status gemm(Model& M, bool ak, const bf16* A, int lda, const bf16* B
     out = M.part;
   }
   dim3 grid(Nc / 64, Mr / 64, splits);
-  if (ak)
-    hipLaunchKernelGGL(k_gemm<true>, grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
-  else
-    hipLaunchKernelGGL(k_gemm<false>, grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
+  hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, M.stream, A, lda, B, ldb, out, ldc, K, kps, stride);
   CHK(hipGetLastError());
   if (splits > 1) {
     hipLaunchKernelGGL(k_split_sum, dim3((unsigned)(stride / 64)), dim3(256), 0, M.stream, M.part,
@@ -1272,17 +1265,16 @@ static void define_layers(Model& M) {
 static pprs_status alloc_batch(Model& M, int B) {
   if (B <= M.cap_b) return PPRS_OK;
   void* ptrs[] = {M.x0, M.a[0], M.a[1], M.a[2], M.a[3], M.a[4], M.col, M.dzb,
-                  M.z, M.y, M.dy, M.dcol, M.da[0], M.da[1], M.da[2], M.da[3], M.da[4],
+                  M.z, M.y, M.dy, M.da[0], M.da[1], M.da[2], M.da[3], M.da[4],
                   M.part, M.lpart, M.wflip};
   for (void* p : ptrs)
     if (p) CHK(hipFree(p));
   long long P128 = (long long)B * 128 * 128, P64 = P128 / 4, P32 = P128 / 16, P16 = P128 / 64;
-  long long col_max = 0, z_max = 0, dcol_max = 0;
+  long long col_max = 0, z_max = 0;
   for (int l = 0; l < 5; ++l) {
     long long pix = (long long)B * M.L[l].hout * M.L[l].hout;
     if (l == 0) col_max = pix * M.L[l].kp;  // the first layer's weight gradient
     z_max = std::max(z_max, pix * (long long)M.L[l].cout);
-    if (l == 1 || l == 2) dcol_max = std::max(dcol_max, pix * M.L[l].kp);  // via col2im
   }
   CHK(hipMalloc(&M.x0, sizeof(bf16) * P128 * 2));
   CHK(hipMalloc(&M.a[0], sizeof(bf16) * P64 * 64));
@@ -1298,7 +1290,6 @@ static pprs_status alloc_batch(Model& M, int B) {
   CHK(hipMalloc(&M.z, sizeof(float) * z_max));
   CHK(hipMalloc(&M.y, sizeof(float) * P128 * 2));
   CHK(hipMalloc(&M.dy, sizeof(float) * P128 * 2));
-  CHK(hipMalloc(&M.dcol, sizeof(float) * dcol_max));
   CHK(hipMalloc(&M.da[0], sizeof(float) * P64 * 64));
   CHK(hipMalloc(&M.da[1], sizeof(float) * P32 * 128));
   CHK(hipMalloc(&M.da[2], sizeof(float) * P16 * 256));
@@ -1320,12 +1311,12 @@ static pprs_status alloc_batch(Model& M, int B) {
 // registers a lane; 256 x 128 takes 128 and leaves one wavefront per SIMD: L4 of 511 pairs 435
 // us against 401; 128 x 64 for L5 693 us against 668), and fewer pixels where the batch is small
 // (one pair: L3 is 256 pixels in all; forward of one pair 97 us with 64 pixels, 202 us before).
-template <bool DGRAD, bool FOLD>
+template <bool DGRAD, bool FOLD, bool S2>
 static pprs_status conv_launch(Model& M, const bf16* s0, int c0, const bf16* s1, int c1, int hin,
                                int stride, const bf16* w, int kp, const float* b, int cout,
                                long long pix, void* out, float* out2 = nullptr) {
   const int bn = cout % 128 == 0 ? 128 : 64;
-  const long long unit = FOLD ? pix / 4 : pix;  // pixels that a tile may not straddle
+  const long long unit = FOLD || S2 ? pix / 4 : pix;  // pixels that a tile may not straddle
   if (unit % 64 || c0 % 64 || c1 % 64 || kp % 8 || cout % bn || (hin & (hin - 1)) ||
       (DGRAD && c1 % bn))
     return cfail(PPRS_EINVAL, "convolution of %d + %d to %d channels does not fit its tiles", c0, c1,
@@ -1334,7 +1325,7 @@ static pprs_status conv_launch(Model& M, const bf16* s0, int c0, const bf16* s1,
   while (mt > 1 && (unit % (64 * mt) || pix / (64 * mt) * (cout / bn) < 512)) mt /= 2;
   dim3 grid((unsigned)(pix / (64 * mt)), cout / bn);
 #define CONV(MT, BN)                                                                           \
-  hipLaunchKernelGGL((k_conv_fwd<MT, BN, DGRAD, FOLD>), grid, dim3(256), 0, M.stream, s0, c0, s1, \
+  hipLaunchKernelGGL((k_conv_fwd<MT, BN, DGRAD, FOLD, S2>), grid, dim3(256), 0, M.stream, s0, c0, s1, \
                      c1, hin, stride, w, kp, b, cout, out, out2)
   if (bn == 128) {
     if (mt == 2) CONV(2, 128);
@@ -1360,9 +1351,9 @@ static pprs_status conv_fused(Model& M, int l, int B) {
   const float* b = M.w + y.boff;
   if (l >= 3)
     // folded upsampling: per output parity, 4 C0 + 9 C1 deep (pixels of one parity per tile)
-    return conv_launch<false, true>(M, s0, c0, s1, c1, y.hin, y.stride, M.wfold[l - 3],
+    return conv_launch<false, true, false>(M, s0, c0, s1, c1, y.hin, y.stride, M.wfold[l - 3],
                                     4 * c0 + 9 * c1, b, y.cout, pix, M.a[l]);
-  return conv_launch<false, false>(M, s0, c0, s1, c1, y.hin, y.stride, M.wb + y.woff, y.kp, b,
+  return conv_launch<false, false, false>(M, s0, c0, s1, c1, y.hin, y.stride, M.wb + y.woff, y.kp, b,
                                    y.cout, pix, M.a[l]);
 }
 
@@ -1476,7 +1467,7 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
       hipLaunchKernelGGL(k_im2col2, dim3(grid1d(pix * y.kp / 8)), dim3(kBlock), 0, st, M.x0, B, y.hin, y.hin, y.stride, y.kp, M.col);
       // one 64 x 64 result: the splits alone fill the GPU (64 of them: 129 us for 64 samples)
       int splits = (int)std::max<long long>(1, std::min<long long>(512, pix / 256));
-      s = gemm(M, true, M.dzb, y.cout, M.col, y.kp, M.g + y.woff, y.kp, y.cout, y.kp, (int)pix, splits);
+      s = gemm(M, M.dzb, y.cout, M.col, y.kp, M.g + y.woff, y.kp, y.cout, y.kp, (int)pix, splits);
     }
     if (s != PPRS_OK) return s;
     if (l == 0) break;
@@ -1486,22 +1477,18 @@ static pprs_status backward(Model& M, const float* target, int B, int margin, do
       hipLaunchKernelGGL(k_flip_weights, dim3(grid1d((long long)y.cin * 9 * y.cout)), dim3(kBlock), 0, st, M.wb + y.woff, y.cout, y.cin, y.kp, M.wflip);
       // input [up2(a[l - 1]), a[4 - l]]: u5 = [a4 128, a1 64] at 64^2, u4 = [a3 256, a2 128] at 32^2
       const int up = M.L[l - 1].cout;
-      s = conv_launch<true, false>(M, M.dzb, y.cout, nullptr, up, y.hout, 1, M.wflip, 9 * y.cout,
+      s = conv_launch<true, false, false>(M, M.dzb, y.cout, nullptr, up, y.hout, 1, M.wflip, 9 * y.cout,
                                    nullptr, y.cin, pix, M.da[l - 1], M.da[4 - l]);
       if (s != PPRS_OK) return s;
       CHK(hipGetLastError());
       continue;
     }
-    // data gradient: dcol[pix][k] = sum_co dZ[pix][co] W[co][k]; then col2im into the input
-    s = gemm(M, false, M.dzb, y.cout, M.wb + y.woff, y.kp, M.dcol, y.kp, (int)pix, y.kp, y.cout, 1);
+    // data gradient of the stride-2 layers, added to the skip connection's gradient that a[l - 1]'s
+    // already holds
+    hipLaunchKernelGGL(k_flip_weights, dim3(grid1d((long long)y.cin * 9 * y.cout)), dim3(kBlock), 0, st, M.wb + y.woff, y.cout, y.cin, y.kp, M.wflip);
+    s = conv_launch<false, false, true>(M, M.dzb, y.cout, nullptr, 0, y.hout, 1, M.wflip,
+                                        9 * y.cout, nullptr, y.cin, 4 * pix, M.da[l - 1]);
     if (s != PPRS_OK) return s;
-    if (l == 2) {
-      // input a2 (32^2 x 128), stride 2; a2 already holds the skip gradient from L4
-      hipLaunchKernelGGL((k_col2im<128, 5>), dim3(grid1d((long long)B * 32 * 32 * 32)), dim3(kBlock), 0, st, M.dcol, B, y.kp, M.da[1]);
-    } else if (l == 1) {
-      // input a1 (64^2 x 64), stride 2; a1 already holds the skip gradient from L5
-      hipLaunchKernelGGL((k_col2im<64, 6>), dim3(grid1d((long long)B * 64 * 64 * 16)), dim3(kBlock), 0, st, M.dcol, B, y.kp, M.da[0]);
-    }
     CHK(hipGetLastError());
   }
   CHK(hipStreamSynchronize(st));
@@ -1738,7 +1725,7 @@ void pprs_cnn_destroy(pprs_cnn* c) {
   (void)hipStreamSynchronize(M.stream);
   void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
                   M.a[1], M.a[2], M.a[3],
-                  M.a[4], M.col, M.dzb, M.z, M.y, M.dy, M.dcol, M.da[0],
+                  M.a[4], M.col, M.dzb, M.z, M.y, M.dy, M.da[0],
                   M.da[1], M.da[2], M.da[3], M.da[4], M.part, M.lpart, M.wflip};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
