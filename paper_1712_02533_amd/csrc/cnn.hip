@@ -143,7 +143,7 @@ __device__ __forceinline__ float dpp_f(float v) {
 // the first-level cache bound it).
 // The product is formed transposed (channels as rows), so that a lane ends with 4 consecutive
 // channels of a pixel and stores them together.
-// Requires C0 % 64 == 0, C1 % 64 == 0, BN | Cout (DGRAD: BN | C1), (pixels of a parity) % (64 MT) == 0,
+// Requires C0 % 64 == 0 (S2: 128), C1 % 64 == 0, BN | Cout (DGRAD: BN | C1), (pixels of a parity) % (64 MT) == 0,
 // Kp % 8 == 0, Hin a power of two.
 
 constexpr int CV_BK = 64, CV_LD = CV_BK + 8;
@@ -297,6 +297,13 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  // S2: a tap's products are summed by themselves, the taps' sums then added in order
+  f32x4 taps[S2 ? MT : 1][S2 ? TN : 1];
+  if (S2)
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) taps[S2 ? i : 0][S2 ? j : 0] = (f32x4){0.f, 0.f, 0.f, 0.f};
   // the weights' operands are read two steps ahead (the barriers keep the compiler from reading a
   // whole chunk's at once, which would not leave registers for the accumulators)
   auto multiply = [&](const u32x4 (&fa)[MT][2], int buf) {
@@ -327,6 +334,14 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
     __syncthreads();
     if (chunk + 2 < nchunks) fetch(a[0]);
     multiply(a[1], 1);
+    if (S2 && (chunk + 2) % (C0 / CV_BK) == 0)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          taps[S2 ? i : 0][S2 ? j : 0] += acc[i][j];
+          acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
     stash(0);  // nothing reads it where no chunk follows
     __syncthreads();
   }
@@ -345,15 +360,13 @@ __global__ void __launch_bounds__(256, 2) k_conv_fwd(
       const int col = n0 + 16 * j + 4 * kq;
       if (S2) {
         f32x4* d = (f32x4*)((float*)out_ + row * Cout + col);
-        *d = *d + acc[i][j];
+        *d = *d + taps[S2 ? i : 0][S2 ? j : 0];
       } else if (DGRAD) {
         f32x4 v = acc[i][j];
         if (n0 < C1) {  // uniform: BN divides C1
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            v[r] += dpp_f<0xb1>(v[r]);  // quad_perm 1, 0, 3, 2
-            v[r] += dpp_f<0x4e>(v[r]);  // quad_perm 2, 3, 0, 1
-          }
+          for (int r = 0; r < 4; ++r)  // the quad's first lane: its four values in order
+            v[r] = ((v[r] + dpp_f<0x55>(v[r])) + dpp_f<0xaa>(v[r])) + dpp_f<0xff>(v[r]);
           if ((row16 & 3) == 0) *(f32x4*)((float*)out_ + (row >> 2) * C1 + col) = v;
         } else {
           const long long X = (row >> 2) & (Hm / 2 - 1), Y = (row >> (lh + 1)) & (Hm / 2 - 1);
@@ -1318,22 +1331,25 @@ static pprs_status conv_launch(Model& M, const bf16* s0, int c0, const bf16* s1,
   const int bn = cout % 128 == 0 ? 128 : 64;
   const long long unit = FOLD || S2 ? pix / 4 : pix;  // pixels that a tile may not straddle
   if (unit % 64 || c0 % 64 || c1 % 64 || kp % 8 || cout % bn || (hin & (hin - 1)) ||
-      (DGRAD && c1 % bn))
+      (DGRAD && c1 % bn) || (S2 && c0 % 128))
     return cfail(PPRS_EINVAL, "convolution of %d + %d to %d channels does not fit its tiles", c0, c1,
                  cout);
-  int mt = bn == 128 ? 2 : 4;
+  // S2 keeps a second set of sums in registers, so half the tile
+  int mt = (bn == 128 ? 2 : 4) / (S2 ? 2 : 1);
   while (mt > 1 && (unit % (64 * mt) || pix / (64 * mt) * (cout / bn) < 512)) mt /= 2;
   dim3 grid((unsigned)(pix / (64 * mt)), cout / bn);
 #define CONV(MT, BN)                                                                           \
   hipLaunchKernelGGL((k_conv_fwd<MT, BN, DGRAD, FOLD, S2>), grid, dim3(256), 0, M.stream, s0, c0, s1, \
                      c1, hin, stride, w, kp, b, cout, out, out2)
   if (bn == 128) {
-    if (mt == 2) CONV(2, 128);
-    else CONV(1, 128);
+    if constexpr (!S2)
+      if (mt == 2) CONV(2, 128);
+    if (mt == 1) CONV(1, 128);
   } else {
-    if (mt == 4) CONV(4, 64);
-    else if (mt == 2) CONV(2, 64);
-    else CONV(1, 64);
+    if constexpr (!S2)
+      if (mt == 4) CONV(4, 64);
+    if (mt == 2) CONV(2, 64);
+    else if (mt == 1) CONV(1, 64);
   }
 #undef CONV
   CHK(hipGetLastError());
