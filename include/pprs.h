@@ -125,8 +125,10 @@ void pprs_default_params(pprs_params* p);
 /* Creates a context on HIP device `device`. `stream` is a hipStream_t to order work on, or
    NULL for a blocking stream the context creates and owns (ordered with the legacy default
    stream, as work the caller issues there). The stream must not be the legacy default stream
-   itself: the series step loop is replayed from a captured graph. The context allocates its
-   device workspace lazily and keeps it until pprs_destroy. */
+   itself: every registration call except pprs_register_pair_noalloc replays its steps from
+   graphs launched into the stream. No call puts a stream into capture, so other threads may
+   use and synchronise the device meanwhile. The context allocates its device workspace lazily
+   and keeps it, and the graphs, until pprs_destroy. */
 pprs_status pprs_create(pprs_ctx** ctx, int device, void* stream);
 void pprs_destroy(pprs_ctx* ctx);
 

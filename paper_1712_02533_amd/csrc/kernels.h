@@ -5,20 +5,28 @@
 #include "pprs_internal.h"
 
 namespace pprs_k {
-hipError_t plan(const BatchDesc& d, hipStream_t st);
+// Where the launches of a step go: into a stream, or (graph set) into a graph under construction,
+// one kernel node after the other.
+struct StepTarget {
+  hipStream_t stream = nullptr;
+  hipGraph_t graph = nullptr;
+  hipGraphNode_t last = nullptr;
+};
+hipError_t plan(const BatchDesc& d, StepTarget& to);
 // nc: step sizes per line-search pass (1, 2, 3, 5 or 7; ladder_rungs_ok)
 bool ladder_rungs_ok(int nc);
 // start energies (eval list) and line-search passes (ladder list) of a step in one launch,
 // and their finalisers
-hipError_t energy_step(const BatchDesc& d, int nc, int grid, hipStream_t st);
-hipError_t energy_step_fin(const BatchDesc& d, int nc, int grid, hipStream_t st);
+hipError_t energy_step(const BatchDesc& d, int nc, int grid, StepTarget& to);
+hipError_t energy_step_fin(const BatchDesc& d, int nc, int grid, StepTarget& to);
 // gradient tile variants: 0 = 32x16, 1 = 64x8, 2 = 128x4, 3 = 64x16 nodes
 void grad_tile(int variant, int* tx, int* ty);
-hipError_t grad(const BatchDesc& d, int variant, int grid, hipStream_t st);
-hipError_t smooth(const BatchDesc& d, int dir, bool big, int grid, size_t lds_bytes, hipStream_t st);
+hipError_t grad(const BatchDesc& d, int variant, int grid, StepTarget& to);
+hipError_t smooth(const BatchDesc& d, int dir, bool big, int grid, size_t lds_bytes,
+                  StepTarget& to);
 hipError_t set_smooth_lds(size_t bytes);
 // windowed metric solve (both axes in one launch); halo 16 or 24
-hipError_t smooth_win(const BatchDesc& d, int halo, int grid, hipStream_t st);
+hipError_t smooth_win(const BatchDesc& d, int halo, int grid, StepTarget& to);
 hipError_t restrict_planes(const float* src, long long s_outer, long long s_inner, float* dst,
                            long long d_outer, long long d_inner, int inner, int nf, int planes,
                            hipStream_t st);
@@ -61,9 +69,9 @@ hipError_t from_nodes_idx(const float* vbuf, const long long* offs, int n, float
 // rigid variant: energy passes (mode 0 start, 1 line search with nc steps), gradient, its
 // per-slot finaliser (the energy finalisers are energy_fin's)
 // start energies (eval list) and line-search passes (ladder list) of the rigid slots, one launch
-hipError_t rigid_energy_step(const BatchDesc& d, int nc, int grid, hipStream_t st);
-hipError_t rigid_grad(const BatchDesc& d, int grid, hipStream_t st);
-hipError_t rigid_grad_fin(const BatchDesc& d, int grid, hipStream_t st);
+hipError_t rigid_energy_step(const BatchDesc& d, int nc, int grid, StepTarget& to);
+hipError_t rigid_grad(const BatchDesc& d, int grid, StepTarget& to);
+hipError_t rigid_grad_fin(const BatchDesc& d, int grid, StepTarget& to);
 // avg[H][W] = mean over i of frames[i] sampled at x + u[i](x) (pixels, clamped, bilinear)
 hipError_t series_average(const float* frames, const float* u, int N, int H, int W, float* out,
                           hipStream_t st);

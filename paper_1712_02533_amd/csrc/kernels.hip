@@ -2570,35 +2570,51 @@ static int grid_for(long long work, int cap = 8192) {
   return (int)g;
 }
 
-hipError_t plan(const BatchDesc& d, hipStream_t st) {
-  if (d.n_slots <= 64)
-    hipLaunchKernelGGL(k_plan<64>, dim3(1), dim3(64), 0, st, d);
-  else
-    hipLaunchKernelGGL(k_plan<PLAN_T>, dim3(1), dim3(PLAN_T), 0, st, d);
-  return hipGetLastError();
+// One launch of a step: into the stream, or as the next kernel node of the graph being built.
+static hipError_t step_launch(void (*kernel)(const BatchDesc), int grid, int block, size_t lds,
+                              const BatchDesc& d, StepTarget& to) {
+  if (!to.graph) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, to.stream, d);
+    return hipGetLastError();
+  }
+  void* args[] = {const_cast<BatchDesc*>(&d)};  // copied into the node
+  hipKernelNodeParams p = {};
+  p.func = reinterpret_cast<void*>(kernel);
+  p.gridDim = dim3(grid);
+  p.blockDim = dim3(block);
+  p.sharedMemBytes = (unsigned)lds;
+  p.kernelParams = args;
+  hipGraphNode_t node = nullptr;
+  hipError_t e = hipGraphAddKernelNode(&node, to.graph, to.last ? &to.last : nullptr,
+                                       to.last ? 1 : 0, &p);
+  if (e == hipSuccess) to.last = node;
+  return e;
+}
+
+hipError_t plan(const BatchDesc& d, StepTarget& to) {
+  if (d.n_slots <= 64) return step_launch(k_plan<64>, 1, 64, 0, d, to);
+  return step_launch(k_plan<PLAN_T>, 1, PLAN_T, 0, d, to);
 }
 bool ladder_rungs_ok(int nc) { return nc == 1 || nc == 2 || nc == 3 || nc == 5 || nc == 7; }
-hipError_t energy_step(const BatchDesc& d, int nc, int grid, hipStream_t st) {
+hipError_t energy_step(const BatchDesc& d, int nc, int grid, StepTarget& to) {
   switch (nc) {
-    case 1: hipLaunchKernelGGL((k_energy_step<1>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 2: hipLaunchKernelGGL((k_energy_step<2>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 3: hipLaunchKernelGGL((k_energy_step<3>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 5: hipLaunchKernelGGL((k_energy_step<5>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 7: hipLaunchKernelGGL((k_energy_step<7>), dim3(grid), dim3(BLOCK), 0, st, d); break;
+    case 1: return step_launch(k_energy_step<1>, grid, BLOCK, 0, d, to);
+    case 2: return step_launch(k_energy_step<2>, grid, BLOCK, 0, d, to);
+    case 3: return step_launch(k_energy_step<3>, grid, BLOCK, 0, d, to);
+    case 5: return step_launch(k_energy_step<5>, grid, BLOCK, 0, d, to);
+    case 7: return step_launch(k_energy_step<7>, grid, BLOCK, 0, d, to);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
-hipError_t energy_step_fin(const BatchDesc& d, int nc, int grid, hipStream_t st) {
+hipError_t energy_step_fin(const BatchDesc& d, int nc, int grid, StepTarget& to) {
   switch (nc) {
-    case 1: hipLaunchKernelGGL((k_energy_step_fin<1>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 2: hipLaunchKernelGGL((k_energy_step_fin<2>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 3: hipLaunchKernelGGL((k_energy_step_fin<3>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 5: hipLaunchKernelGGL((k_energy_step_fin<5>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 7: hipLaunchKernelGGL((k_energy_step_fin<7>), dim3(grid), dim3(BLOCK), 0, st, d); break;
+    case 1: return step_launch(k_energy_step_fin<1>, grid, BLOCK, 0, d, to);
+    case 2: return step_launch(k_energy_step_fin<2>, grid, BLOCK, 0, d, to);
+    case 3: return step_launch(k_energy_step_fin<3>, grid, BLOCK, 0, d, to);
+    case 5: return step_launch(k_energy_step_fin<5>, grid, BLOCK, 0, d, to);
+    case 7: return step_launch(k_energy_step_fin<7>, grid, BLOCK, 0, d, to);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 const int kGradTiles[4][2] = {{32, 16}, {64, 8}, {128, 4}, {64, 16}};
 void grad_tile(int variant, int* tx, int* ty) {
@@ -2606,30 +2622,24 @@ void grad_tile(int variant, int* tx, int* ty) {
   *tx = kGradTiles[variant][0];
   *ty = kGradTiles[variant][1];
 }
-hipError_t grad(const BatchDesc& d, int variant, int grid, hipStream_t st) {
+hipError_t grad(const BatchDesc& d, int variant, int grid, StepTarget& to) {
   switch (variant) {
-    case 1: hipLaunchKernelGGL((k_grad<64, 8>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 2: hipLaunchKernelGGL((k_grad<128, 4>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 3: hipLaunchKernelGGL((k_grad<64, 16>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    default: hipLaunchKernelGGL((k_grad<32, 16>), dim3(grid), dim3(BLOCK), 0, st, d); break;
+    case 1: return step_launch(k_grad<64, 8>, grid, BLOCK, 0, d, to);
+    case 2: return step_launch(k_grad<128, 4>, grid, BLOCK, 0, d, to);
+    case 3: return step_launch(k_grad<64, 16>, grid, BLOCK, 0, d, to);
+    default: return step_launch(k_grad<32, 16>, grid, BLOCK, 0, d, to);
   }
-  return hipGetLastError();
 }
-hipError_t smooth(const BatchDesc& d, int dir, bool big, int grid, size_t lds_bytes, hipStream_t st) {
-  if (big) {
-    if (dir == 0) hipLaunchKernelGGL((k_smooth<0, true>), dim3(grid), dim3(SM_THREADS), lds_bytes, st, d);
-    else hipLaunchKernelGGL((k_smooth<1, true>), dim3(grid), dim3(SM_THREADS), lds_bytes, st, d);
-  } else {
-    if (dir == 0) hipLaunchKernelGGL((k_smooth<0, false>), dim3(grid), dim3(SM_THREADS), lds_bytes, st, d);
-    else hipLaunchKernelGGL((k_smooth<1, false>), dim3(grid), dim3(SM_THREADS), lds_bytes, st, d);
-  }
-  return hipGetLastError();
+hipError_t smooth(const BatchDesc& d, int dir, bool big, int grid, size_t lds_bytes,
+                  StepTarget& to) {
+  auto k = big ? (dir == 0 ? k_smooth<0, true> : k_smooth<1, true>)
+               : (dir == 0 ? k_smooth<0, false> : k_smooth<1, false>);
+  return step_launch(k, grid, SM_THREADS, lds_bytes, d, to);
 }
-hipError_t smooth_win(const BatchDesc& d, int halo, int grid, hipStream_t st) {
-  if (halo == 16) hipLaunchKernelGGL(k_smooth_win<16>, dim3(grid), dim3(SW_THREADS), 0, st, d);
-  else if (halo == 24) hipLaunchKernelGGL(k_smooth_win<24>, dim3(grid), dim3(SW_THREADS), 0, st, d);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+hipError_t smooth_win(const BatchDesc& d, int halo, int grid, StepTarget& to) {
+  if (halo == 16) return step_launch(k_smooth_win<16>, grid, SW_THREADS, 0, d, to);
+  if (halo == 24) return step_launch(k_smooth_win<24>, grid, SW_THREADS, 0, d, to);
+  return hipErrorInvalidValue;
 }
 hipError_t set_smooth_lds(size_t bytes) {
   const void* fns[4] = {(const void*)k_smooth<0, false>, (const void*)k_smooth<1, false>,
@@ -2760,24 +2770,21 @@ hipError_t from_nodes_idx(const float* vbuf, const long long* offs, int n, float
   return hipGetLastError();
 }
 
-hipError_t rigid_energy_step(const BatchDesc& d, int nc, int grid, hipStream_t st) {
+hipError_t rigid_energy_step(const BatchDesc& d, int nc, int grid, StepTarget& to) {
   switch (nc) {
-    case 1: hipLaunchKernelGGL((k_rigid_energy_step<1>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 2: hipLaunchKernelGGL((k_rigid_energy_step<2>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 3: hipLaunchKernelGGL((k_rigid_energy_step<3>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 5: hipLaunchKernelGGL((k_rigid_energy_step<5>), dim3(grid), dim3(BLOCK), 0, st, d); break;
-    case 7: hipLaunchKernelGGL((k_rigid_energy_step<7>), dim3(grid), dim3(BLOCK), 0, st, d); break;
+    case 1: return step_launch(k_rigid_energy_step<1>, grid, BLOCK, 0, d, to);
+    case 2: return step_launch(k_rigid_energy_step<2>, grid, BLOCK, 0, d, to);
+    case 3: return step_launch(k_rigid_energy_step<3>, grid, BLOCK, 0, d, to);
+    case 5: return step_launch(k_rigid_energy_step<5>, grid, BLOCK, 0, d, to);
+    case 7: return step_launch(k_rigid_energy_step<7>, grid, BLOCK, 0, d, to);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
-hipError_t rigid_grad(const BatchDesc& d, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_rigid_grad, dim3(grid), dim3(BLOCK), 0, st, d);
-  return hipGetLastError();
+hipError_t rigid_grad(const BatchDesc& d, int grid, StepTarget& to) {
+  return step_launch(k_rigid_grad, grid, BLOCK, 0, d, to);
 }
-hipError_t rigid_grad_fin(const BatchDesc& d, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_rigid_grad_fin, dim3(grid), dim3(BLOCK), 0, st, d);
-  return hipGetLastError();
+hipError_t rigid_grad_fin(const BatchDesc& d, int grid, StepTarget& to) {
+  return step_launch(k_rigid_grad_fin, grid, BLOCK, 0, d, to);
 }
 
 hipError_t series_average(const float* frames, const float* u, int N, int H, int W, float* out,

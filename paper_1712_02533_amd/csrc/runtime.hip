@@ -66,7 +66,7 @@ static pprs_status fail(pprs_status s, const char* fmt, ...) {
 namespace {
 
 const int kGridFin = 512;       // finalisation: one workgroup per listed slot (grid-stride)
-const int kMaxStepGraphs = 32;  // captured step groups a context keeps
+const int kMaxStepGraphs = 32;  // step groups a context keeps as graphs
 const int kPoolSlotsDefault = 512;  // concurrent registrations of a series (pprs_set_pool)
 
 // A device buffer of a context: grown by ensure(), freed with the context unless it is a
@@ -111,7 +111,7 @@ struct StepGrid {
   }
 };
 
-// A captured group of steps: every launch's kernel and arguments follow from these values (the
+// A group of steps as a graph: every launch's kernel and arguments follow from these values (the
 // batch descriptor is an argument of every launch, so all of it counts).
 struct StepGraph {
   StepGrid grid;
@@ -140,7 +140,7 @@ struct pprs_ctx {
   // scan elements [M][2][nL^2] and staging
   DevBuf elems;
   int* active_host = nullptr;        // mapped host word: slots active in the last planned step
-  std::vector<StepGraph> graphs;     // captured step groups (empty where eager is set)
+  std::vector<StepGraph> graphs;     // step groups kept as graphs (none where eager is set)
   bool eager = false;                // launch every step (no graph: nothing is allocated)
   bool log = false;  // one progress line per batch on stderr (environment PPRS_LOG=1)
   pprs_cnn* cnn = nullptr;  // warm start network (not owned)
@@ -641,7 +641,7 @@ SlotItems slot_items(const BatchDesc& hd, int l_stop) {
 
 // Launch grids for a step whose slots have at most these items: the tuned grid, or as many
 // workgroups as there can be items where that is fewer (a power of two of at least 128, which
-// the XCD placement of items needs; few distinct shapes, so few captured graphs). A workgroup
+// the XCD placement of items needs; few distinct shapes, so few graphs). A workgroup
 // without an item still costs its dispatch: 8192 of them 2 us a launch, measured with one 64 x
 // 64 pair (launches of the empty kernels 3.2 us at 8192 workgroups, 1.6 us at 128).
 StepGrid step_grid(const pprs_ctx* c, const SlotItems& items, int slots) {
@@ -658,20 +658,20 @@ StepGrid step_grid(const pprs_ctx* c, const SlotItems& items, int slots) {
 
 // One step of every active slot: plan, gradient (with the prolongations of slots that
 // finished a level), metric solve, line search.
-pprs_status launch_step(pprs_ctx* c, int nc, const StepGrid& g) {
+pprs_status launch_step(pprs_ctx* c, int nc, const StepGrid& g, pprs_k::StepTarget& to) {
   size_t lds0 = c->lds_smooth[0], lds1 = c->lds_smooth[1];
-  TIMED(TK_PLAN, pprs_k::plan(c->hd, c->stream));
-  TIMED(TK_GRAD, pprs_k::grad(c->hd, grad_variant(c->tile_grad), g.grad, c->stream));
+  TIMED(TK_PLAN, pprs_k::plan(c->hd, to));
+  TIMED(TK_GRAD, pprs_k::grad(c->hd, grad_variant(c->tile_grad), g.grad, to));
   if (c->hd.smooth_halo) {
-    TIMED(TK_SMW, pprs_k::smooth_win(c->hd, c->hd.smooth_halo, g.smooth, c->stream));
+    TIMED(TK_SMW, pprs_k::smooth_win(c->hd, c->hd.smooth_halo, g.smooth, to));
   } else {
     bool big = level_n(c->hd.finest) > 9 * 64;  // lines longer than 9 nodes per lane
-    TIMED(TK_SMY, pprs_k::smooth(c->hd, 0, big, g.smooth, lds0, c->stream));
-    TIMED(TK_SMX, pprs_k::smooth(c->hd, 1, big, g.smooth, lds1, c->stream));
+    TIMED(TK_SMY, pprs_k::smooth(c->hd, 0, big, g.smooth, lds0, to));
+    TIMED(TK_SMX, pprs_k::smooth(c->hd, 1, big, g.smooth, lds1, to));
   }
   // start energies of the slots that begin a level and the line-search passes, one launch
-  TIMED(TK_LADDER, pprs_k::energy_step(c->hd, nc, g.energy, c->stream));
-  TIMED(TK_FIN, pprs_k::energy_step_fin(c->hd, nc, g.fin, c->stream));
+  TIMED(TK_LADDER, pprs_k::energy_step(c->hd, nc, g.energy, to));
+  TIMED(TK_FIN, pprs_k::energy_step_fin(c->hd, nc, g.fin, to));
   return PPRS_OK;
 }
 
@@ -679,26 +679,30 @@ pprs_status launch_step(pprs_ctx* c, int nc, const StepGrid& g) {
 // the start energies of the slots that begin a level and the line-search passes (a slot that
 // begins a level iterates from the next step on, as the plan lists it), and the finaliser the
 // field path uses.
-pprs_status launch_step_rigid(pprs_ctx* c, int nc, const StepGrid& g) {
-  TIMED(TK_PLAN, pprs_k::plan(c->hd, c->stream));
-  TIMED(TK_GRAD, pprs_k::rigid_grad(c->hd, g.grad, c->stream));
-  TIMED(TK_FIN, pprs_k::rigid_grad_fin(c->hd, g.fin, c->stream));
+pprs_status launch_step_rigid(pprs_ctx* c, int nc, const StepGrid& g, pprs_k::StepTarget& to) {
+  TIMED(TK_PLAN, pprs_k::plan(c->hd, to));
+  TIMED(TK_GRAD, pprs_k::rigid_grad(c->hd, g.grad, to));
+  TIMED(TK_FIN, pprs_k::rigid_grad_fin(c->hd, g.fin, to));
   // start energies of the slots that begin a level and the line-search passes, one launch
-  TIMED(TK_LADDER, pprs_k::rigid_energy_step(c->hd, nc, g.energy, c->stream));
-  TIMED(TK_FIN, pprs_k::energy_step_fin(c->hd, nc, g.fin, c->stream));
+  TIMED(TK_LADDER, pprs_k::rigid_energy_step(c->hd, nc, g.energy, to));
+  TIMED(TK_FIN, pprs_k::energy_step_fin(c->hd, nc, g.fin, to));
   return PPRS_OK;
 }
 
 // Runs `steps` steps of the context's slots. They always launch the same kernels with the same
-// arguments (all per-slot state lives on the device), so a group is captured once and
+// arguments (all per-slot state lives on the device), so a group is made a graph once and
 // replayed, in this call and in later ones of the same launch shape (a context keeps at most
 // kMaxStepGraphs groups); with per-launch timing events, or in a context that must not
-// allocate, the steps launch one by one.
+// allocate, the steps launch one by one. The graph is built from its kernel nodes, not
+// captured from the stream: during a capture no thread of the program may synchronise the device,
+// nor use the legacy default stream where the captured one is ordered with it.
 pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
   const bool rigid = c->hd.rigid != 0;
+  pprs_k::StepTarget to;
+  to.stream = c->stream;
   auto launch = [&]() -> pprs_status {
     for (int k = 0; k < steps; ++k)
-      STCHK(rigid ? launch_step_rigid(c, nc, g) : launch_step(c, nc, g));
+      STCHK(rigid ? launch_step_rigid(c, nc, g, to) : launch_step(c, nc, g, to));
     return PPRS_OK;
   };
   if (c->timing || c->eager) return launch();
@@ -715,17 +719,12 @@ pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
     for (StepGraph& e : c->graphs) (void)hipGraphExecDestroy(e.exec);
     c->graphs.clear();
   }
-  hipGraph_t graph = nullptr;
-  HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+  HIPCHK(hipGraphCreate(&to.graph, 0));
   pprs_status cs = launch();
-  hipError_t ce = hipStreamEndCapture(c->stream, &graph);
-  if (cs != PPRS_OK) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return cs;
-  }
-  if (ce != hipSuccess) return fail(PPRS_EHIP, "graph capture failed: %s", hipGetErrorString(ce));
-  hipError_t ie = hipGraphInstantiate(&key.exec, graph, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(graph);
+  hipError_t ie = hipSuccess;
+  if (cs == PPRS_OK) ie = hipGraphInstantiate(&key.exec, to.graph, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(to.graph);
+  STCHK(cs);
   if (ie != hipSuccess)
     return fail(PPRS_EHIP, "graph instantiation failed: %s", hipGetErrorString(ie));
   c->graphs.push_back(key);

@@ -599,3 +599,52 @@ def test_pairs_do_not_depend_on_the_batch(count):
         assert torch.equal(u[k], u1[0]), (k, key)
         assert list(st[k].iters) == list(s1[0].iters) and st[k].energy == s1[0].energy
     assert torch.equal(P.register_pairs(frames, ref, tmpl, params=params)[0], u)
+
+
+def test_registrations_beside_another_threads_work_on_the_default_stream():
+    """A program may work on the default stream (launches, synchronisations) in one thread while
+    another registers: neither may be refused or change the other's result. Every call here has
+    parameters of its own, so none finds its step groups ready; each is compared with the same
+    call made alone afterwards."""
+    import threading
+    torch = _torch()
+    import paper_1712_02533_amd as P
+    from dataclasses import replace
+    frames = torch.tensor(make_series(SeriesSpec(5, 64, 3.0, 1.0, 10.0, 78)).frames, device="cuda")
+    base = _gpu_params(2)
+    calls = [replace(base, lam=base.lam * (1.0 + 0.01 * k)) for k in range(24)]
+    stop, failed, rounds = threading.Event(), [], [0]
+
+    def beside():
+        try:
+            a = torch.zeros(1 << 16, device="cuda")
+            while not stop.is_set():
+                for _ in range(20):
+                    a.add_(1.0)
+                torch.cuda.synchronize()
+                rounds[0] += 1
+            assert torch.all(a == 20.0 * rounds[0]).item()
+        except Exception as e:
+            failed.append(e)
+
+    say("24 pairs, rigid pairs and series beside default-stream work")
+
+    def one(p):
+        u, _ = P.register_pair(frames[0], frames[1], params=p)
+        r, _ = P.register_pairs_rigid(frames, [0, 1], [1, 2], params=p)
+        v, _, _ = P.prefix_register_series(frames, params=p)
+        return u, r, v
+
+    th = threading.Thread(target=beside)
+    th.start()
+    try:
+        got = [one(p) for p in calls]
+    finally:
+        stop.set()
+        th.join()
+    assert not failed, failed[0]
+    assert rounds[0] > 0
+    for p, g in zip(calls, got):
+        for x, y in zip(g, one(p)):
+            assert np.array_equal(np.asarray(x.cpu() if hasattr(x, "cpu") else x),
+                                  np.asarray(y.cpu() if hasattr(y, "cpu") else y))
