@@ -66,7 +66,10 @@ static pprs_status fail(pprs_status s, const char* fmt, ...) {
 namespace {
 
 const int kGridFin = 512;       // finalisation: one workgroup per listed slot (grid-stride)
-const int kMaxStepGraphs = 32;  // step groups a context keeps as graphs
+// Step groups a context keeps as graphs (0.15 MB of device memory each for 8 steps, 0.3 MB for 16).
+// A series takes one per distinct grids of its pool as that fills and drains, 4 to 13 of them (24
+// frames of 64 x 64 to 512 of 512 x 512), so several series shapes called in turn find theirs.
+const int kMaxStepGraphs = 64;
 const int kPoolSlotsDefault = 512;  // concurrent registrations of a series (pprs_set_pool)
 
 // A device buffer of a context: grown by ensure(), freed with the context unless it is a
@@ -119,6 +122,7 @@ struct StepGraph {
   int steps, nc, variant;
   size_t lds[2];
   hipGraphExec_t exec;
+  long long used;  // stamp of its last launch (not part of what is compared)
   bool same(const StepGraph& o) const {
     return grid == o.grid && steps == o.steps && nc == o.nc && variant == o.variant &&
            lds[0] == o.lds[0] && lds[1] == o.lds[1] && !memcmp(&desc, &o.desc, sizeof desc);
@@ -141,6 +145,7 @@ struct pprs_ctx {
   DevBuf elems;
   int* active_host = nullptr;        // mapped host word: slots active in the last planned step
   std::vector<StepGraph> graphs;     // step groups kept as graphs (none where eager is set)
+  long long graph_stamp = 0;         // launches of them so far
   bool eager = false;                // launch every step (no graph: nothing is allocated)
   bool log = false;  // one progress line per batch on stderr (environment PPRS_LOG=1)
   pprs_cnn* cnn = nullptr;  // warm start network (not owned)
@@ -643,7 +648,10 @@ SlotItems slot_items(const BatchDesc& hd, int l_stop) {
 // workgroups as there can be items where that is fewer (a power of two of at least 128, which
 // the XCD placement of items needs; few distinct shapes, so few graphs). A workgroup
 // without an item still costs its dispatch: 8192 of them 2 us a launch, measured with one 64 x
-// 64 pair (launches of the empty kernels 3.2 us at 8192 workgroups, 1.6 us at 128).
+// 64 pair (launches of the empty kernels 3.2 us at 8192 workgroups, 1.6 us at 128). The
+// finalisers, a workgroup per slot, follow from the pool's slots and not from those in use: at
+// most 512 workgroups, so little to save and a shape more per halving (24 frames of 64 x 64 at
+// new parameters 11.7 -> 11.1 ms).
 StepGrid step_grid(const pprs_ctx* c, const SlotItems& items, int slots) {
   auto fit = [](int cfg, long long n) {
     long long g = 128;
@@ -691,9 +699,10 @@ pprs_status launch_step_rigid(pprs_ctx* c, int nc, const StepGrid& g, pprs_k::St
 
 // Runs `steps` steps of the context's slots. They always launch the same kernels with the same
 // arguments (all per-slot state lives on the device), so a group is made a graph once and
-// replayed, in this call and in later ones of the same launch shape (a context keeps at most
-// kMaxStepGraphs groups); with per-launch timing events, or in a context that must not
-// allocate, the steps launch one by one. The graph is built from its kernel nodes, not
+// replayed, in this call and in later ones of the same launch shape; a context keeps at most
+// kMaxStepGraphs of them and gives up the least recently used one for a new one (making one takes
+// 0.14 ms). With per-launch timing events, or in a context that must not allocate, the steps
+// launch one by one. The graph is built from its kernel nodes, not
 // captured from the stream: during a capture no thread of the program may synchronise the device,
 // nor use the legacy default stream where the captured one is ordered with it.
 pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
@@ -707,17 +716,21 @@ pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
   };
   if (c->timing || c->eager) return launch();
   StepGraph key{g, c->hd, steps, nc, grad_variant(c->tile_grad),
-                {c->lds_smooth[0], c->lds_smooth[1]}, nullptr};
+                {c->lds_smooth[0], c->lds_smooth[1]}, nullptr, ++c->graph_stamp};
   if (rigid) key.variant = 0, key.lds[0] = key.lds[1] = 0;
-  for (const StepGraph& e : c->graphs)
+  for (StepGraph& e : c->graphs)
     if (e.same(key)) {
+      e.used = key.used;
       HIPCHK(hipGraphLaunch(e.exec, c->stream));
       return PPRS_OK;
     }
   if ((int)c->graphs.size() >= kMaxStepGraphs) {
-    HIPCHK(hipStreamSynchronize(c->stream));
-    for (StepGraph& e : c->graphs) (void)hipGraphExecDestroy(e.exec);
-    c->graphs.clear();
+    auto old = std::min_element(
+        c->graphs.begin(), c->graphs.end(),
+        [](const StepGraph& a, const StepGraph& b) { return a.used < b.used; });
+    HIPCHK(hipStreamSynchronize(c->stream));  // it may still run
+    (void)hipGraphExecDestroy(old->exec);
+    c->graphs.erase(old);
   }
   HIPCHK(hipGraphCreate(&to.graph, 0));
   pprs_status cs = launch();
@@ -728,6 +741,10 @@ pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
   if (ie != hipSuccess)
     return fail(PPRS_EHIP, "graph instantiation failed: %s", hipGetErrorString(ie));
   c->graphs.push_back(key);
+  if (c->log) {
+    fprintf(stderr, "[pprs] %d steps made a graph (%zu kept)\n", steps, c->graphs.size());
+    fflush(stderr);
+  }
   HIPCHK(hipGraphLaunch(key.exec, c->stream));
   return PPRS_OK;
 }
@@ -1267,16 +1284,14 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
     }
     // 2. step every slot G times, on grids for the slots in use
     SlotItems items;
-    int busy = 0;
     for (int s = 0; s < S; ++s) {
       if (slot_op[s] < 0) continue;
       const SlotItems& m = level_items[ops[slot_op[s]].stop_level()];
       items.energy += m.energy;
       items.grad += m.grad;
       items.smooth += m.smooth;
-      ++busy;
     }
-    STCHK(run_steps(c, G, nc, step_grid(c, items, busy)));
+    STCHK(run_steps(c, G, nc, step_grid(c, items, S)));
     done_steps += G;
     // 3. poll: retire finished slots, release their dependents
     HIPCHK(hipMemcpyAsync(st.data(), hd.state, sizeof(SlotState) * S, hipMemcpyDeviceToHost,

@@ -648,3 +648,33 @@ def test_registrations_beside_another_threads_work_on_the_default_stream():
         for x, y in zip(g, one(p)):
             assert np.array_equal(np.asarray(x.cpu() if hasattr(x, "cpu") else x),
                                   np.asarray(y.cpu() if hasattr(y, "cpu") else y))
+
+
+def test_a_launch_shape_in_use_keeps_its_graph(monkeypatch, capfd):
+    """A context keeps a bounded number of step groups as graphs and gives up the least recently
+    used one for a new one. 100 launch shapes (pairs that differ in lambda) pass by beside one
+    that is used every time: each is made a graph once (the context's progress lines count
+    them), and a shape whose graph was given up gives the same bits when it comes back."""
+    torch = _torch()
+    import paper_1712_02533_amd as P
+    from dataclasses import replace
+    frames = torch.tensor(make_series(SeriesSpec(2, 64, 3.0, 1.0, 10.0, 79)).frames, device="cuda")
+    base = _gpu_params(2)
+    other = [replace(base, lam=base.lam * (1.0 + 0.01 * (k + 1))) for k in range(100)]
+    torch.cuda.synchronize()
+    monkeypatch.setenv("PPRS_LOG", "1")
+    with torch.cuda.stream(torch.cuda.Stream()):  # a context of its own
+        pair = lambda p: P.register_pair(frames[0], frames[1], params=p)[0]
+        u0, first = pair(base), []
+        for p in other:
+            first.append(pair(p))
+            assert torch.equal(pair(base), u0)
+        made = capfd.readouterr().err.count("made a graph")
+        again = [pair(p) for p in other[:3]]
+        remade = capfd.readouterr().err.count("made a graph")
+        torch.cuda.synchronize()
+    say("101 launch shapes: %d graphs made, %d of 3 given up made again" % (made, remade))
+    assert made == 101
+    assert remade == 3
+    for a, b in zip(first, again):
+        assert torch.equal(a, b)
