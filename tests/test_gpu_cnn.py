@@ -201,6 +201,54 @@ def test_gradients_of_small_batches(batch):
         assert ew < 5e-2 and eb < 5e-2 and cos > 0.998
 
 
+@pytest.mark.parametrize("batch", [10, 11, 15, 16, 21, 22, 64])
+def test_gradients_where_the_tiles_change(batch):
+    """The data gradients' tiles follow from the batch: those of layer 5 reach their largest from 11
+    samples on, of layer 2 from 16, of layer 4 from 22 (two workgroups per compute unit). Either
+    side of each and a training batch, held to the FP64 reference per layer, bars of the tests
+    above."""
+    torch = _torch()
+    net, p = _net_with_biases(14)
+    rng = np.random.default_rng(batch)
+    x = C.bf16_round(rng.normal(size=(batch, 128, 128, 2)).astype(np.float32))
+    t = rng.normal(0, 1.0, size=(batch, 128, 128, 2)).astype(np.float32)
+    say("gradients B=%d" % batch)
+    loss, g = net.gradients(torch.tensor(x, device="cuda"), torch.tensor(t, device="cuda"),
+                            margin=4)
+    rloss, rg = C.loss_and_grad(_bf16_params(p), x, t, margin=4)
+    assert abs(loss - rloss) < 1e-2 * rloss
+    for l, (w, b) in enumerate(C.layout()[0]):
+        gw, rw = g[w:b], rg[w:b]
+        ew, eb = _rel(gw, rw), _rel(g[b:b + C.COUT[l]], rg[b:b + C.COUT[l]])
+        cos = float(np.dot(gw, rw) / (np.linalg.norm(gw) * np.linalg.norm(rw) + 1e-30))
+        say("B=%d layer %d: weight rel %.3e cos %.6f, bias rel %.3e" % (batch, l + 1, ew, cos, eb))
+        assert ew < 5e-2 and eb < 5e-2 and cos > 0.998
+
+
+@pytest.mark.parametrize("batch", [16, 32, 64])
+def test_gradients_are_the_mean_of_their_parts(batch):
+    """The loss is a mean, so a batch's gradient is the mean of the gradients of its parts of 8
+    samples, which smaller tiles compute. The parts are a power of two in number, so every BF16
+    rounding on the way scales exactly and only the order of the FP32 sums over pixels differs: an
+    accumulator takes fewer than 2^11 additions, 2^-13 of the sum of the magnitudes at worst, and a
+    factor of 8 is left for cancellation: 1e-3 per layer."""
+    torch = _torch()
+    net, _ = _net_with_biases(15)
+    gen = torch.Generator(device="cuda").manual_seed(batch)
+    x = torch.randn((batch, 128, 128, 2), device="cuda", generator=gen)
+    t = torch.randn((batch, 128, 128, 2), device="cuda", generator=gen)
+    say("gradients B=%d and its parts" % batch)
+    loss, g = net.gradients(x, t, margin=4)
+    parts = [net.gradients(x[k:k + 8].contiguous(), t[k:k + 8].contiguous(), margin=4)
+             for k in range(0, batch, 8)]
+    mean = np.mean([q.astype(np.float64) for _, q in parts], axis=0)
+    assert abs(loss - np.mean([v for v, _ in parts])) < 1e-6 * loss
+    for l, (w, b) in enumerate(C.layout()[0]):
+        ew, eb = _rel(g[w:b], mean[w:b]), _rel(g[b:b + C.COUT[l]], mean[b:b + C.COUT[l]])
+        say("B=%d layer %d: weight rel %.3e, bias rel %.3e" % (batch, l + 1, ew, eb))
+        assert ew < 1e-3 and eb < 1e-3
+
+
 def test_train_steps_reduce_loss():
     torch = _torch()
     import paper_1712_02533_amd as P
