@@ -2722,6 +2722,8 @@ hipError_t finish(BatchDesc* d, const int* out_idx, float* elems, long long estr
 
 hipError_t pool_assign(BatchDesc* d, const SlotState* staged, const int* slots, int ops,
                        hipStream_t st) {
+  // the packed upload places the list by its type's alignment
+  if (reinterpret_cast<uintptr_t>(staged) % alignof(SlotState)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_pool_assign, dim3(grid_for((long long)ops * sizeof(SlotState) / 4)),
                      dim3(BLOCK), 0, st, d, staged, slots, ops);
   return hipGetLastError();

@@ -1021,12 +1021,12 @@ struct PoolSpec {
 
 // Bytes of one poll's packed upload for a pool of S slots: at most S finished slots (slot and
 // version offset each), S starting registrations (staged state and slot) and their initial-
-// guess lists (slot, stage index, two version offsets), every list 8-byte aligned, with one
-// list per finest level and one per kind, finest and start level at most.
+// guess lists (slot, stage index, two version offsets), every list 8-byte aligned and the states
+// by their type, with one list per finest level and one per kind, finest and start level at most.
 size_t pool_pack_bytes(int S) {
   const size_t lists = PPRS_MAXL + 2 + 4 * PPRS_MAXL * PPRS_MAXL;
   return (size_t)S * (sizeof(int) + sizeof(long long)) +
-         (size_t)S * (sizeof(SlotState) + sizeof(int)) +
+         (size_t)S * (sizeof(SlotState) + sizeof(int)) + alignof(SlotState) +
          (size_t)S * (2 * sizeof(int) + 2 * sizeof(long long)) + lists * 4 * 8;
 }
 
@@ -1109,8 +1109,10 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
   std::vector<char> hpack(pack_cap);
   size_t pack_used = 0;
   bool pack_over = false;
-  auto put = [&](const void* src, size_t bytes) -> size_t {
-    size_t o = (pack_used + 7) & ~(size_t)7;
+  auto put = [&](const auto* src, int count) -> size_t {
+    constexpr size_t al = std::max<size_t>(8, alignof(decltype(*src)));
+    static_assert(al <= kArenaAlign, "the buffer itself is aligned to this much");
+    const size_t o = (pack_used + al - 1) / al * al, bytes = sizeof(*src) * count;
     if (o + bytes > pack_cap) {
       pack_over = true;
       return 0;
@@ -1217,8 +1219,8 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
     std::vector<InitList> init_lists;
     size_t a_states = 0, a_slots = 0;
     if (na > 0) {
-      a_states = put(h_states.data(), sizeof(SlotState) * na);
-      a_slots = put(a_slot.data(), sizeof(int) * na);
+      a_states = put(h_states.data(), na);
+      a_slots = put(a_slot.data(), na);
       for (int kind : {(int)INIT_IDENTITY, (int)INIT_COMPOSE, (int)INIT_PREPARED,
                        (int)INIT_RESUME}) {
         for (int Lv = m0min; Lv <= Lmax; ++Lv) {
@@ -1239,11 +1241,11 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
               return fail(PPRS_ESTATE, "staged guesses on level %d cannot start level %d",
                           spec.stage_level, lv);
             InitList il{kind, Lv, lv, cnt, 0, 0, 0, 0};
-            il.slots = put(lst.data(), sizeof(int) * cnt);
-            if (kind == INIT_PREPARED) il.stage = put(lst_stage.data(), sizeof(int) * cnt);
+            il.slots = put(lst.data(), cnt);
+            if (kind == INIT_PREPARED) il.stage = put(lst_stage.data(), cnt);
             if (kind == INIT_COMPOSE || kind == INIT_RESUME)
-              il.o0 = put(lst_o0.data(), sizeof(long long) * cnt);
-            if (kind == INIT_COMPOSE) il.o1 = put(lst_o1.data(), sizeof(long long) * cnt);
+              il.o0 = put(lst_o0.data(), cnt);
+            if (kind == INIT_COMPOSE) il.o1 = put(lst_o1.data(), cnt);
             init_lists.push_back(il);
           }
         }
@@ -1349,8 +1351,8 @@ pprs_status run_pool(pprs_ctx* c, std::vector<PoolOp>& ops, int S, float* vbuf,
         }
       if (cnt == 0) continue;
       FinishList f{Lv, cnt, 0, 0};
-      f.slots = put(lst.data(), sizeof(int) * cnt);
-      f.outs = put(lst_o0.data(), sizeof(long long) * cnt);
+      f.slots = put(lst.data(), cnt);
+      f.outs = put(lst_o0.data(), cnt);
       finish_lists.push_back(f);
     }
     for (int s : fin) {

@@ -678,3 +678,22 @@ def test_a_launch_shape_in_use_keeps_its_graph(monkeypatch, capfd):
     assert remade == 3
     for a, b in zip(first, again):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("slots,group", [(5, 3), (4, 1), (1, 2)])
+def test_few_slots_restarted_often_do_not_change_results(slots, group):
+    """Every poll packs the finished slots' lists and the starting registrations' states into one
+    upload, each list at its type's alignment (the library refuses another): few slots polled
+    often, with odd counts of finished slots before the states, give the bits of the default pool."""
+    torch = _torch()
+    import paper_1712_02533_amd as P
+    frames = torch.tensor(make_series(SeriesSpec(12, 64, 3.0, 1.0, 10.0, 80)).frames, device="cuda")
+    params = _gpu_params(2)
+    u1, _, _ = P.prefix_register_series(frames, params=params)
+    try:
+        P.set_pool(slots=slots, group_steps=group)
+        say("12 frames on %d slots, polled every %d steps" % (slots, group))
+        u2, _, _ = P.prefix_register_series(frames, params=params)
+    finally:
+        P.set_pool()
+    assert torch.equal(u1, u2)
