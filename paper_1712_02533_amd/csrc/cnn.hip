@@ -1275,46 +1275,62 @@ static void define_layers(Model& M) {
   M.n_params = off;
 }
 
-static pprs_status alloc_batch(Model& M, int B) {
-  if (B <= M.cap_b) return PPRS_OK;
-  void* ptrs[] = {M.x0, M.a[0], M.a[1], M.a[2], M.a[3], M.a[4], M.col, M.dzb,
-                  M.z, M.y, M.dy, M.da[0], M.da[1], M.da[2], M.da[3], M.da[4],
-                  M.part, M.lpart, M.wflip};
-  for (void* p : ptrs)
-    if (p) CHK(hipFree(p));
-  long long P128 = (long long)B * 128 * 128, P64 = P128 / 4, P32 = P128 / 16, P16 = P128 / 64;
-  long long col_max = 0, z_max = 0;
+// Floats of the partials' buffer for B samples: split-K partials of the weight gradients (<= 64
+// splits of the largest weight) or layer outputs.
+static size_t partial_floats(const Model& M, int B) {
+  long long wmax = 0;
+  for (int l = 0; l < 5; ++l) wmax = std::max(wmax, (long long)M.L[l].cout * M.L[l].kp);
+  return (size_t)std::max(64 * wmax, (long long)B * (64 / L6T) * (64 / L6T) * (2 * 9 * L6C + 2));
+}
+
+// The buffers that follow from the batch, and their sizes for B samples.
+struct BatchBuf {
+  void** p;
+  size_t bytes;
+};
+static std::vector<BatchBuf> batch_bufs(Model& M, int B) {
+  const long long P128 = (long long)B * 128 * 128, P64 = P128 / 4, P32 = P128 / 16, P16 = P128 / 64;
+  long long col_max = 0, z_max = 0, wf = 0;
   for (int l = 0; l < 5; ++l) {
     long long pix = (long long)B * M.L[l].hout * M.L[l].hout;
     if (l == 0) col_max = pix * M.L[l].kp;  // the first layer's weight gradient
     z_max = std::max(z_max, pix * (long long)M.L[l].cout);
   }
-  CHK(hipMalloc(&M.x0, sizeof(bf16) * P128 * 2));
-  CHK(hipMalloc(&M.a[0], sizeof(bf16) * P64 * 64));
-  CHK(hipMalloc(&M.a[1], sizeof(bf16) * P32 * 128));
-  CHK(hipMalloc(&M.a[2], sizeof(bf16) * P16 * 256));
-  CHK(hipMalloc(&M.a[3], sizeof(bf16) * P32 * 128));
-  CHK(hipMalloc(&M.a[4], sizeof(bf16) * P64 * 64));
-  long long wf = 0;
   for (int l = 3; l < 5; ++l) wf = std::max(wf, (long long)M.L[l].cin * 9 * M.L[l].cout);
-  CHK(hipMalloc(&M.wflip, sizeof(bf16) * wf));
-  CHK(hipMalloc(&M.col, sizeof(bf16) * col_max));
-  CHK(hipMalloc(&M.dzb, sizeof(bf16) * z_max));
-  CHK(hipMalloc(&M.z, sizeof(float) * z_max));
-  CHK(hipMalloc(&M.y, sizeof(float) * P128 * 2));
-  CHK(hipMalloc(&M.dy, sizeof(float) * P128 * 2));
-  CHK(hipMalloc(&M.da[0], sizeof(float) * P64 * 64));
-  CHK(hipMalloc(&M.da[1], sizeof(float) * P32 * 128));
-  CHK(hipMalloc(&M.da[2], sizeof(float) * P16 * 256));
-  CHK(hipMalloc(&M.da[3], sizeof(float) * P32 * 128));
-  CHK(hipMalloc(&M.da[4], sizeof(float) * P64 * 64));
-  // split-K partials: weight gradients (<= 64 splits of the largest weight) or layer outputs
-  long long wmax = 0;
-  for (int l = 0; l < 5; ++l) wmax = std::max(wmax, (long long)M.L[l].cout * M.L[l].kp);
-  M.part_floats = (size_t)std::max(64 * wmax, (long long)B * (64 / L6T) * (64 / L6T) *
-                                                  (2 * 9 * L6C + 2));
-  CHK(hipMalloc(&M.part, sizeof(float) * M.part_floats));
-  CHK(hipMalloc(&M.lpart, sizeof(double) * 1024));
+  return {{(void**)&M.x0, sizeof(bf16) * P128 * 2},      {(void**)&M.a[0], sizeof(bf16) * P64 * 64},
+          {(void**)&M.a[1], sizeof(bf16) * P32 * 128},   {(void**)&M.a[2], sizeof(bf16) * P16 * 256},
+          {(void**)&M.a[3], sizeof(bf16) * P32 * 128},   {(void**)&M.a[4], sizeof(bf16) * P64 * 64},
+          {(void**)&M.wflip, sizeof(bf16) * wf},         {(void**)&M.col, sizeof(bf16) * col_max},
+          {(void**)&M.dzb, sizeof(bf16) * z_max},        {(void**)&M.z, sizeof(float) * z_max},
+          {(void**)&M.y, sizeof(float) * P128 * 2},      {(void**)&M.dy, sizeof(float) * P128 * 2},
+          {(void**)&M.da[0], sizeof(float) * P64 * 64},  {(void**)&M.da[1], sizeof(float) * P32 * 128},
+          {(void**)&M.da[2], sizeof(float) * P16 * 256}, {(void**)&M.da[3], sizeof(float) * P32 * 128},
+          {(void**)&M.da[4], sizeof(float) * P64 * 64},  {(void**)&M.part, sizeof(float) * partial_floats(M, B)},
+          {(void**)&M.lpart, sizeof(double) * 1024}};
+}
+static void free_batch(Model& M) {
+  for (const BatchBuf& x : batch_bufs(M, 0)) {
+    if (*x.p) (void)hipFree(*x.p);
+    *x.p = nullptr;
+  }
+  M.cap_b = 0;
+}
+
+// Buffers for B samples. Where they cannot be had the network holds none: no pointer to freed
+// memory stays behind, and the next call allocates what it needs.
+static pprs_status alloc_batch(Model& M, int B) {
+  if (B <= M.cap_b) return PPRS_OK;
+  free_batch(M);
+  for (const BatchBuf& x : batch_bufs(M, B)) {
+    hipError_t e = hipMalloc(x.p, x.bytes);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      *x.p = nullptr;
+      free_batch(M);
+      return cfail(PPRS_EHIP, "hipMalloc(%zu) for %d samples: %s", x.bytes, B, hipGetErrorString(e));
+    }
+  }
+  M.part_floats = partial_floats(M, B);
   M.cap_b = B;
   return PPRS_OK;
 }
@@ -1726,7 +1742,8 @@ pprs_status pprs_cnn_create(pprs_cnn** out, int device, void* stream, unsigned l
     e = hipMalloc(&M.wfold[l - 3], sizeof(bf16) * 4 * M.L[l].cout * (4 * c0 + 9 * c1));
   }
   if (e != hipSuccess) {
-    delete c;
+    (void)hipGetLastError();
+    pprs_cnn_destroy(c);
     return cfail(PPRS_ENOMEM, "cnn allocation failed");
   }
   *out = c;
@@ -1739,10 +1756,8 @@ void pprs_cnn_destroy(pprs_cnn* c) {
   Model& M = c->M;
   (void)hipSetDevice(M.device);
   (void)hipStreamSynchronize(M.stream);
-  void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6, M.w6f, M.wfold[0], M.wfold[1], M.x0, M.a[0],
-                  M.a[1], M.a[2], M.a[3],
-                  M.a[4], M.col, M.dzb, M.z, M.y, M.dy, M.da[0],
-                  M.da[1], M.da[2], M.da[3], M.da[4], M.part, M.lpart, M.wflip};
+  free_batch(M);
+  void* ptrs[] = {M.w, M.m, M.v, M.g, M.wb, M.w1, M.w6, M.w6f, M.wfold[0], M.wfold[1]};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   delete c;

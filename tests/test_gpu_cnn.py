@@ -311,6 +311,28 @@ def test_level7_targets_match_reference():
     assert err < 1e-4
 
 
+def test_a_batch_too_large_for_the_memory_leaves_the_network_usable():
+    """Buffers for 2^26 samples (4.4 TB for the input alone) cannot be had: the call is refused by
+    the first allocation, the network then holds no buffers, and the next forward pass and
+    gradients allocate theirs and give the bits they gave before."""
+    torch = _torch()
+    from paper_1712_02533_amd import api
+    net, _ = _net_with_biases(16)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((3, 128, 128, 2), device="cuda", generator=g)
+    t = torch.randn((3, 128, 128, 2), device="cuda", generator=g)
+    y, (loss, grad) = net.forward(x), net.gradients(x, t)
+    out = torch.empty_like(x)
+    for _ in range(2):
+        status = api._lib().pprs_cnn_forward(net.handle, x.data_ptr(), 1 << 26, out.data_ptr())
+        say("forward of 2^26 samples: status", status, api._lib().pprs_cnn_last_error().decode())
+        assert status == -3  # PPRS_EHIP
+    assert torch.equal(net.forward(x[:2].contiguous()), y[:2])
+    assert torch.equal(net.forward(x), y)
+    loss2, grad2 = net.gradients(x, t)
+    assert loss2 == loss and np.array_equal(grad2, grad)
+
+
 def test_bad_arguments_raise():
     torch = _torch()
     import paper_1712_02533_amd as P
