@@ -1195,7 +1195,7 @@ struct Model {
   int cap_b = 0;
   // activations and workspaces (sized for cap_b)
   bf16 *x0 = nullptr, *a[5] = {nullptr}, *col = nullptr, *dzb = nullptr;
-  float *z = nullptr, *y = nullptr, *dy = nullptr,
+  float *y = nullptr, *dy = nullptr,
         *da[5] = {nullptr}, *part = nullptr, *w6 = nullptr, *w6f = nullptr, *w1 = nullptr;
   double* lpart = nullptr;
   size_t part_floats = 0;
@@ -1275,8 +1275,11 @@ static void define_layers(Model& M) {
   M.n_params = off;
 }
 
-// Floats of the partials' buffer for B samples: split-K partials of the weight gradients (<= 64
-// splits of the largest weight) or layer outputs.
+// Floats of the partials' buffer for B samples, one user at a time: k_wgrad's pixel shares (up to
+// 512 workgroups of 64 x 64 x 9 results, 19 M floats; wgrad takes no more shares than fit), the
+// first layer's GEMM (512 splits of 64 x 64), k_relu_bwd's column sums (1024 x 256) and k_l6_bwd_w's
+// (one record per workgroup, the only one that grows with the batch). 64 times the largest weight, 28
+// M floats, holds the first three.
 static size_t partial_floats(const Model& M, int B) {
   long long wmax = 0;
   for (int l = 0; l < 5; ++l) wmax = std::max(wmax, (long long)M.L[l].cout * M.L[l].kp);
@@ -1301,11 +1304,11 @@ static std::vector<BatchBuf> batch_bufs(Model& M, int B) {
           {(void**)&M.a[1], sizeof(bf16) * P32 * 128},   {(void**)&M.a[2], sizeof(bf16) * P16 * 256},
           {(void**)&M.a[3], sizeof(bf16) * P32 * 128},   {(void**)&M.a[4], sizeof(bf16) * P64 * 64},
           {(void**)&M.wflip, sizeof(bf16) * wf},         {(void**)&M.col, sizeof(bf16) * col_max},
-          {(void**)&M.dzb, sizeof(bf16) * z_max},        {(void**)&M.z, sizeof(float) * z_max},
-          {(void**)&M.y, sizeof(float) * P128 * 2},      {(void**)&M.dy, sizeof(float) * P128 * 2},
-          {(void**)&M.da[0], sizeof(float) * P64 * 64},  {(void**)&M.da[1], sizeof(float) * P32 * 128},
-          {(void**)&M.da[2], sizeof(float) * P16 * 256}, {(void**)&M.da[3], sizeof(float) * P32 * 128},
-          {(void**)&M.da[4], sizeof(float) * P64 * 64},  {(void**)&M.part, sizeof(float) * partial_floats(M, B)},
+          {(void**)&M.dzb, sizeof(bf16) * z_max},        {(void**)&M.y, sizeof(float) * P128 * 2},
+          {(void**)&M.dy, sizeof(float) * P128 * 2},     {(void**)&M.da[0], sizeof(float) * P64 * 64},
+          {(void**)&M.da[1], sizeof(float) * P32 * 128}, {(void**)&M.da[2], sizeof(float) * P16 * 256},
+          {(void**)&M.da[3], sizeof(float) * P32 * 128}, {(void**)&M.da[4], sizeof(float) * P64 * 64},
+          {(void**)&M.part, sizeof(float) * partial_floats(M, B)},
           {(void**)&M.lpart, sizeof(double) * 1024}};
 }
 static void free_batch(Model& M) {

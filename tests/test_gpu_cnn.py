@@ -333,6 +333,44 @@ def test_a_batch_too_large_for_the_memory_leaves_the_network_usable():
     assert loss2 == loss and np.array_equal(grad2, grad)
 
 
+def test_network_holds_the_buffers_it_uses():
+    """Device memory that a network takes for a batch: the activations, the gradients' columns, dZ
+    and data gradients, input, output and loss gradient, partials and flipped weights, each
+    rounded up to the allocator's pages (2 MiB) at most."""
+    torch = _torch()
+    import paper_1712_02533_amd as P
+    net, B = P.WarmStartNet(seed=17), 192
+    x = torch.zeros((B, 128, 128, 2), device="cuda")
+    y1 = net.forward(x[:1].contiguous())  # code objects and the runtime's own pools
+    net = P.WarmStartNet(seed=17)
+    net.forward(x[:1].contiguous())
+    torch.cuda.synchronize()
+    y = torch.empty_like(x)
+    free0 = torch.cuda.mem_get_info()[0]
+    one = _buffer_bytes(1)
+    from paper_1712_02533_amd import api
+    assert api._lib().pprs_cnn_forward(net.handle, x.data_ptr(), B, y.data_ptr()) == 0
+    torch.cuda.synchronize()
+    taken = free0 - torch.cuda.mem_get_info()[0]
+    need = _buffer_bytes(B)
+    say("%d samples take %.1f MB more than one, the buffers need %.1f"
+        % (B, taken / 1e6, (sum(need) - sum(one)) / 1e6))
+    assert taken <= sum(need) - sum(one) + len(need) * (2 << 20)
+    assert torch.equal(y[:1], y1)
+
+
+def _buffer_bytes(B):
+    pix = [64 * 64, 32 * 32, 16 * 16, 32 * 32, 64 * 64]  # outputs of layers 1 to 5
+    acts = [B * p * c for p, c in zip(pix, C.COUT)]
+    image = B * 128 * 128 * 2
+    wmax = max(C.COUT[l] * C.kp(l) for l in range(5))
+    part = max(64 * wmax, B * 16 * (2 * 9 * 66 + 2))
+    return ([2 * a for a in acts] + [4 * a for a in acts] +   # activations and their gradients
+            [2 * image, 4 * image, 4 * image] +               # input, output, its gradient
+            [2 * max(acts), 2 * B * pix[0] * C.kp(0),         # dZ; columns of layer 1
+             2 * 384 * 9 * 128, 4 * part, 8 * 1024])
+
+
 def test_bad_arguments_raise():
     torch = _torch()
     import paper_1712_02533_amd as P
