@@ -752,6 +752,20 @@ __device__ __forceinline__ double ladder_top(double step_cap, int n, double dmax
   return fmin(ldexp(tau_prev, ladder_k), *tau_max);
 }
 
+// Begins the line search along a slot's direction (G.d and max |d| in st), or ends the level
+// where there is none or its first step would already be below tau_min_rel tau_max.
+__device__ __forceinline__ void begin_ladder(SlotState& st, int n, double step_cap, int ladder_k,
+                                             double tau_min_rel) {
+  if (!(st.gtd > 0.0) || !(st.dmax > 0.0)) {
+    level_done(st);
+    return;
+  }
+  st.top = ladder_top(step_cap, n, st.dmax, st.tau_prev, ladder_k, &st.tau_max);
+  st.rung = 0;
+  if (st.top < tau_min_rel * st.tau_max) level_done(st);
+  else st.phase = PH_LADDER;
+}
+
 // Finalisation of the metric solve: G.d, max |d|, step bound and first ladder step (st is the
 // register copy of the slot's scalars).
 __device__ __forceinline__ void smooth_finalize(const BatchDesc* D, SlotState& st, int s, int n,
@@ -764,15 +778,7 @@ __device__ __forceinline__ void smooth_finalize(const BatchDesc* D, SlotState& s
   st.tau_pend = 0.0;
   st.gtd = gtd;
   st.dmax = dmax;
-  if (!(gtd > 0.0) || !(dmax > 0.0)) {
-    level_done(st);
-  } else {
-    st.top = ladder_top(fo.step_cap, n, dmax, st.tau_prev, fo.ladder_k, &st.tau_max);
-    st.rung = 0;
-    // a line search whose first step is already below tau_min_rel * tau_max is not begun
-    if (st.top < fo.tau_min_rel * st.tau_max) level_done(st);
-    else st.phase = PH_LADDER;
-  }
+  begin_ladder(st, n, fo.step_cap, fo.ladder_k, fo.tau_min_rel);
 }
 
 // Works on a register copy of the slot's scalar fields (loaded together up front, stored back
@@ -932,8 +938,8 @@ __device__ __forceinline__ float dmax_reduce(float m) {
 // MODE 0).
 // A slot whose direction the metric solve of this step has just written (still in GRAD: its
 // state moves on in the finaliser after this pass) takes its first step size from the solve's
-// partials here, tile by tile: the first wavefront reduces them (2 (n + 15) / 16 values, loaded
-// with the tile's) and leaves the step sizes in s_tau. A launch between the solve and this pass
+// partials here, tile by tile: the first wavefront reduces them (one per row strip or window and
+// component: 66 at 513 nodes in 16-line strips, loaded with the tile's) and leaves the step sizes in s_tau. A launch between the solve and this pass
 // cost 4.6 us of every step; reducing in all four wavefronts cost the pass 6%.
 template <int MODE, int NC>
 __device__ __forceinline__ void energy_item(const BatchDesc* D, int s, int t, float* s_ux, float* s_uy,
@@ -2494,16 +2500,7 @@ __global__ void __launch_bounds__(BLOCK) k_rigid_grad_fin(const BatchDesc Dv) {
         }
       st.gtd = tot[0] * tot[0] + tot[1] * tot[1] + tot[2] * tot[2];
       st.dmax = dm;
-      if (!(st.gtd > 0.0) || !(st.dmax > 0.0)) {
-        level_done(st);
-      } else {
-        double hh = 1.0 / (n - 1);
-        st.tau_max = D->step_cap * hh / st.dmax;
-        st.top = fmin(ldexp(st.tau_prev, D->ladder_k), st.tau_max);
-        st.rung = 0;
-        if (st.top < D->tau_min_rel * st.tau_max) level_done(st);
-        else st.phase = PH_LADDER;
-      }
+      begin_ladder(st, n, D->step_cap, D->ladder_k, D->tau_min_rel);
       next_frames(D, st);
       store_head(*stp, st);
     }

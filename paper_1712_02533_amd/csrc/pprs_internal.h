@@ -94,7 +94,6 @@ struct ListEntry {
 };
 #define LIST_PAD 66
 
-// Everything the per-step kernels need; lives in device memory, pointers fixed per context.
 // Row pitch (floats) of a level's gradient and metric-solve buffers: rows start on 128-byte
 // lines, so the column-strip solve reads and writes whole lines instead of straddling two.
 #define WPAD 32
@@ -102,6 +101,8 @@ __host__ __device__ inline int row_pitch(int n) { return (n + WPAD - 1) / WPAD *
 // Entries per coefficient array of a level's line solves: n rounded up to whole 64-lane chunks.
 __host__ __device__ inline int coef_pitch(int n) { return (n + 63) / 64 * 64; }
 
+// Everything the kernels of a run need. The host fills it per run (the buffers' addresses are the
+// context's); the step kernels take it by value, the setup kernels read its copy in device memory.
 struct BatchDesc {
   int n_slots;
   int finest;
