@@ -145,7 +145,9 @@ pprs_status pprs_workspace_query(int N, int H, int W, const pprs_params* params,
 /* Allocates on ctx the workspace pprs_workspace_query describes (for ctx's pool shape), so that
    a later pprs_prefix_register_series call of that size allocates nothing more. */
 pprs_status pprs_reserve_workspace(pprs_ctx* ctx, int N, int H, int W, const pprs_params* params);
-/* Device memory (bytes) ctx holds right now in its workspace buffers (host pointer). */
+/* Device memory (bytes) ctx holds right now in its workspace buffers (host pointer). The graphs of
+   steps it keeps (at most 64, 0.15 to 0.3 MB each at the default pool_group) are the runtime's and
+   not counted, here or in pprs_workspace_query. */
 pprs_status pprs_workspace_bytes(pprs_ctx* ctx, size_t* bytes);
 
 /* Function A: registers f_tmpl to f_ref (reference f_i, template f_k: f_k o phi ~ f_i).

@@ -1,5 +1,6 @@
-// Launch wrappers of the HIP kernels (kernels.hip). All take the context stream. The step kernels
-// get the batch descriptor as an argument; the setup kernels read its copy in device memory.
+// Launch wrappers of the HIP kernels (kernels.hip). The step kernels go into a stream or a graph
+// (StepTarget) and get the batch descriptor as an argument; the others take the context stream, and
+// the setup kernels read the descriptor's copy in device memory.
 #pragma once
 #include <hip/hip_runtime.h>
 #include "pprs_internal.h"
