@@ -68,8 +68,9 @@ namespace {
 const int kGridFin = 512;       // finalisation: one workgroup per listed slot (grid-stride)
 // Step groups a context keeps as graphs (0.15 MB of device memory each for 8 steps, 0.3 MB for 16).
 // A series takes one per distinct grids of its pool as that fills and drains, 4 to 13 of them (24
-// frames of 64 x 64 to 512 of 512 x 512), so several series shapes called in turn find theirs.
-const int kMaxStepGraphs = 64;
+// frames of 64 x 64 to 512 of 512 x 512), so several series shapes called in turn find theirs. Groups
+// of more steps than the default count for as much more (1024 steps: 8 MB), or are the only one kept.
+const int kMaxStepGraphs = 64, kMaxGraphSteps = 1024;
 const int kPoolSlotsDefault = 512;  // concurrent registrations of a series (pprs_set_pool)
 
 // A device buffer of a context: grown by ensure(), freed with the context unless it is a
@@ -700,11 +701,11 @@ pprs_status launch_step_rigid(pprs_ctx* c, int nc, const StepGrid& g, pprs_k::St
 // Runs `steps` steps of the context's slots. They always launch the same kernels with the same
 // arguments (all per-slot state lives on the device), so a group is made a graph once and
 // replayed, in this call and in later ones of the same launch shape; a context keeps at most
-// kMaxStepGraphs of them and gives up the least recently used one for a new one (making one takes
+// kMaxStepGraphs of them and gives up the least recently used for a new one (making one takes
 // 0.14 ms). With per-launch timing events, or in a context that must not allocate, the steps
-// launch one by one. The graph is built from its kernel nodes, not
-// captured from the stream: during a capture no thread of the program may synchronise the device,
-// nor use the legacy default stream where the captured one is ordered with it.
+// launch one by one. The graph is built from its kernel nodes, not captured from the stream: during
+// a capture no thread of the program may synchronise the device, nor use the legacy default stream
+// where the captured one is ordered with it.
 pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
   const bool rigid = c->hd.rigid != 0;
   pprs_k::StepTarget to;
@@ -724,7 +725,13 @@ pprs_status run_steps(pprs_ctx* c, int steps, int nc, const StepGrid& g) {
       HIPCHK(hipGraphLaunch(e.exec, c->stream));
       return PPRS_OK;
     }
-  if ((int)c->graphs.size() >= kMaxStepGraphs) {
+  auto kept = [&] {
+    long long n = 0;
+    for (const StepGraph& e : c->graphs) n += e.steps;
+    return n;
+  };
+  while (!c->graphs.empty() &&
+         ((int)c->graphs.size() >= kMaxStepGraphs || kept() + steps > kMaxGraphSteps)) {
     auto old = std::min_element(
         c->graphs.begin(), c->graphs.end(),
         [](const StepGraph& a, const StepGraph& b) { return a.used < b.used; });

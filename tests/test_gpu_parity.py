@@ -697,3 +697,30 @@ def test_few_slots_restarted_often_do_not_change_results(slots, group):
     finally:
         P.set_pool()
     assert torch.equal(u1, u2)
+
+
+def test_long_step_groups_keep_few_graphs():
+    """pool_group may be up to 1024 steps, and a step group's graph grows with it: the graphs a
+    context keeps hold 1024 steps together, or one group. Series at new parameters on such groups,
+    each a shape of its own, give the default pool's bits, and the device memory that they leave
+    behind stays within a few groups' (8 MB each), not one per shape."""
+    torch = _torch()
+    import paper_1712_02533_amd as P
+    from dataclasses import replace
+    frames = torch.tensor(make_series(SeriesSpec(3, 64, 3.0, 1.0, 10.0, 81)).frames, device="cuda")
+    base = _gpu_params(2)
+    calls = [replace(base, lam=base.lam * (1.0 + 0.01 * k)) for k in range(24)]
+    want = [P.prefix_register_series(frames, params=p)[0] for p in calls]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):  # a context of its own
+        P.set_pool(group_steps=1024)
+        say("24 series at groups of 1024 steps")
+        assert torch.equal(P.prefix_register_series(frames, params=calls[0])[0], want[0])
+        torch.cuda.synchronize()
+        free0 = torch.cuda.mem_get_info()[0]
+        for p, u in zip(calls[1:], want[1:]):
+            assert torch.equal(P.prefix_register_series(frames, params=p)[0], u)
+        torch.cuda.synchronize()
+        left = free0 - torch.cuda.mem_get_info()[0]
+    say("  device memory left behind: %.1f MB" % (left / 1e6))
+    assert left < 100e6
